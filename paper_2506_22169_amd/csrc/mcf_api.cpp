@@ -224,7 +224,12 @@ static int run(const mcf_problem *p_in, int softmax, float scale, const void *A,
     k.m_tiles = (int32_t)m_tiles;
     k.h_tiles = (int32_t)h_tiles;
     k.n_blocks = (int32_t)(p->batch * m_tiles * h_tiles);
-    division_magic((uint32_t)m_tiles, &k.m_magic, &k.m_shift);
+    // Longest first pays where blocks wait for a compute unit; where each has one of its own from the
+    // start, the order that keeps a batch within one L2 is 4-7 % faster (15 x 757 x 757, K = L = 64,
+    // 180 blocks: 9.8 against 10.5 us; 125 x 128 x 128, 250 blocks: 5.0 against 5.2 us).
+    k.lpt = causal && k.n_blocks > kComputeUnits;
+    k.divisor = (int32_t)(k.lpt ? p->batch : m_tiles * h_tiles);
+    division_magic((uint32_t)k.divisor, &k.d_magic, &k.d_shift);
     division_magic((uint32_t)h_tiles, &k.h_magic, &k.h_shift);
     k.c1 = 1.0f; k.a_mode = 0;
     k.k_chunks = (int32_t)(p->K / v->K);

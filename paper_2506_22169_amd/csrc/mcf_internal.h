@@ -25,10 +25,13 @@ struct KParams {
     int32_t n_blocks;   // batch * m_tiles * h_tiles
     int32_t m_tiles;    // ceil(M / T_M)
     int32_t h_tiles;    // L / T_L: column tiles of E, each a block of its own (1 when T_L = L)
-    // floor(n / m_tiles) = umulhi(n, m_magic) >> m_shift for 0 <= n < 2^31 (m_magic = 0: m_tiles = 1);
+    // divisor of the block index: the blocks of a batch (m_tiles * h_tiles) or, with lpt, the batches
+    int32_t divisor;
+    // floor(n / divisor) = umulhi(n, d_magic) >> d_shift for 0 <= n < 2^31 (d_magic = 0: divisor = 1);
     // the same for h_tiles.  Saves the blocks an integer division each before their first load.
-    uint32_t m_magic, h_magic;
-    int32_t m_shift, h_shift;
+    uint32_t d_magic, h_magic;
+    int32_t d_shift, h_shift;
+    int32_t lpt;        // causal mask: 1 = longest blocks first over all batches, 0 = batch by batch
     int32_t M, N;
     int32_t a_mode;     // 0: A as is, 1: -A (negative scale), 2: A := 0 (scale == 0)
     int32_t k_chunks;   // kernels with a k loop: K / T_K (otherwise unused)

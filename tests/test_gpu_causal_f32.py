@@ -65,6 +65,17 @@ def test_causal_offsets(off):
         assert torch.equal(mcf.causal_softmax_gemm_chain(A, B, D, w.scale, causal_offset=off), mcf.softmax_gemm_chain(A, B, D, w.scale))
 
 
+@pytest.mark.parametrize("batch,M,N,L,tiles", [(7, 1300, 1300, 64, (1, 1, 4, 1)), (7, 1300, 700, 128, (1, 1, 4, 1, 64)),
+                                               (1, 8225, 96, 64, (1, 1, 4, 1)), (257, 33, 40, 64, (1, 4, 1, 1))])
+def test_causal_more_blocks_than_compute_units(batch, M, N, L, tiles):
+    """More than 256 blocks: they are handed out longest first over all batches (287 blocks, a ragged last
+    m-tile; two h tiles for each; a single batch; a single m-tile)."""
+    w = mi.make_problem(batch, M, L, N, L, "f16", True, "normal", seed=8300 + M)
+    x = mi.make_inputs(w)
+    print(f"case causal blocks {batch}x{M}x{N} L={L} tiles={tiles}", flush=True)
+    _check_causal(w, x, N - M, tiles)
+
+
 def test_causal_full_size_attention():
     """The short attention workload (96 heads, seq 512, head 64) under the lower-triangle mask,
     every element; and every tile arrangement at that size."""
