@@ -142,7 +142,12 @@ template <int N> static __device__ __forceinline__ void wait_vm() {
 template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD> constexpr int waves_per_simd() {
     constexpr int extra = PD > 0 ? chain3_f_bytes(LD, PD) + 1024 : 0;
     if (pipe_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, extra) > 0) return pipe_waves_per_simd(KD, LD, MB, RG, NS, NJ, extra);
-    return RG * NS >= 4 ? RG * NS / 4 : 1;
+    constexpr int per_block = RG * NS >= 4 ? RG * NS / 4 : 1;
+    // a k loop: half the register file at most where the tiles a lane must hold leave it 150 registers for the
+    // operands and load offsets (with all of it the compiler keeps accumulators in the accumulation half
+    // and moves them out and back; with fewer left it spills)
+    if (KSPLIT && MB * h_blocks(LD) * 16 + NJ * MB * (16 + 8) + 150 <= 256) return per_block > 2 ? per_block : 2;
+    return per_block;
 }
 template <typename T, int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool BKC, bool KSPLIT = false, int PD = 0>
 __global__ __launch_bounds__(64 * RG * NS) __attribute__((amdgpu_waves_per_eu(waves_per_simd<KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD>())))
@@ -451,7 +456,8 @@ void chain_kernel(const KParams p) {
         for (int t = 0; t < n_pre; ++t) issue_tile(t, t);
     }
 
-    // ---- L_A: A tile (or chunk) in LDS -> registers, as the second MFMA operand A^T[k][m] ---
+    // ---- L_A: A tile in LDS -> registers, as the second MFMA operand A^T[k][m] (with a k loop the
+    //      operands of a chunk are fetched step by step in the loop) ---
     // a_mode (softmax only: a negative or zero scale) as two masks, so that a kernel with a k
     // loop, which runs this once per chunk, pays two operations per register and a plain chain none.
     v8 a[MB][KS];
@@ -568,16 +574,14 @@ void chain_kernel(const KParams p) {
     v8 dop[T2];          // D operands of GEMM 2
 
     // ---- C_C: C^T[n][m] = sum_k B^T[n][k] A^T[k][m], NJ independent 32-column slices -------
-    auto phase_g1 = [&](unsigned slot_off, bool first = true) __attribute__((always_inline)) {
+    auto phase_g1 = [&](unsigned slot_off) __attribute__((always_inline)) {
         set_b_slot(slot_off);
-        if (first) { // with a k loop: the first chunk of an n-tile
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) accC[j][mb][r] = 0.f;
-        }
+                for (int r = 0; r < 16; ++r) accC[j][mb][r] = 0.f;
         v8 bop[T1];
 #pragma unroll
         for (int t = 0; t < PF && t < T1; ++t) bop[t] = load_b(t / KS, t % KS);
@@ -673,36 +677,113 @@ void chain_kernel(const KParams p) {
     // share the SIMDs pairwise) a phase apart, see below.
     constexpr bool SKEW = skewed_groups(RG, NS, SOFTMAX, KSPLIT);
     if constexpr (KSPLIT) {
-        // One ring item per iteration: the k steps of an n-tile accumulate C^T, its D item turns
-        // C^T into P^T and feeds GEMM 2.  Same protocol as below: one barrier per item, loads
-        // S-1 items ahead.
+        // The k steps of an n-tile accumulate C^T, one ring item each, and its D item turns C^T into
+        // P^T and feeds GEMM 2.  What bounds this loop on the shapes that need it (few blocks, one or
+        // two waves on a SIMD) is the chain of latencies within a wave, so the item after the one in
+        // hand is always complete already (where the ring has the depth for it) and the
+        // operands of its first steps are fetched behind the last MFMAs of this one.  The loops are
+        // nested as the tiling expression is: with the D item as a branch inside one loop over the items the
+        // compiler moved every accumulator between the two halves of the register file once an item.
+        // Measured per item of 24 KiB (A chunk 32 x 128, B chunk 128 x 64; two waves, L = 128): 0.87 -> 0.38 us,
+        // of which the direct loads alone take about as long as the MFMAs; 40 KiB, four waves: 1.05 -> 0.51 us.
+        constexpr bool AHEAD = S >= 3;
+        constexpr int LIVE = AHEAD ? 2 : 1; // complete items at the top of an iteration
+        constexpr int KPF = 3 < KS ? 3 : KS; // steps the operands are fetched ahead
         const int NI = KC + 1;
-        int stage_c = 0, stage_l = S - 1;
+        int stage_c = 0, stage_l = n_pre % S; // slot of the item in hand, slot of the next one requested
         int lt = n_pre / NI, lr = n_pre % NI; // next item to request
-        int ct = 0, cr = 0;                   // item being consumed
-        for (int q = 0; q < n_items; ++q) {
-            if (n_items - q >= S - 1) wait_vm<(S - 2) * P>();
+        int left = n_items;                   // items from the one in hand on
+        auto top = [&]() __attribute__((always_inline)) {
+            // S-1 items have been requested from this one on (fewer near the end): all but the LIVE oldest may be in flight
+            if (left >= S - 1) wait_vm<(S - 1 - LIVE) * P>();
             else wait_vm<0>();
-            __syncthreads(); // item q is complete for every wave; the slot of item q-1 is free
-            if (q + S - 1 < n_items) {
+            __syncthreads(); // the LIVE oldest items are complete for every wave; the slot of the item before this one is free
+            if (left > S - 1) {
                 issue_item(lt, lr, stage_l);
                 if (++lr == NI) { lr = 0; ++lt; }
                 stage_l = stage_l + 1 == S ? 0 : stage_l + 1;
             }
-            const int n0 = ct * TN + wn * (32 * NJ);
-            if (n0 < N) {
-                const unsigned st = stage_c * STAGE;
-                if (cr < KC) {
-                    load_a(st + A_LDS);
-                    phase_g1(st, cr == 0);
-                } else {
-                    phase_g2_prefetch(st);
-                    phase_sm(n0);
-                    phase_g2();
+            --left;
+        };
+        auto next_stage = [&](int st) __attribute__((always_inline)) { return st + 1 == S ? 0 : st + 1; };
+        const lds_u8 *arow[MB];
+        int asw[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int row = wr * (32 * MB) + 32 * mb + c;
+            arow[mb] = smem + A_LDS + row * RBA;
+            asw[mb] = swz_b128(RBA, row);
+        }
+        // operands of step t = (k-step, slice) of a chunk: the A operand is fetched with the first slice
+        constexpr int TC = KS * NJ;
+        constexpr int CPF = KPF * NJ;
+        v8 pa[MB][KPF], pb[CPF]; // those of the first steps of the chunk in hand
+        auto fetch_a = [&](unsigned slot, int mb, int ks) __attribute__((always_inline)) -> v8 {
+            u32x4 raw = *(const lds_u32x4 *)(arow[mb] + slot + 16 * ((2 * ks + g) ^ asw[mb]));
+            if constexpr (SOFTMAX) raw = (raw ^ a_flip) & a_keep;
+            return __builtin_bit_cast(v8, raw);
+        };
+        auto fetch_head = [&](unsigned slot) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < CPF; ++t) {
+                if (t % NJ == 0) {
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) pa[mb][t / NJ] = fetch_a(slot, mb, t / NJ);
+                }
+                pb[t] = load_b(t % NJ, t / NJ);
+            }
+        };
+        for (int ct = 0; ct < n_iters; ++ct) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) accC[j][mb][r] = 0.f;
+            for (int r = 0; r < KC; ++r) {
+                top();
+                unsigned slot = stage_c * STAGE;
+                set_b_slot(slot);
+                if (!AHEAD || r == 0) fetch_head(slot);
+                stage_c = next_stage(stage_c);
+                v8 ao[MB][KS], bo[TC];
+#pragma unroll
+                for (int t = 0; t < CPF; ++t) bo[t] = pb[t];
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int ks = 0; ks < KPF; ++ks) ao[mb][ks] = pa[mb][ks];
+#pragma unroll
+                for (int t = 0; t < TC; ++t) {
+                    const int tf = t + CPF; // the step fetched here
+                    if (tf == TC && AHEAD) { // from here on of the next chunk (after the last one: of the D item, not used)
+                        slot = stage_c * STAGE;
+                        set_b_slot(slot);
+                    }
+                    if (tf < TC) {
+                        if (tf % NJ == 0) {
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb) ao[mb][tf / NJ] = fetch_a(slot, mb, tf / NJ);
+                        }
+                        bo[tf] = load_b(tf % NJ, tf / NJ);
+                    } else if (AHEAD) {
+                        const int th = tf - TC;
+                        if (th % NJ == 0) {
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb) pa[mb][th / NJ] = fetch_a(slot, mb, th / NJ);
+                        }
+                        pb[th] = load_b(th % NJ, th / NJ);
+                    }
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) accC[t % NJ][mb] = M_::run(bo[t], ao[mb][t / NJ], accC[t % NJ][mb]);
+                    __builtin_amdgcn_sched_barrier(0x406);
                 }
             }
-            if (++cr == NI) { cr = 0; ++ct; }
-            stage_c = stage_c + 1 == S ? 0 : stage_c + 1;
+            top();
+            phase_g2_prefetch(stage_c * STAGE);
+            stage_c = next_stage(stage_c);
+            phase_sm(ct * TN + wn * (32 * NJ)); // (a wave with no column of a ragged tile: all of C^T masked)
+            phase_g2();
         }
     } else if constexpr (PIPE) {
         // Software pipeline over n-tiles (softmax chains; plain chains with K and L of 32, where a
