@@ -1,4 +1,5 @@
-"""ctypes binding of include/mcf.h (same names, argument marshalling only).
+"""Binding of include/mcf.h (same names, argument marshalling only): the chain calls through the
+extension module _mcf_torch (csrc/mcf_torch.cpp), everything else through ctypes.
 
 torch is used for device memory and streams: tensors come in as torch CUDA(=HIP) tensors,
 their data pointers, strides and the current stream are handed to the C ABI.
@@ -149,6 +150,25 @@ def load_library():
     return lib
 
 
+_chain = None
+
+
+def _native_chain():
+    """chain() of the extension module; raises if it has not been built (there is no fallback path)."""
+    global _chain
+    if _chain is None:
+        import torch  # noqa: F401  (the extension links against its libraries)
+        load_library()
+        try:
+            from . import _mcf_torch
+        except ImportError as e:
+            raise McfError(-1, f"the extension module _mcf_torch is missing or does not load ({e}): build it with "
+                               "`python -m paper_2506_22169_amd.build`; there is no fallback") from e
+        _mcf_torch.set_error(McfError)
+        _chain = _mcf_torch.chain
+    return _chain
+
+
 def status_string(status):
     return load_library().mcf_status_string(int(status)).decode()
 
@@ -224,49 +244,34 @@ def _stream_ptr(stream):
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
-def _tiles_arg(tiles):
-    if tiles is None:
-        return None
-    if isinstance(tiles, Tiles):
-        return ctypes.byref(tiles)
+def _make_tiles(tiles):
     t = Tiles()
     t.mb, t.rg, t.ns, t.nj = tiles[:4]
     t.tl = tiles[4] if len(tiles) > 4 else 0    # (mb, rg, ns, nj[, tl]); tl = 0 means T_L = L
-    return ctypes.byref(t)
+    return t
 
 
-def _run(softmax, scale, A, B, D, out, tiles, stream, causal_offset=None):
-    import torch
-    lib = load_library()
-    if out is None:
-        out = torch.empty((A.shape[0], A.shape[1], D.shape[2]), dtype=A.dtype, device=A.device)
-    p = _problem_from_tensors(A, B, D, out)
-    args = [ctypes.c_void_p(A.data_ptr()), ctypes.c_void_p(B.data_ptr()), ctypes.c_void_p(D.data_ptr()),
-            ctypes.c_void_p(out.data_ptr()), _tiles_arg(tiles), _stream_ptr(stream)]
-    if causal_offset is not None:
-        _check(lib.mcf_causal_softmax_gemm_chain(ctypes.byref(p), ctypes.c_float(scale), ctypes.c_int64(int(causal_offset)), *args))
-    elif softmax:
-        _check(lib.mcf_softmax_gemm_chain(ctypes.byref(p), ctypes.c_float(scale), *args))
-    else:
-        _check(lib.mcf_gemm_chain(ctypes.byref(p), *args))
-    return out
+def _call(kind, scale, causal_offset, A, B, D, F, out, tiles, stream):
+    t = None if tiles is None else tiles if isinstance(tiles, Tiles) else _make_tiles(tiles)
+    return (_chain or _native_chain())(kind, scale, causal_offset, A, B, D, F, out, 0 if t is None else ctypes.addressof(t),
+                                       None if stream is None else _stream_ptr(stream).value or 0)
 
 
 def gemm_chain(A, B, D, out=None, tiles=None, stream=None):
     """mcf_gemm_chain: E = (A . B) . D on device tensors A[b,M,K], B[b,K,N] (any of the two
     supported layouts, e.g. a transposed view of [b,N,K]), D[b,N,L].  tiles: None (picker),
     a Tiles struct or an (mb, rg, ns, nj) tuple."""
-    return _run(False, 1.0, A, B, D, out, tiles, stream)
+    return _call(0, 1.0, 0, A, B, D, None, out, tiles, stream)
 
 
 def softmax_gemm_chain(A, B, D, scale, out=None, tiles=None, stream=None):
     """mcf_softmax_gemm_chain: E = softmax_rows(scale * A . B) . D."""
-    return _run(True, float(scale), A, B, D, out, tiles, stream)
+    return _call(1, scale, 0, A, B, D, None, out, tiles, stream)
 
 
 def causal_softmax_gemm_chain(A, B, D, scale, causal_offset=0, out=None, tiles=None, stream=None):
     """mcf_causal_softmax_gemm_chain: the softmax chain with row i seeing the columns n <= i + causal_offset."""
-    return _run(True, float(scale), A, B, D, out, tiles, stream, causal_offset=causal_offset)
+    return _call(2, scale, int(causal_offset), A, B, D, None, out, tiles, stream)
 
 
 def pick_tiles(problem, softmax=False):
@@ -372,11 +377,17 @@ def tune_tiles(A, B, D, scale=None, out=None, launches=0, population=0, top_n=0,
     return best, rep
 
 
-def gemm_chain3(A, B, D, F, scale=None, out=None, tiles=None, stream=None, _tune=None):
+def gemm_chain3(A, B, D, F, scale=None, out=None, tiles=None, stream=None):
     """mcf_gemm_chain3: G = ((A . B) . D) . F, or (softmax_rows(scale * A . B) . D) . F when scale is
     given, on device tensors; F[b,L,P] with unit column stride, G[b,M,P]."""
+    return _call(0 if scale is None else 1, 0.0 if scale is None else scale, 0, A, B, D, F, out, tiles, stream)
+
+
+def tune_tiles3(A, B, D, F, scale=None, out=None, launches=0, population=0, top_n=0, epsilon=0.0, seed=0,
+                max_generations=0, stream=None):
+    """mcf_tune_tiles3: Alg. 1 measured on the device for the three-GEMM chain over these tensors.
+    `out` is overwritten.  Returns (Tiles, SearchReport)."""
     import torch
-    lib = load_library()
     if F.dim() != 3 or F.shape[0] != A.shape[0] or F.shape[1] != D.shape[2]:
         raise McfError(1, f"F{tuple(F.shape)} does not continue D{tuple(D.shape)}")
     P = F.shape[2]
@@ -400,25 +411,13 @@ def gemm_chain3(A, B, D, F, scale=None, out=None, tiles=None, stream=None, _tune
     if F.shape[0] <= 1:
         sf[0] = 0
     fs = (ctypes.c_int64 * 3)(*sf)
-    ptrs = [ctypes.c_void_p(t.data_ptr()) for t in (A, B, D, F, out)]
-    if _tune is not None:      # mcf_tune_tiles3 over the same arguments
-        sp = _search_params(*_tune["search"])
-        best, rep = Tiles(), SearchReport()
-        _check(lib.mcf_tune_tiles3(ctypes.byref(p), int(scale is not None), ctypes.c_float(0.0 if scale is None else scale),
-                                   ctypes.c_int64(P), fs, *ptrs, ctypes.byref(sp), int(_tune["launches"]), _stream_ptr(stream),
-                                   ctypes.byref(best), ctypes.byref(rep)))
-        return best, rep
-    _check(lib.mcf_gemm_chain3(ctypes.byref(p), int(scale is not None), ctypes.c_float(0.0 if scale is None else scale),
-                               ctypes.c_int64(P), fs, *ptrs, _tiles_arg(tiles), _stream_ptr(stream)))
-    return out
-
-
-def tune_tiles3(A, B, D, F, scale=None, out=None, launches=0, population=0, top_n=0, epsilon=0.0, seed=0,
-                max_generations=0, stream=None):
-    """mcf_tune_tiles3: Alg. 1 measured on the device for the three-GEMM chain over these tensors.
-    `out` is overwritten.  Returns (Tiles, SearchReport)."""
-    return gemm_chain3(A, B, D, F, scale=scale, out=out, stream=stream,
-                       _tune={"search": (population, top_n, epsilon, seed, max_generations), "launches": launches})
+    sp = _search_params(population, top_n, epsilon, seed, max_generations)
+    best, rep = Tiles(), SearchReport()
+    _check(load_library().mcf_tune_tiles3(
+        ctypes.byref(p), int(scale is not None), ctypes.c_float(0.0 if scale is None else scale), ctypes.c_int64(P), fs,
+        *[ctypes.c_void_p(t.data_ptr()) for t in (A, B, D, F, out)], ctypes.byref(sp), int(launches), _stream_ptr(stream),
+        ctypes.byref(best), ctypes.byref(rep)))
+    return best, rep
 
 
 class _MetaLike:

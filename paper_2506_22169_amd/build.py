@@ -14,6 +14,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(ROOT, "_build", "mcf")
 LIB = os.path.join(HERE, "libmcf.so")
+TORCH_EXT = os.path.join(HERE, "_mcf_torch.so")   # extension module of the binding: no kernels, links against libmcf.so
+TORCH_SRC = "mcf_torch.cpp"
 
 # -packed-fp32-ops is switched off on purpose: hipcc must not form packed fp32 instructions.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
@@ -21,7 +23,7 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "
 
 
 def sources():
-    return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")))
+    return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")) and f != TORCH_SRC)
 
 
 def _headers_mtime():
@@ -101,6 +103,26 @@ def _write_resource_table(path):
     return len(rows)
 
 
+def _build_torch_ext():
+    """The extension module the chain calls of the binding go through (host code only)."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           os.path.join(CSRC, TORCH_SRC), "-o", TORCH_EXT, LIB, "-L", os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
+           "-ltorch_hip", "-ltorch", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True, cwd=HERE)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("build of " + TORCH_EXT + " failed")
+    return TORCH_EXT
+
+
 def build_library(force=True, jobs=8, verbose=False):
     """Compile every source and link libmcf.so.  force=False reuses up-to-date objects."""
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -115,13 +137,14 @@ def build_library(force=True, jobs=8, verbose=False):
         objs += list(ex.map(lambda s: _compile(s, True, hdr, ["-I", OBJ_DIR]), host))
     if verbose:
         print("kernel resource table:", n, "kernels")
-    cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
+    cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libmcf.so", "-o", LIB] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
         raise RuntimeError("link of libmcf.so failed")
+    _build_torch_ext()
     if verbose:
-        print("built", LIB, "from", len(objs), "objects")
+        print("built", LIB, "from", len(objs), "objects, and", TORCH_EXT)
     return LIB
 
 

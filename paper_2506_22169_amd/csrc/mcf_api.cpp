@@ -36,10 +36,7 @@ static bool span_fits(int64_t batch, int64_t rows, int64_t cols, const int64_t s
 int decode_layout(const mcf_problem *p, Layout *o) {
     if (p->in_dtype != MCF_F16 && p->in_dtype != MCF_BF16) return MCF_EUNSUPPORTED;
     if (p->out_dtype != p->in_dtype && p->out_dtype != MCF_F32) return MCF_EUNSUPPORTED;
-    {
-        int tk = 0, ksplit = 0;
-        if (p->K > 65536 || p->L > 4096 || !resolve_group(p->in_dtype, p->K, p->L, &tk, &ksplit)) return MCF_EUNSUPPORTED;
-    }
+    if (p->K > 65536 || p->L > 4096 || !resolve_group(p->in_dtype, p->K, p->L)) return MCF_EUNSUPPORTED;
     if (p->M >= (1ll << 31) - 512 || p->N >= (1ll << 31) - 512 || p->batch >= (1ll << 31)) return MCF_EUNSUPPORTED;
     const int64_t *in[4] = {p->a_stride, p->b_stride, p->d_stride, p->e_stride};
     int64_t *out[4] = {o->sa, o->sb, o->sd, o->se};
@@ -98,9 +95,9 @@ static const Variant *find_variant3(int dtype, int64_t K, int64_t L, int64_t P, 
                                     int ns, int nj) {
     int n = 0;
     const Variant *v = variants3(&n);
-    for (int i = 0; i < n; ++i)
-        if (v[i].dtype == dtype && v[i].K == K && v[i].L == L && v[i].P == P && v[i].softmax == softmax &&
-            v[i].b_kcontig == b_kcontig && v[i].mb == mb && v[i].rg == rg && v[i].ns == ns && v[i].nj == nj)
+    const Group *g = group3(dtype, K, L, P);
+    for (int i = g ? g->begin : 0; g && i < g->end; ++i)
+        if (v[i].softmax == softmax && v[i].b_kcontig == b_kcontig && v[i].mb == mb && v[i].rg == rg && v[i].ns == ns && v[i].nj == nj)
             return &v[i];
     return nullptr;
 }
@@ -112,10 +109,9 @@ int candidates3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, std
     int n = 0;
     const Variant *v = variants3(&n);
     out->clear();
-    for (int i = 0; i < n; ++i) {
-        if (v[i].dtype != p->in_dtype || v[i].K != p->K || v[i].L != p->L || v[i].P != P ||
-            v[i].softmax != (softmax != 0) || v[i].b_kcontig != b_kcontig || v[i].scratch_bytes != 0)
-            continue;
+    const Group *g = group3(p->in_dtype, p->K, p->L, P);
+    for (int i = g ? g->begin : 0; g && i < g->end; ++i) {
+        if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != b_kcontig || v[i].scratch_bytes != 0) continue;
         mcf_tiles t;
         memset(&t, 0, sizeof(t));
         t.mb = v[i].mb; t.rg = v[i].rg; t.ns = v[i].ns; t.nj = v[i].nj;
@@ -320,10 +316,9 @@ extern "C" int mcf_list_variants3(const mcf_problem *p, int64_t P, int softmax, 
     if (mcf::decode_layout(&pc, &lay) != MCF_OK) return 0;
     int n = 0, total = 0;
     const mcf::Variant *v = mcf::variants3(&n);
-    for (int i = 0; i < n; ++i) {
-        if (v[i].dtype != p->in_dtype || v[i].K != p->K || v[i].L != p->L || v[i].P != P ||
-            v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig)
-            continue;
+    const mcf::Group *g = mcf::group3(p->in_dtype, p->K, p->L, P);
+    for (int i = g ? g->begin : 0; g && i < g->end; ++i) {
+        if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig) continue;
         if (out && total < cap) {
             out[4 * total] = v[i].mb; out[4 * total + 1] = v[i].rg; out[4 * total + 2] = v[i].ns; out[4 * total + 3] = v[i].nj;
         }

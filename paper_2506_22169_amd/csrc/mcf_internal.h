@@ -77,9 +77,13 @@ const Variant *variants(int *count);
 // ... and the three-GEMM chain (P > 0).
 const Variant *variants3(int *count);
 // The kernel group that serves a problem's (dtype, K, L): the group with T_K = K if it is built,
-// otherwise a group with a k loop whose chunk divides K.  Returns false if there is neither;
-// *tk is the K of the group's variants, *ksplit whether they loop over k.
-bool resolve_group(int dtype, int64_t K, int64_t L, int *tk, int *ksplit);
+// otherwise a group with a k loop whose chunk divides K; nullptr if there is neither.  Its variants are
+// [begin, end) of the table; K is that of the variants, ksplit whether they loop over k.
+struct Group {
+    int32_t dtype, K, L, ksplit, P, begin, end;
+};
+const Group *resolve_group(int dtype, int64_t K, int64_t L);
+const Group *group3(int dtype, int64_t K, int64_t L, int64_t P); // the same in the table of the three-GEMM chain
 // Variant of that group with the given arrangement (K is the problem's K), or nullptr.
 const Variant *find_variant(int dtype, int64_t K, int64_t L, int softmax, int b_kcontig, int mb, int rg, int ns, int nj);
 

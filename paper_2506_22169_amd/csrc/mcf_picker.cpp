@@ -150,13 +150,12 @@ using namespace mcf;
 extern "C" int mcf_list_variants(const mcf_problem *p, int softmax, int32_t *out, int cap) {
     Layout lay;
     if (check_problem(p, &lay) != MCF_OK) return 0;
-    int n = 0, total = 0, tk = 0, ksplit = 0;
-    if (!resolve_group(p->in_dtype, p->K, p->L, &tk, &ksplit)) return 0;
+    int n = 0, total = 0;
+    const Group *g = resolve_group(p->in_dtype, p->K, p->L);
+    if (!g) return 0;
     const Variant *v = variants(&n);
-    for (int i = 0; i < n; ++i) {
-        if (v[i].dtype != p->in_dtype || v[i].K != tk || v[i].ksplit != ksplit || v[i].L != p->L ||
-            v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig)
-            continue;
+    for (int i = g->begin; i < g->end; ++i) {
+        if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig) continue;
         if (out && total < cap) {
             out[4 * total] = v[i].mb; out[4 * total + 1] = v[i].rg; out[4 * total + 2] = v[i].ns; out[4 * total + 3] = v[i].nj;
         }
@@ -183,37 +182,37 @@ extern "C" int mcf_eval_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
 // T_L that divides L and has kernels, in registry order, the feasible variants that satisfy
 // Rule 3; if Rule 3 leaves nothing (e.g. M smaller than every tile) it is dropped so that a
 // feasible variant is always found when one covers the shape.
-int mcf::feasible_candidates(const mcf_problem *p, int softmax, std::vector<mcf_tiles> *out) {
+// f(candidate) for each of them.
+template <typename F> static int each_candidate(const mcf_problem *p, int softmax, F &&f) {
     Layout lay;
     int st = check_problem(p, &lay);
     if (st != MCF_OK) return st;
-    int n = 0, tk = 0, ksplit = 0;
-    if (!resolve_group(p->in_dtype, p->K, p->L, &tk, &ksplit)) return MCF_EUNSUPPORTED;
+    int n = 0;
     const Variant *v = variants(&n);
-    std::vector<int> tls; // T_L options, the full L first, then descending
-    tls.push_back((int)p->L);
-    for (int tl = (int)p->L / 2; tl >= 32; --tl) {
-        int tk2 = 0, ks2 = 0;
-        if (p->L % tl == 0 && resolve_group(p->in_dtype, p->K, tl, &tk2, &ks2)) tls.push_back(tl);
-    }
-    for (int pass = 0; pass < 2; ++pass) {
-        out->clear();
-        for (int tl : tls) {
-            resolve_group(p->in_dtype, p->K, tl, &tk, &ksplit);
-            for (int i = 0; i < n; ++i) {
-                if (v[i].dtype != p->in_dtype || v[i].K != tk || v[i].ksplit != ksplit || v[i].L != tl ||
-                    v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig)
-                    continue;
+    // T_L options, the full L first, then descending (L is at most 256 where there are kernels)
+    const Group *g[256];
+    int n_g = 0;
+    if (!(g[n_g++] = resolve_group(p->in_dtype, p->K, p->L))) return MCF_EUNSUPPORTED;
+    for (int tl = (int)p->L / 2; tl >= 32 && n_g < 256; --tl)
+        if (p->L % tl == 0 && (g[n_g] = resolve_group(p->in_dtype, p->K, tl))) ++n_g;
+    bool any = false;
+    for (int pass = 0; pass < 2 && !any; ++pass)
+        for (int q = 0; q < n_g; ++q)
+            for (int i = g[q]->begin; i < g[q]->end; ++i) {
+                if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig) continue;
                 mcf_tiles t;
                 eval_model(p, softmax != 0, &v[i], &t);
                 if (!feasible(t)) continue;
                 if (pass == 0 && p->M > 0 && p->N > 0 && !(padding_ok(p->M, t.tm) && padding_ok(p->N, t.tn))) continue;
-                out->push_back(t);
+                any = true;
+                f(t);
             }
-        }
-        if (!out->empty()) return MCF_OK;
-    }
-    return MCF_EUNSUPPORTED;
+    return any ? MCF_OK : MCF_EUNSUPPORTED;
+}
+
+int mcf::feasible_candidates(const mcf_problem *p, int softmax, std::vector<mcf_tiles> *out) {
+    out->clear();
+    return each_candidate(p, softmax, [&](const mcf_tiles &t) { out->push_back(t); });
 }
 
 extern "C" int mcf_list_candidates(const mcf_problem *p, int softmax, mcf_tiles *out, int cap) {
@@ -225,12 +224,9 @@ extern "C" int mcf_list_candidates(const mcf_problem *p, int softmax, mcf_tiles 
 
 extern "C" int mcf_pick_tiles(const mcf_problem *p, int softmax, mcf_tiles *out) {
     if (!out) return MCF_EINVAL;
-    std::vector<mcf_tiles> cands;
-    int st = feasible_candidates(p, softmax, &cands);
-    if (st != MCF_OK) return st;
-    const mcf_tiles *best = &cands[0];
-    for (const mcf_tiles &t : cands)
-        if (better(t, *best)) best = &t;
-    *out = *best;
-    return MCF_OK;
+    bool first = true;
+    return each_candidate(p, softmax, [&](const mcf_tiles &t) {
+        if (first || better(t, *out)) *out = t;
+        first = false;
+    });
 }

@@ -79,28 +79,44 @@ const Variant *variants(int *count) {
     return t.data();
 }
 
-bool resolve_group(int dtype, int64_t K, int64_t L, int *tk, int *ksplit) {
-    int best = 0;
-    for (const Variant &v : all()) {
-        if (v.dtype != dtype || v.L != L) continue;
-        if (!v.ksplit && v.K == K) {
-            *tk = v.K; *ksplit = 0;
-            return true;
-        }
-        if (v.ksplit && K > v.K && K % v.K == 0 && v.K > best) best = v.K; // the largest chunk that divides K
+// The groups of a table: the variants of one (dtype, K, L, P) stand together in it.
+static std::vector<Group> group_index(const std::vector<Variant> &t) {
+    std::vector<Group> out;
+    for (int i = 0; i < (int)t.size(); ++i) {
+        const Variant &v = t[i];
+        if (out.empty() || out.back().dtype != v.dtype || out.back().K != v.K || out.back().L != v.L || out.back().ksplit != v.ksplit ||
+            out.back().P != v.P)
+            out.push_back({v.dtype, v.K, v.L, v.ksplit, v.P, i, i});
+        out.back().end = i + 1;
     }
-    if (!best) return false;
-    *tk = best; *ksplit = 1;
-    return true;
+    return out;
+}
+
+const Group *resolve_group(int dtype, int64_t K, int64_t L) {
+    static const std::vector<Group> groups = group_index(all());
+    const Group *best = nullptr;
+    for (const Group &g : groups) {
+        if (g.dtype != dtype || g.L != L) continue;
+        if (!g.ksplit && g.K == K) return &g;
+        if (g.ksplit && K > g.K && K % g.K == 0 && (!best || g.K > best->K)) best = &g; // the largest chunk that divides K
+    }
+    return best;
+}
+
+const Group *group3(int dtype, int64_t K, int64_t L, int64_t P) {
+    static const std::vector<Group> groups = group_index(all3());
+    for (const Group &g : groups)
+        if (g.dtype == dtype && g.K == K && g.L == L && g.P == P) return &g;
+    return nullptr;
 }
 
 const Variant *find_variant(int dtype, int64_t K, int64_t L, int softmax, int b_kcontig, int mb, int rg, int ns, int nj) {
-    int tk = 0, ksplit = 0;
-    if (!resolve_group(dtype, K, L, &tk, &ksplit)) return nullptr;
-    for (const Variant &v : all())
-        if (v.dtype == dtype && v.K == tk && v.L == L && v.ksplit == ksplit && v.softmax == softmax &&
-            v.b_kcontig == b_kcontig && v.mb == mb && v.rg == rg && v.ns == ns && v.nj == nj)
-            return &v;
+    const Group *g = resolve_group(dtype, K, L);
+    if (!g) return nullptr;
+    const Variant *t = all().data();
+    for (int i = g->begin; i < g->end; ++i)
+        if (t[i].softmax == softmax && t[i].b_kcontig == b_kcontig && t[i].mb == mb && t[i].rg == rg && t[i].ns == ns && t[i].nj == nj)
+            return &t[i];
     return nullptr;
 }
 
