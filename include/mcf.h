@@ -169,6 +169,33 @@ int mcf_gemm_chain3(const mcf_problem *problem, int softmax, float scale, int64_
                     const int64_t *f_stride, const void *A, const void *B, const void *D,
                     const void *F, void *G, const mcf_tiles *tiles_or_null, void *hip_stream);
 
+/*
+ * One chain of any of the kinds above, with a workspace.  Where the (batch, m-tile, h-tile) blocks of
+ * a call leave compute units idle, its n range is split over blocks (as Sec. III-A splits m and h):
+ * each range leaves its fp32 result, for a softmax divided by its own row sum and with the logarithm of
+ * that sum, in the workspace, and a second kernel on the same stream puts the ranges together in a fixed order and
+ * rounds once.  The calls above have no workspace and never split n.
+ *   P, f_stride, F  : as mcf_gemm_chain3; P = 0: a chain of two GEMMs (F is not read)
+ *   softmax, causal : as the calls above (causal implies softmax; MCF_EUNSUPPORTED with P > 0)
+ *   n_split         : ranges of n (cut to the number of n-tiles); 0: the library decides, which is 1 where tiles are given
+ * mcf_call_workspace: the bytes such a call wants (0: it does not split n); host only.
+ * mcf_call_run      : device pointer workspace (16-byte aligned, MCF_EINVAL if smaller than that, may be
+ *                     NULL for 0 bytes), in use until the call's work on hip_stream is done.
+ */
+typedef struct mcf_call {
+    mcf_problem problem;
+    int64_t P, f_stride[3];
+    int32_t softmax, causal;
+    float scale;
+    int32_t n_split;
+    int64_t causal_offset;
+    const void *A, *B, *D, *F;
+    void *E;
+    const mcf_tiles *tiles;
+} mcf_call;
+int mcf_call_workspace(const mcf_call *call, int64_t *bytes);
+int mcf_call_run(const mcf_call *call, void *workspace, int64_t workspace_bytes, void *hip_stream);
+
 /* The arrangement mcf_gemm_chain3 takes when given no tiles; the model terms in *out are those
  * of its two-GEMM part (problem->e_stride is not read).  MCF_EUNSUPPORTED: none built. */
 int mcf_pick_tiles3(const mcf_problem *problem, int64_t P, int softmax, mcf_tiles *out);

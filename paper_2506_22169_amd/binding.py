@@ -45,6 +45,14 @@ class Tiles(ctypes.Structure):
         return {n: getattr(self, n) for n, _ in self._fields_}
 
 
+class Call(ctypes.Structure):
+    """struct mcf_call"""
+    _fields_ = [("problem", Problem), ("P", ctypes.c_int64), ("f_stride", ctypes.c_int64 * 3), ("softmax", ctypes.c_int32),
+                ("causal", ctypes.c_int32), ("scale", ctypes.c_float), ("n_split", ctypes.c_int32),
+                ("causal_offset", ctypes.c_int64), ("A", ctypes.c_void_p), ("B", ctypes.c_void_p), ("D", ctypes.c_void_p),
+                ("F", ctypes.c_void_p), ("E", ctypes.c_void_p), ("tiles", ctypes.c_void_p)]
+
+
 MCF_MAX_SUB_EXPRESSIONS = 8
 MCF_TRIPS_NO_HOIST, MCF_TRIPS_KEEP_UNIT_LOOPS, MCF_TRIPS_BIND_BLOCK = 1, 2, 4
 
@@ -130,6 +138,10 @@ def load_library():
     for f in (lib.mcf_pick_tiles, lib.mcf_eval_tiles, lib.mcf_list_variants, lib.mcf_gemm_chain,
               lib.mcf_softmax_gemm_chain, lib.mcf_search_tiles, lib.mcf_tune_tiles, lib.mcf_list_candidates,
               lib.mcf_gemm_chain3, lib.mcf_list_variants3, lib.mcf_pick_tiles3):
+        f.restype = ctypes.c_int
+    lib.mcf_call_workspace.argtypes = [ctypes.POINTER(Call), ctypes.POINTER(ctypes.c_int64)]
+    lib.mcf_call_run.argtypes = [ctypes.POINTER(Call), vp, ctypes.c_int64, vp]
+    for f in (lib.mcf_call_workspace, lib.mcf_call_run):
         f.restype = ctypes.c_int
     lib.mcf_probe_copy.argtypes = [vp, vp, ctypes.c_int64, vp]
     lib.mcf_probe_mfma.argtypes = [vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, vp]
@@ -251,10 +263,10 @@ def _make_tiles(tiles):
     return t
 
 
-def _call(kind, scale, causal_offset, A, B, D, F, out, tiles, stream):
+def _call(kind, scale, causal_offset, A, B, D, F, out, tiles, stream, n_split=0):
     t = None if tiles is None else tiles if isinstance(tiles, Tiles) else _make_tiles(tiles)
     return (_chain or _native_chain())(kind, scale, causal_offset, A, B, D, F, out, 0 if t is None else ctypes.addressof(t),
-                                       None if stream is None else _stream_ptr(stream).value or 0)
+                                       None if stream is None else _stream_ptr(stream).value or 0, n_split)
 
 
 def gemm_chain(A, B, D, out=None, tiles=None, stream=None):

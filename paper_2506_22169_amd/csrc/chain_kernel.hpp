@@ -198,7 +198,12 @@ void chain_kernel(const KParams p) {
     const unsigned lds0 = (unsigned)(size_t)smem;
 
     // kernel arguments -> scalar registers, once
-    const int M = p.M, N = p.N, m_tiles = p.m_tiles, h_tiles = p.h_tiles, n_blocks = p.n_blocks, a_mode = p.a_mode;
+    const int M = p.M, m_tiles = p.m_tiles, h_tiles = p.h_tiles, n_blocks = p.n_blocks, a_mode = p.a_mode;
+    // The n range of this block: all of it, or with a grid of two dimensions the blockIdx.y-th of the
+    // ranges a call is split into where its (batch, m-tile, h-tile) blocks leave compute units idle.
+    // Everything below sees a problem whose N is the length of the range and whose B, D and mask begin there.
+    const int n_first = blockIdx.y * p.split_cols;
+    const int N = p.N - n_first < p.split_cols ? p.N - n_first : p.split_cols;
     const int sa_r = (int)p.sa_r, sb_r = (int)p.sb_r, sd_r = (int)p.sd_r;
     const int64_t se_r = p.se_r;
     const float c1 = p.c1;
@@ -243,8 +248,8 @@ void chain_kernel(const KParams p) {
     const int mrow0 = mt * TM; // first row of the block
 
     const T *Ag = (const T *)p.A + batch * p.sa_b + (int64_t)mrow0 * sa_r;
-    const T *Bg = (const T *)p.B + batch * p.sb_b;
-    const T *Dg = (const T *)p.D + batch * p.sd_b + ht * LD;
+    const T *Bg = (const T *)p.B + batch * p.sb_b + (BKC ? (int64_t)n_first * sb_r : n_first);
+    const T *Dg = (const T *)p.D + batch * p.sd_b + (int64_t)n_first * sd_r + ht * LD;
     T *Eg = (T *)p.E + batch * p.se_b + ht * LD;
 
     // ---- per-lane byte offsets of the B / D pieces this wave loads for every n-tile ----------
@@ -284,7 +289,7 @@ void chain_kernel(const KParams p) {
     // ends at or below what the wave's first row sees (n_clean); in the other tiles a lane masks
     // the columns its row does not see, which may be all of them.  Without a mask (causal_off =
     // N - 1) both are N.
-    const int causal_off = p.causal_off;
+    const int causal_off = p.causal_off - n_first;
     auto sees = [&](int row) __attribute__((always_inline)) { // columns row `row` sees, 0 .. N
         if constexpr (!SOFTMAX) return N;
         const int v = row + causal_off + 1;
@@ -1243,6 +1248,7 @@ void chain_kernel(const KParams p) {
                         if (CH3) f[w] *= lw[w]; // the partial products were formed from E_w / l_w
                     }
                     l_run[mb] = l_all;
+                    m_run[mb] = m_all;
                 }
 #pragma unroll
                 for (int hb = 0; hb < HB; ++hb) {
@@ -1281,28 +1287,47 @@ void chain_kernel(const KParams p) {
     constexpr int BPWX = blocks_per_wave(LDX, MB, NS);
     const int blk0x = wn * BPWX; // this wave owns blocks [blk0x, blk0x + BPWX) that exist
     // fp32 output (bit 0 of the output pointer, which is 16-byte aligned, says so: a flag of its
-    // own would occupy a scalar register from the first instruction to here): the accumulators go
-    // out as they are held, 16 consecutive columns of a row per lane in four 16-byte stores
-    const bool out_f32 = ((uintptr_t)p.E & 1) != 0;
-    if (out_f32) {
-        float *Ef = (float *)((char *)p.E - 1) + batch * p.se_b + ht * LD; // (pointer arithmetic, so that the stores stay global ones)
+    // own would occupy a scalar register from the first instruction to here): one 32 x 32 block after
+    // the other goes through 4 KiB of LDS, so that a store instruction writes eight whole 128-byte row segments
+    // (stored as the accumulators are held, 16 bytes of a row segment by every lane, 40 x [1000,96].
+    // [96,776].[776,96] took 25.8 us a call instead of 21.2).
+    // The result of an n range goes out the same way, one row set per range (bit 1), to be read again soon;
+    // for a softmax the base-2 logarithm of the row sum it was divided by stands behind its columns.
+    const unsigned out_bits = (unsigned)(uintptr_t)p.E & 3;
+    if (out_bits) {
+        float *Ef = (float *)((char *)p.E - out_bits) + blockIdx.y * p.se_s + batch * p.se_b + ht * LD; // (pointer arithmetic, so that the stores stay global ones)
+        lds_u8 *es = smem + combine_bytes(LDX, MB, RG, NS) + (wr * owning_waves(LDX, MB, NS) + wn) * estage_wave_bytes(LDX, MB, NS);
+        const bool again = (out_bits & 2) != 0;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const int row = wrow0 + 32 * mb + c;
+            if (SOFTMAX && again && ht == 0 && g == 0 && mb * HBX >= blk0x && mb * HBX < blk0x + BPWX && row < M)
+                Ef[(int64_t)row * se_r + (se_r - 4)] = l_run[mb] > 0.f ? m_run[mb] * c1 + __builtin_amdgcn_logf(l_run[mb]) : -INFINITY;
 #pragma unroll
             for (int hb = 0; hb < HBX; ++hb) {
                 const int blk = mb * HBX + hb;
-                if (blk >= blk0x && blk < blk0x + BPWX && row < M) {
+                if (blk < blk0x || blk >= blk0x + BPWX) continue;
+                const int sw = swz_b128(128, c);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        f32x4 v;
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            if constexpr (CH3 && NS == 1) v[e] = accO[mb][hb][4 * q + e];
-                            else v[e] = accE[mb][hb][4 * q + e] * inv[mb];
-                        }
-                        const int col = 32 * hb + 16 * g + 4 * q;
-                        if (col < LDX) __builtin_nontemporal_store(v, (f32x4 *)(Ef + (int64_t)row * se_r + col));
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (CH3 && NS == 1) v[e] = accO[mb][hb][4 * q + e];
+                        else v[e] = accE[mb][hb][4 * q + e] * inv[mb];
+                    }
+                    *(lds_u32x4 *)(es + c * 128 + 16 * ((4 * g + q) ^ sw)) = __builtin_bit_cast(u32x4, v);
+                }
+#pragma unroll
+                for (int ps = 0; ps < 4; ++ps) {
+                    const int r = 8 * ps + lane / 8;
+                    const int ch = (lane % 8) ^ swz_b128(128, r);
+                    const u32x4 v = *(const lds_u32x4 *)(es + 1024 * ps + 16 * lane);
+                    const int grow = wrow0 + 32 * mb + r, col = 32 * hb + 4 * ch;
+                    u32x4 *dst = (u32x4 *)(Ef + (int64_t)grow * se_r + col);
+                    if (grow < M && col < LDX) {
+                        if (again) *dst = v;
+                        else __builtin_nontemporal_store(v, dst);
                     }
                 }
             }
@@ -1314,7 +1339,7 @@ void chain_kernel(const KParams p) {
         constexpr int RBS = estage_row_bytes(LDX, MB, NS); // staged row bytes: HPW * 64, rounded up to a power of two
         constexpr bool EPAD = RBS != HPW * 64 || pitch_elems(LDX) != LDX; // some staged pieces are padding or lie beyond the last column
         const int mb0 = blk0x / HBX, h0 = blk0x % HBX;
-        lds_u8 *es = smem + combine_bytes(LDX, MB, RG, NS) + wave * estage_wave_bytes(LDX, MB, NS);
+        lds_u8 *es = smem + combine_bytes(LDX, MB, RG, NS) + (wr * owning_waves(LDX, MB, NS) + wn) * estage_wave_bytes(LDX, MB, NS);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const float sc = inv[mb]; // (the product of a single wave per row set is final: not scaled)
@@ -1383,7 +1408,7 @@ int launch_chain(const KParams &p, void *stream) {
             if (dev >= 0 && dev < 64) attr_done[dev] = true;
         }
     }
-    hipLaunchKernelGGL(kern, dim3(p.n_blocks), dim3(64 * RG * NS), lds, (hipStream_t)stream, p);
+    hipLaunchKernelGGL(kern, dim3(p.n_blocks, p.n_split), dim3(64 * RG * NS), lds, (hipStream_t)stream, p);
     return (int)hipGetLastError();
 }
 

@@ -136,24 +136,31 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
     return MCF_OK;
 }
 
-// P == 0: the two-GEMM chain into E[b, M, L].  P > 0: the three-GEMM chain; F[b, L, P] with
-// strides fstr (all zero = packed), and E / e_stride describe the output [b, M, P].
-static int run(const mcf_problem *p_in, int softmax, float scale, const void *A, const void *B, const void *D, void *E,
-               const mcf_tiles *tiles, void *stream, int64_t P = 0, const int64_t *fstr = nullptr,
-               const void *F = nullptr, bool causal = false, int64_t causal_off = 0) {
+// Validation, tile choice and kernel arguments of one call.  P == 0: the two-GEMM chain into
+// E[b, M, L].  P > 0: the three-GEMM chain; F[b, L, P] with strides f_stride (all zero = packed),
+// and E / e_stride describe the output [b, M, P].
+int prepare(const mcf_call *call, Launch *o) {
     set_last_error("");
-    if (!p_in) return MCF_EINVAL;
-    mcf_problem pc = *p_in;
+    o->v = nullptr;
+    o->workspace_bytes = 0;
+    if (!call || call->P < 0 || call->n_split < 0) return MCF_EINVAL;
+    mcf_problem pc = call->problem;
     const mcf_problem *p = &pc;
-    if (p->batch < 0 || p->M < 0 || p->K < 0 || p->N < 0 || p->L < 0 || P < 0) return MCF_EINVAL;
+    const int softmax = call->softmax != 0 || call->causal != 0;
+    const int64_t P = call->P;
+    const float scale = call->scale;
+    const void *A = call->A, *B = call->B, *D = call->D, *F = call->F;
+    void *E = call->E;
+    if (p->batch < 0 || p->M < 0 || p->K < 0 || p->N < 0 || p->L < 0) return MCF_EINVAL;
     const bool ch3 = P > 0;
+    if (ch3 && call->causal) return MCF_EUNSUPPORTED;
     int64_t sg[3] = {0, 0, 0}, sf[3] = {0, 0, 0};
     if (ch3) {
         // A, B, D are laid out as in the two-GEMM chain; the output and F are checked here
         memcpy(sg, p->e_stride, sizeof(sg));
         memset(pc.e_stride, 0, sizeof(pc.e_stride));
         if (all_zero(sg)) packed(sg, p->M, P);
-        if (fstr) memcpy(sf, fstr, sizeof(sf));
+        memcpy(sf, call->f_stride, sizeof(sf));
         if (all_zero(sf)) packed(sf, p->L, P);
         for (int d = 0; d < 3; ++d)
             if (sg[d] < 0 || sf[d] < 0) return MCF_EINVAL;
@@ -184,8 +191,8 @@ static int run(const mcf_problem *p_in, int softmax, float scale, const void *A,
         if (ptrs[t] % 16 != 0) return MCF_EALIGN;
 
     mcf_tiles chosen;
-    if (tiles) {
-        chosen = *tiles;
+    if (call->tiles) {
+        chosen = *call->tiles;
     } else {
         st = ch3 ? pick3(p, softmax, lay.b_kcontig, P, &chosen) : mcf_pick_tiles(p, softmax, &chosen);
         if (st != MCF_OK) return st;
@@ -196,7 +203,7 @@ static int run(const mcf_problem *p_in, int softmax, float scale, const void *A,
     const Variant *v = ch3 ? find_variant3(p->in_dtype, p->K, p->L, P, softmax, lay.b_kcontig, chosen.mb, chosen.rg, chosen.ns, nj_)
                            : find_variant(p->in_dtype, p->K, tl, softmax, lay.b_kcontig, chosen.mb, chosen.rg, chosen.ns, nj_);
     if (!v) {
-        if (!ch3) return tiles ? MCF_EINVAL : MCF_EUNSUPPORTED;
+        if (!ch3) return call->tiles ? MCF_EINVAL : MCF_EUNSUPPORTED;
         // no kernels for this (K, L, P) at all, or only this arrangement is missing?
         mcf_tiles any;
         return pick3(p, softmax, lay.b_kcontig, P, &any) == MCF_OK ? MCF_EINVAL : MCF_EUNSUPPORTED;
@@ -209,7 +216,7 @@ static int run(const mcf_problem *p_in, int softmax, float scale, const void *A,
     const int64_t h_tiles = p->L / tl;
     if (p->batch * m_tiles * h_tiles >= (1ll << 31)) return MCF_EUNSUPPORTED;
 
-    KParams k;
+    KParams &k = o->k;
     memset(&k, 0, sizeof(k));
     k.A = A; k.B = B; k.D = D; k.E = E;
     k.sa_b = lay.sa[0]; k.sa_r = lay.sa[1];
@@ -223,7 +230,7 @@ static int run(const mcf_problem *p_in, int softmax, float scale, const void *A,
     // Longest first pays where blocks wait for a compute unit; where each has one of its own from the
     // start, the order that keeps a batch within one L2 is 4-7 % faster (15 x 757 x 757, K = L = 64,
     // 180 blocks: 9.8 against 10.5 us; 125 x 128 x 128, 250 blocks: 5.0 against 5.2 us).
-    k.lpt = causal && k.n_blocks > kComputeUnits;
+    k.lpt = call->causal && k.n_blocks > kComputeUnits;
     k.divisor = (int32_t)(k.lpt ? p->batch : m_tiles * h_tiles);
     division_magic((uint32_t)k.divisor, &k.d_magic, &k.d_shift);
     division_magic((uint32_t)h_tiles, &k.h_magic, &k.h_shift);
@@ -235,7 +242,8 @@ static int run(const mcf_problem *p_in, int softmax, float scale, const void *A,
         // row i sees the columns n <= i + causal_off, which the kernel forms in 32 bits; an offset
         // of N - 1 (or more) hides nothing and stands for "no mask", below -M nothing is seen either
         if (p->M + p->N >= (1ll << 31) - 1024) { set_last_error("softmax chain: M + N must stay below 2^31 - 1024"); return MCF_EUNSUPPORTED; }
-        k.causal_off = (int32_t)(!causal || causal_off > p->N - 1 ? p->N - 1 : causal_off < -p->M - 1 ? -p->M - 1 : causal_off);
+        const int64_t off = call->causal_offset;
+        k.causal_off = (int32_t)(!call->causal || off > p->N - 1 ? p->N - 1 : off < -p->M - 1 ? -p->M - 1 : off);
     }
     if (softmax) {
         // exp(scale*s - max) = exp2(|scale|*log2(e) * (s' - max')) with s' = +-s; a zero scale
@@ -244,12 +252,67 @@ static int run(const mcf_problem *p_in, int softmax, float scale, const void *A,
         if (scale == 0.0f) { k.a_mode = 2; k.c1 = log2e; }
         else { k.a_mode = scale < 0.0f ? 1 : 0; k.c1 = fabsf(scale) * log2e; }
     }
-    int err = v->launch(k, stream);
+
+    // n ranges of whole n-tiles, each a row of blocks of its own; more would leave some empty
+    const int64_t tn = 32ll * v->ns * v->nj, n_tiles = (p->N + tn - 1) / tn;
+    int64_t n_split = call->n_split > 0 ? call->n_split : 1;
+    int64_t per = n_split < n_tiles ? (n_tiles + n_split - 1) / n_split : 1;
+    n_split = n_tiles > 0 ? (n_tiles + per - 1) / per : 1;
+    k.n_split = (int32_t)n_split;
+    k.split_cols = n_split > 1 ? (int32_t)(per * tn) : k.N;
+    o->dtype = p->in_dtype;
+    o->softmax = softmax;
+    if (n_split > 1) {
+        if (n_split > 65535) return MCF_EINVAL;
+        CombineParams &c = o->c;
+        c.L = (int32_t)(ch3 ? P : p->L);
+        c.pitch = c.L + (softmax ? 4 : 0);
+        c.rows = p->batch * p->M; c.M = p->M;
+        c.split_stride = c.rows * c.pitch;
+        c.se_b = k.se_b; c.se_r = k.se_r;
+        c.E = E; c.n_split = (int32_t)n_split; c.out_f32 = p->out_dtype == MCF_F32;
+        k.se_b = p->M * c.pitch; k.se_r = c.pitch; k.se_s = c.split_stride;
+        o->workspace_bytes = n_split * c.split_stride * 4;
+        if (c.rows * (c.L >> 2) / 256 >= (1ll << 31) - 1 || c.split_stride > (1ll << 40)) return MCF_EUNSUPPORTED;
+    }
+    o->v = v;
+    return MCF_OK;
+}
+
+// Launches what prepare() laid out.  Host errors of the launches as MCF_ELAUNCH.
+int launch(Launch *o, void *workspace, int64_t workspace_bytes, void *stream) {
+    if (!o->v) return MCF_OK; // nothing to compute
+    if (o->workspace_bytes > 0) {
+        if (!workspace || workspace_bytes < o->workspace_bytes) return MCF_EINVAL;
+        if ((uintptr_t)workspace % 16 != 0) return MCF_EALIGN;
+        o->c.part = (const float *)workspace;
+        o->k.E = (void *)((uintptr_t)workspace | 2); // the kernels read bit 1 as "results of n ranges"
+    }
+    int err = o->v->launch(o->k, stream);
+    if (err == 0 && o->workspace_bytes > 0) err = launch_combine(o->c, o->dtype, o->softmax, stream);
     if (err != 0) {
         set_last_error(hipGetErrorString((hipError_t)err));
         return MCF_ELAUNCH;
     }
     return MCF_OK;
+}
+
+// The calls without a workspace: n is never split.
+static int run(const mcf_problem *p, int softmax, float scale, const void *A, const void *B, const void *D, void *E,
+               const mcf_tiles *tiles, void *stream, int64_t P = 0, const int64_t *fstr = nullptr,
+               const void *F = nullptr, bool causal = false, int64_t causal_off = 0) {
+    if (!p) return MCF_EINVAL;
+    mcf_call call;
+    memset(&call, 0, sizeof(call));
+    call.problem = *p;
+    call.P = P;
+    if (fstr) memcpy(call.f_stride, fstr, sizeof(call.f_stride));
+    call.softmax = softmax; call.causal = causal; call.scale = scale; call.causal_offset = causal_off;
+    call.n_split = 1;
+    call.A = A; call.B = B; call.D = D; call.F = F; call.E = E; call.tiles = tiles;
+    Launch o;
+    const int st = prepare(&call, &o);
+    return st != MCF_OK ? st : launch(&o, nullptr, 0, stream);
 }
 
 } // namespace mcf
@@ -274,6 +337,20 @@ extern "C" int mcf_gemm_chain3(const mcf_problem *p, int softmax, float scale, i
                                const mcf_tiles *tiles, void *stream) {
     if (P <= 0) return P == 0 && p && p->batch >= 0 ? MCF_OK : MCF_EINVAL; // no output columns: nothing to do
     return mcf::run(p, softmax != 0, softmax ? scale : 1.0f, A, B, D, G, tiles, stream, P, f_stride, F);
+}
+
+extern "C" int mcf_call_workspace(const mcf_call *call, int64_t *bytes) {
+    if (!bytes) return MCF_EINVAL;
+    mcf::Launch o;
+    const int st = mcf::prepare(call, &o);
+    *bytes = st == MCF_OK ? o.workspace_bytes : 0;
+    return st;
+}
+
+extern "C" int mcf_call_run(const mcf_call *call, void *workspace, int64_t workspace_bytes, void *stream) {
+    mcf::Launch o;
+    const int st = mcf::prepare(call, &o);
+    return st != MCF_OK ? st : mcf::launch(&o, workspace, workspace_bytes, stream);
 }
 
 extern "C" int mcf_pick_tiles3(const mcf_problem *p, int64_t P, int softmax, mcf_tiles *out) {

@@ -51,7 +51,8 @@ constexpr int combine_bytes(int L, int mb, int rg, int ns) {
     return ns > 1 ? rg * ns * (parked_blocks(L, mb, ns) * 16 + 2 * mb) * 64 * 4 : 0;
 }
 // Staging tile of the E store, per wave: the rows of the row sets it owns (32 each) times the
-// bytes of the h blocks it owns in a row, that pitch rounded up to a power of two.
+// bytes of the h blocks it owns in a row, that pitch rounded up to a power of two; at least what an
+// fp32 store stages at a time.
 constexpr int estage_row_bytes(int L, int mb, int ns) {
     const int hb = h_blocks(L), bpw = blocks_per_wave(L, mb, ns);
     const int hpw = bpw < hb ? bpw : hb;
@@ -60,9 +61,14 @@ constexpr int estage_row_bytes(int L, int mb, int ns) {
 constexpr int estage_wave_bytes(int L, int mb, int ns) {
     const int hb = h_blocks(L), bpw = blocks_per_wave(L, mb, ns);
     const int mpw = bpw < hb ? 1 : bpw / hb;
-    return mpw * 32 * estage_row_bytes(L, mb, ns);
+    const int b16 = mpw * 32 * estage_row_bytes(L, mb, ns);
+    return b16 > 4096 ? b16 : 4096; // (one 32 x 32 block of fp32 at a time)
 }
-constexpr int estage_bytes(int L, int mb, int rg, int ns) { return rg * ns * estage_wave_bytes(L, mb, ns); }
+// Waves of a row-group that own a run of blocks (there may be fewer blocks than waves).
+constexpr int owning_waves(int L, int mb, int ns) {
+    return (mb * h_blocks(L) + blocks_per_wave(L, mb, ns) - 1) / blocks_per_wave(L, mb, ns);
+}
+constexpr int estage_bytes(int L, int mb, int rg, int ns) { return rg * owning_waves(L, mb, ns) * estage_wave_bytes(L, mb, ns); }
 // Kernels with a k loop inside the block (T_K < K; `K` below is then the chunk T_K): the ring
 // carries two kinds of items, an A chunk + B chunk (tm x T_K, T_K x tn) per k step and the D
 // tile once per n-tile; a slot is as large as the larger of the two.

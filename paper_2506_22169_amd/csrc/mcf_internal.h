@@ -33,17 +33,21 @@ struct KParams {
     int32_t d_shift, h_shift;
     int32_t lpt;        // causal mask: 1 = longest blocks first over all batches, 0 = batch by batch
     int32_t M, N;
+    int32_t split_cols; // columns of an n range (N where n is not split), a multiple of T_N
+    int32_t n_split;    // n ranges: the second dimension of the grid
     int32_t a_mode;     // 0: A as is, 1: -A (negative scale), 2: A := 0 (scale == 0)
     int32_t k_chunks;   // kernels with a k loop: K / T_K (otherwise unused)
     float c1;           // |scale| * log2(e) (softmax only)
     int32_t causal_off; // softmax only: row i sees the columns n <= i + causal_off (N - 1: no mask); no flag
                         // beside it: a branch on one splits the scalar loads of the arguments in two
     const void *A, *B, *D;
-    void *E;            // bit 0 set: written as fp32 (the pointer itself is 16-byte aligned; strides then count fp32 elements)
+    void *E;            // bit 0 set: written as fp32 (the pointer itself is 16-byte aligned; strides then count fp32 elements);
+                        // bit 1 set: fp32 results of n ranges, for the combine kernel (se_r then is the pitch of its rows)
     int64_t sa_b, sa_r; // A: batch / row stride (col stride 1)
     int64_t sb_b, sb_r; // B: batch stride / stride of the non-contiguous index
     int64_t sd_b, sd_r; // D: batch / row stride
     int64_t se_b, se_r; // E: batch / row stride
+    int64_t se_s;       // stride between n ranges (bit 1 of E)
     const void *F;      // three-GEMM chain: F[b, L, P] (col stride 1); E is then the output [b, M, P]
     int64_t sf_b, sf_r; // F: batch / row stride
 };
@@ -57,6 +61,18 @@ inline void division_magic(uint32_t d, uint32_t *magic, int32_t *shift) {
     *magic = (uint32_t)(((1ull << (31 + s)) + d - 1) / d);
     *shift = s - 1;
 }
+
+// Arguments of the second pass over the results of n ranges (see mcf_combine.hip).
+struct CombineParams {
+    const float *part;    // [n_split][rows][pitch]: L columns, then (softmax) the base-2 logarithm of the row sum
+    int64_t split_stride; // rows * pitch
+    int64_t rows;         // batch * M
+    int64_t M;
+    int64_t se_b, se_r;   // E: batch / row stride
+    void *E;
+    int32_t pitch, L, n_split, out_f32;
+};
+int launch_combine(const CombineParams &p, int dtype, int softmax, void *stream); // returns hipError_t as int
 
 typedef int (*LaunchFn)(const KParams &p, void *stream); // returns hipError_t as int
 
@@ -108,6 +124,18 @@ int feasible_candidates(const mcf_problem *p, int softmax, std::vector<mcf_tiles
 // terms of their two-GEMM part.
 int problem3(const mcf_problem *p, int64_t P, mcf_problem *two_gemm_part, int *b_kcontig);
 int candidates3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, std::vector<mcf_tiles> *out);
+
+// One call, validated and laid out: the kernel with its arguments, and with n_split > 1 the second
+// pass and the workspace between the two.  v == nullptr: nothing to compute.
+struct Launch {
+    const Variant *v;
+    KParams k;
+    CombineParams c;
+    int64_t workspace_bytes;
+    int32_t dtype, softmax;
+};
+int prepare(const mcf_call *call, Launch *out); // MCF_OK or an error status; host only
+int launch(Launch *l, void *workspace, int64_t workspace_bytes, void *stream);
 
 void set_last_error(const char *msg);
 

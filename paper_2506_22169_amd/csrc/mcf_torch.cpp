@@ -5,12 +5,14 @@
 #include <Python.h>
 
 #include <ATen/ops/empty.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <stdio.h>
+#include <string.h>
 
-#include "../../include/mcf.h"
+#include "mcf_internal.h"
 
 namespace {
 
@@ -48,16 +50,18 @@ void strides3(const at::Tensor &t, int64_t s[3]) {
 
 bool is_tensor(PyObject *o) { return THPVariable_Check(o); }
 
-// chain(kind, scale, causal_offset, A, B, D, F, out, tiles, stream) -> out
+// chain(kind, scale, causal_offset, A, B, D, F, out, tiles, stream, n_split) -> out
 //   kind: 0 plain, 1 softmax, 2 causal softmax; F: None or the third factor (kind 0 or 1)
 //   tiles: 0 or the address of an mcf_tiles; stream: None (torch's current one) or a hipStream_t as an integer
+//   n_split: ranges of n, 0 for the library's choice (mcf_call)
 PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
-    if (n != 10) return PyErr_Format(PyExc_TypeError, "chain takes 10 arguments");
+    if (n != 11) return PyErr_Format(PyExc_TypeError, "chain takes 11 arguments");
     const long kind = PyLong_AsLong(arg[0]);
     const double scale = PyFloat_AsDouble(arg[1]);
     const long long causal_offset = PyLong_AsLongLong(arg[2]);
     const mcf_tiles *tiles = (const mcf_tiles *)PyLong_AsVoidPtr(arg[8]);
     void *stream = arg[9] == Py_None ? nullptr : PyLong_AsVoidPtr(arg[9]);
+    const long n_split = PyLong_AsLong(arg[10]);
     if (PyErr_Occurred()) return nullptr;
     if (!is_tensor(arg[3]) || !is_tensor(arg[4]) || !is_tensor(arg[5]) || (arg[6] != Py_None && !is_tensor(arg[6])) ||
         (arg[7] != Py_None && !is_tensor(arg[7])))
@@ -83,7 +87,8 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
         if (E.scalar_type() != type && E.scalar_type() != at::kFloat) return fail(MCF_EINVAL, "A, B, D must share one dtype; E has that dtype or float32");
         if (!E.is_cuda() || E.device() != A.device()) return fail(MCF_EINVAL, "A, B, D, E must live on one device");
     }
-    mcf_problem p;
+    mcf_call call;
+    mcf_problem &p = call.problem;
     p.batch = b; p.M = M; p.K = K; p.N = N; p.L = L;
     p.in_dtype = type == at::kHalf ? MCF_F16 : MCF_BF16;
     p.out_dtype = E.scalar_type() == at::kFloat ? MCF_F32 : p.in_dtype;
@@ -91,20 +96,28 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
     strides3(B, p.b_stride);
     strides3(D, p.d_stride);
     strides3(E, p.e_stride);
+    call.P = F ? cols : 0;
+    if (F) strides3(*F, call.f_stride);
+    else memset(call.f_stride, 0, sizeof(call.f_stride));
+    call.softmax = kind != 0; call.causal = kind == 2;
+    call.scale = (float)scale; call.causal_offset = causal_offset;
+    call.n_split = (int32_t)n_split;
+    call.A = A.data_ptr(); call.B = B.data_ptr(); call.D = D.data_ptr(); call.F = F ? F->data_ptr() : nullptr; call.E = E.data_ptr();
+    call.tiles = tiles;
     if (arg[9] == Py_None) stream = (void *)c10::hip::getCurrentHIPStream().stream();
-    const void *a = A.data_ptr(), *bp = B.data_ptr(), *d = D.data_ptr();
-    void *e = E.data_ptr();
     int st;
-    if (F) {
-        int64_t fs[3];
-        strides3(*F, fs);
-        st = mcf_gemm_chain3(&p, kind != 0, (float)scale, cols, fs, a, bp, d, F->data_ptr(), e, tiles, stream);
-    } else if (kind == 2) {
-        st = mcf_causal_softmax_gemm_chain(&p, (float)scale, causal_offset, a, bp, d, e, tiles, stream);
-    } else if (kind == 1) {
-        st = mcf_softmax_gemm_chain(&p, (float)scale, a, bp, d, e, tiles, stream);
+    if (F && cols == 0) {
+        st = MCF_OK; // no output columns: nothing to do
     } else {
-        st = mcf_gemm_chain(&p, a, bp, d, e, tiles, stream);
+        mcf::Launch l;
+        st = mcf::prepare(&call, &l);
+        if (st == MCF_OK) {
+            // The workspace of split ranges comes from torch's allocator for the stream that the call runs
+            // on: freed here, it is only handed out again to later work of that stream.
+            void *ws = l.workspace_bytes > 0 ? c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)l.workspace_bytes, (hipStream_t)stream) : nullptr;
+            st = mcf::launch(&l, ws, l.workspace_bytes, stream);
+            if (ws) c10::hip::HIPCachingAllocator::raw_delete(ws);
+        }
     }
     if (st != MCF_OK) return fail_status(st);
     if (arg[7] == Py_None) return THPVariable_Wrap(std::move(made));
