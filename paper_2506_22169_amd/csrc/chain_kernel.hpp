@@ -813,17 +813,25 @@ void chain_kernel(const KParams p) {
         constexpr int TA = TT >= 12 ? TT / 6 : (TT >= 6 ? 2 : 1);
         constexpr int TB = TT - TA;
         constexpr int EA = (NE + TA - 1) / TA; // elements per maximum step
-        constexpr int EB = (NE + TB - 1) / TB; // elements per exponential step
+        constexpr int EB = (NE + TB - 1) / TB; // elements per exponential step behind the maximum
+        // elements whose exponential is issued before step k: EB a step from TA on behind the maximum, spread
+        // evenly over the steps where the reference stands
+        constexpr auto exps = [](int k, bool with_max) constexpr {
+            const int e = with_max ? (k <= TA ? 0 : (k - TA) * EB) : NE * k / (TT > 1 ? TT - 1 : 1);
+            return e < NE ? e : NE;
+        };
         const int ncol0 = wn * (32 * NJ);
+        constexpr int STANDS = 0, LAZY = 1, EXACT = 2;
         f32x16 cc[2][NJ][MB]; // C^T of the tile in the softmax and of the tile GEMM 1 is producing
         float mx[MB], mneg[MB], corr[MB], sum0[MB], sum1[MB];
 
         // element e of a row set <-> slice j = e / 16, accumulator register r = e % 16
         // (a plain chain has no softmax: its slices are the mask of a ragged tile and the conversion)
-        auto vstep = [&](auto kc, auto curc, int n0) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value, CUR = decltype(curc)::value;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
+        // mode: how the reference follows the row maximum (see the loop below)
+        auto vstep = [&](auto kc, auto mbc, auto curc, auto modec, int n0) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value, mb = decltype(mbc)::value, CUR = decltype(curc)::value;
+            constexpr int MODE = decltype(modec)::value;
+            {
                 if constexpr (k == 0) {
                     // a ragged last tile, or a tile on or beyond the mask's edge: columns a row does
                     // not see contribute nothing (tiles before the last are whole in memory, so
@@ -842,7 +850,7 @@ void chain_kernel(const KParams p) {
                         }
                     }
                 }
-                if constexpr (SOFTMAX && k < TA) {
+                if constexpr (SOFTMAX && MODE != STANDS && k < TA) {
                     if constexpr (k == 0) mx[mb] = cc[CUR][0][mb][0];
 #pragma unroll
                     for (int e = k * EA; e < (k + 1) * EA && e < NE; ++e) mx[mb] = fmaxf(mx[mb], cc[CUR][e / 16][mb][e % 16]);
@@ -850,7 +858,7 @@ void chain_kernel(const KParams p) {
                     if constexpr (k == TA - 1) {
                         const float m_row = xhalf_max(mx[mb]);
                         float m_new = fmaxf(m_run[mb], m_row);
-                        if (MCF_LAZY_MAX > 0) m_new = (m_new - m_run[mb]) * c1 > (float)MCF_LAZY_MAX ? m_new : m_run[mb];
+                        if (MODE == LAZY && MCF_LAZY_MAX > 0) m_new = (m_new - m_run[mb]) * c1 > (float)MCF_LAZY_MAX ? m_new : m_run[mb];
                         // (under a mask) a row that has seen no column yet keeps m = -inf: p = 0, nothing to rescale
                         const bool blind = m_new == -INFINITY;
                         corr[mb] = blind ? 1.0f : __builtin_amdgcn_exp2f((m_run[mb] - m_new) * c1);
@@ -862,8 +870,12 @@ void chain_kernel(const KParams p) {
                         sum1[mb] = 0.f;
                     }
                 } else if constexpr (SOFTMAX) {
+                    if constexpr (MODE == STANDS && k == 0) {
+                        sum0[mb] = 0.f;
+                        sum1[mb] = 0.f;
+                    }
 #pragma unroll
-                    for (int e = (k - TA) * EB; e < (k - TA + 1) * EB && e < NE; ++e) {
+                    for (int e = exps(k, MODE != STANDS); e < exps(k + 1, MODE != STANDS); ++e) {
                         float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(cc[CUR][e / 16][mb][e % 16], c1, mneg[mb]));
                         pin(pv);
                         cc[CUR][e / 16][mb][e % 16] = pv;
@@ -876,10 +888,10 @@ void chain_kernel(const KParams p) {
                 if constexpr (k >= T2) {
                     // elements that are final (softmax: whose exponential was issued in an earlier
                     // step), spread evenly over the steps of GEMM 1; the last step takes what is left
-                    constexpr int done_prev = !SOFTMAX ? NE : (k - 1 < TA ? 0 : ((k - TA) * EB < NE ? (k - TA) * EB : NE));
+                    constexpr int done_prev = !SOFTMAX ? NE : exps(k, MODE != STANDS);
                     constexpr int quota = NE * (k - T2 + 1) / T1;
                     constexpr int hi = k == TT - 1 ? NE : ((done_prev < quota ? done_prev : quota) & ~1);
-                    constexpr int done_prev2 = !SOFTMAX ? NE : (k - 2 < TA ? 0 : ((k - 1 - TA) * EB < NE ? (k - 1 - TA) * EB : NE));
+                    constexpr int done_prev2 = !SOFTMAX ? NE : exps(k - 1, MODE != STANDS);
                     constexpr int quota2 = NE * (k - T2) / T1;
                     constexpr int lo = k == T2 ? 0 : ((done_prev2 < quota2 ? done_prev2 : quota2) & ~1);
 #pragma unroll
@@ -891,23 +903,19 @@ void chain_kernel(const KParams p) {
             }
         };
         auto ring_off = [&](int t) __attribute__((always_inline)) { return (unsigned)((t % S) * STAGE); }; // t >= 0
-        auto g2_step = [&](auto tc, const v8 &x) __attribute__((always_inline)) {
-            constexpr int t = decltype(tc)::value, j = t / (2 * HB), hb = (t / 2) % HB, qp = t % 2;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) accE[mb][hb] = M_::run(x, pop[j][mb][qp], accE[mb][hb]);
+        auto g2_step = [&](auto tc, auto mbc, const v8 &x) __attribute__((always_inline)) {
+            constexpr int t = decltype(tc)::value, j = t / (2 * HB), hb = (t / 2) % HB, qp = t % 2, mb = decltype(mbc)::value;
+            accE[mb][hb] = M_::run(x, pop[j][mb][qp], accE[mb][hb]);
         };
-        auto g1_step = [&](auto tc, auto nxtc, const v8 &x) __attribute__((always_inline)) {
-            constexpr int t = decltype(tc)::value, j = t / KS, ks = t % KS, NXT = decltype(nxtc)::value;
+        auto g1_step = [&](auto tc, auto mbc, auto nxtc, const v8 &x) __attribute__((always_inline)) {
+            constexpr int t = decltype(tc)::value, j = t / KS, ks = t % KS, mb = decltype(mbc)::value, NXT = decltype(nxtc)::value;
+            if constexpr (ks == 0) {
+                f32x16 zero;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                if constexpr (ks == 0) {
-                    f32x16 zero;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-                    cc[NXT][j][mb] = M_::run(x, a[mb][ks], zero);
-                } else {
-                    cc[NXT][j][mb] = M_::run(x, a[mb][ks], cc[NXT][j][mb]);
-                }
+                for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+                cc[NXT][j][mb] = M_::run(x, a[mb][ks], zero);
+            } else {
+                cc[NXT][j][mb] = M_::run(x, a[mb][ks], cc[NXT][j][mb]);
             }
         };
         auto fetch_d = [&](auto tc) __attribute__((always_inline)) -> v8 {
@@ -926,7 +934,7 @@ void chain_kernel(const KParams p) {
             static_for<0, T2>([&](auto tc) {
                 constexpr int t_ = decltype(tc)::value;
                 if constexpr (t_ + PF < T2) op[t_ + PF] = fetch_d(std::integral_constant<int, t_ + PF>{});
-                g2_step(tc, op[t_]);
+                static_for<0, MB>([&](auto mbc) { g2_step(tc, mbc, op[t_]); });
                 __builtin_amdgcn_sched_barrier(0x406);
             });
         };
@@ -937,7 +945,7 @@ void chain_kernel(const KParams p) {
             static_for<0, T1>([&](auto tc) {
                 constexpr int t_ = decltype(tc)::value;
                 if constexpr (t_ + PF < T1) op[t_ + PF] = fetch_b(std::integral_constant<int, t_ + PF>{});
-                g1_step(tc, nxtc, op[t_]);
+                static_for<0, MB>([&](auto mbc) { g1_step(tc, mbc, nxtc, op[t_]); });
                 __builtin_amdgcn_sched_barrier(0x406);
             });
         };
@@ -956,8 +964,8 @@ void chain_kernel(const KParams p) {
             }
         };
         // steady state (tiles i-1, i, i+1 all complete): one straight run, the steps of GEMM 2 of
-        // tile i-1, then those of GEMM 1 of tile i+1, a slice of the softmax of tile i behind each
-        auto steady = [&](auto curc, int i) __attribute__((always_inline)) {
+        // tile i-1, then those of GEMM 1 of tile i+1, a slice of the softmax of tile i behind each MFMA
+        auto steady = [&](auto curc, auto modec, int i) __attribute__((always_inline)) {
             constexpr int CUR = decltype(curc)::value;
             const int n0 = i * TN + ncol0;
             set_d_slot(ring_off(i - 1));
@@ -972,19 +980,38 @@ void chain_kernel(const KParams p) {
             static_for<0, TT>([&](auto tc) {
                 constexpr int t = decltype(tc)::value;
                 if constexpr (t + PF < TT) fetch(std::integral_constant<int, t + PF>{});
-                if constexpr (t < T2) g2_step(tc, op[t]);
-                else g1_step(std::integral_constant<int, t - T2>{}, std::integral_constant<int, CUR ^ 1>{}, op[t]);
-                vstep(tc, curc, n0);
-                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, MB>([&](auto mbc) {
+                    if constexpr (t < T2) g2_step(tc, mbc, op[t]);
+                    else g1_step(std::integral_constant<int, t - T2>{}, mbc, std::integral_constant<int, CUR ^ 1>{}, op[t]);
+                    vstep(tc, mbc, curc, modec, n0);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
             });
-            settle();
+            if constexpr (decltype(modec)::value != STANDS) settle();
+        };
+        // After a tile whose reference stood: whether some row sum of the wave says that it must move
+        // (also for a NaN); otherwise the row sums are taken over.  A lane's sum is at least each of its p, which
+        // so stay within the range of fp16.
+        auto outgrown = [&]() __attribute__((always_inline)) -> bool {
+            bool any = false;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) any = any || !(sum0[mb] + sum1[mb] <= 16384.f);
+            if (__builtin_amdgcn_ballot_w64(any) != 0) return true;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) l_run[mb] += sum0[mb] + sum1[mb];
+            return false;
         };
         // the softmax of tile t alone (first and last tiles; the last may be ragged, and a wave
         // whose slice of it is empty contributes P = 0)
-        auto softmax_only = [&](auto curc, int t) __attribute__((always_inline)) {
+        auto softmax_only = [&](auto curc, auto modec, int t) __attribute__((always_inline)) {
             const int n0 = t * TN + ncol0;
             if (n0 < N) {
-                static_for<0, TT>([&](auto tc) { vstep(tc, curc, n0); });
+                static_for<0, TT>([&](auto tc) {
+                    static_for<0, MB>([&](auto mbc) {
+                        vstep(tc, mbc, curc, modec, n0);
+                        __builtin_amdgcn_sched_barrier(0); // (left to itself the compiler starts them all at once: spills)
+                    });
+                });
                 settle();
             } else {
 #pragma unroll
@@ -1019,19 +1046,59 @@ void chain_kernel(const KParams p) {
             // iteration 0: no tile before it
             top(0);
             if (last >= 1) g1_only(std::integral_constant<int, 1>{}, 1);
-            softmax_only(std::integral_constant<int, 0>{}, 0);
-            // iterations 1 .. last-1: two per trip, the two C^T buffers swap roles at compile time
+            using Lazy = std::integral_constant<int, LAZY>;
+            using Buf0 = std::integral_constant<int, 0>;
+            using Buf1 = std::integral_constant<int, 1>;
+            softmax_only(Buf0{}, Lazy{}, 0);
+            // iterations 1 .. last-1, the two C^T buffers swap roles at compile time
             int i = 1;
-            for (; i + 1 <= last - 1; i += 2) {
-                top(i);
-                steady(std::integral_constant<int, 1>{}, i);
-                top(i + 1);
-                steady(std::integral_constant<int, 0>{}, i + 1);
+            if constexpr (reference_stands(KD, LD, MB, RG, NS, NJ, SOFTMAX, F_EXTRA)) {
+                // The reference m of the exponentials only has to keep them in range, and after the first
+                // tile it hardly ever has to move.  So these iterations leave it where it stands and look for no row
+                // maximum (a fifth of the vector work, and a chain of operations that the first exponential waited
+                // for); the row sums of the tile tell whether that was right.  If it was not, or if a row of the
+                // wave had seen no column before, the scores of the tile are computed once more (its B is still in the
+                // ring) and go through the softmax with their exact maximum.  No barrier depends on it.
+                // Measured (us a call, before and after): 64 x 4096 x 4096, bf16, K = L = 128, (1,8,1,2): 506 and 483,
+                // causal 32 x 4096 x 4096: 147 and 137; 64 x 4096 x 4096, fp16, K = L = 64: 326 and 308.  Scores
+                // of a standard deviation of 16 whose largest come last take the second way often: 75 and 93 us for 32 x
+                // 2048 x 2048, K = L = 128.  With one wave on a SIMD nothing covers the check behind a tile
+                // ((1,2,2,1): 32 x 2048 x 2048, K = L = 80: 104 and 120; K = L = 128: 122 and 136), so
+                // those kernels keep the maximum.
+                using Stands = std::integral_constant<int, STANDS>;
+                using Exact = std::integral_constant<int, EXACT>;
+                auto blind = [&]() __attribute__((always_inline)) -> bool {
+                    bool any = false;
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) any = any || m_run[mb] == -INFINITY;
+                    return __builtin_amdgcn_ballot_w64(any) != 0;
+                };
+                bool some_blind = blind();
+                auto one = [&](auto curc, int t) __attribute__((always_inline)) {
+                    top(t);
+                    steady(curc, Stands{}, t);
+                    if (__builtin_expect(some_blind || outgrown(), 0)) {
+                        g1_only(curc, t);
+                        __builtin_amdgcn_sched_barrier(0);
+                        softmax_only(curc, Exact{}, t);
+                        some_blind = blind();
+                    }
+                };
+                for (; i + 1 <= last - 1; i += 2) {
+                    one(Buf1{}, i);
+                    one(Buf0{}, i + 1);
+                }
+            } else {
+                for (; i + 1 <= last - 1; i += 2) {
+                    top(i);
+                    steady(Buf1{}, Lazy{}, i);
+                    top(i + 1);
+                    steady(Buf0{}, Lazy{}, i + 1);
+                }
             }
             if (i <= last - 1) {
                 top(i);
-                steady(std::integral_constant<int, 1>{}, i);
-                ++i;
+                steady(Buf1{}, Lazy{}, i);
             }
             // iteration `last` (if it is not iteration 0): GEMM 2 of the tile before, softmax of the
             // last, which is moved to the first C^T buffer if it sits in the second (two copies of
@@ -1045,7 +1112,7 @@ void chain_kernel(const KParams p) {
                 }
                 top(last);
                 g2_only(last - 1);
-                softmax_only(std::integral_constant<int, 0>{}, last);
+                softmax_only(Buf0{}, Lazy{}, last);
             }
             // GEMM 2 of the last tile
             g2_only(last);

@@ -136,6 +136,14 @@ constexpr int pipe_waves_per_simd(int K, int L, int mb, int rg, int ns, int nj, 
     const int held = mb * h_blocks(L) * 16 + 2 * nj * mb * 16 + nj * mb * 8;
     return held + 56 <= 512 / (2 * per_block) ? 2 * per_block : per_block;
 }
+// Whether a pipelined softmax kernel leaves the reference of its exponentials where it stands between the
+// first tile and the last (see the loop): with two waves on a SIMD or more, and 72 registers beside the held tiles,
+// which the way back from an outgrown reference needs (with 56 the 8-wave kernels of K = L = 64 spill in the loop).
+constexpr bool reference_stands(int K, int L, int mb, int rg, int ns, int nj, bool softmax, int extra = 0) {
+    const int waves = pipe_waves_per_simd(K, L, mb, rg, ns, nj, extra);
+    const int held = mb * h_blocks(L) * 16 + 2 * nj * mb * 16 + nj * mb * 8;
+    return softmax && waves >= 2 && held + 72 <= 512 / waves;
+}
 // Softmax chains that cannot be pipelined, in blocks of 8 waves, run their two wave groups a
 // phase apart, which keeps two n-tiles live: their ring is at least 3 deep.
 constexpr bool skewed_groups(int rg, int ns, bool softmax, bool ksplit = false) { return softmax && rg * ns == 8 && !ksplit; }
