@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include "mcf_geometry.h"
 #include "mcf_internal.h"
 
 namespace mcf {
@@ -136,6 +137,59 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
     return MCF_OK;
 }
 
+// The arrangement a call without one runs, from the model's pick.  The model does not see what an n-tile costs
+// a block beside its loads and flops (a barrier, an LDS round trip, the load latency a short ring leaves bare).
+//  * Where a ragged N pads least with it, it takes the narrowest n-tile.  Four waves with an n-tile of 32 columns
+//    give way to eight with 128 (or 64) on the same rows: 15 x [1635,64].[64,4048].[4048,128] 85 -> 40 us, softmax
+//    5 x 3887 x 2207, K = L = 64: 34 -> 24 us, three GEMMs 20 x [827,128].[128,1112].[1112,64].[64,64] 25 -> 15 us.
+//  * Among equal estimates it takes the wider n-tile.  A softmax chain of four waves a compute unit whose waves
+//    hold two slices each runs better with one slice and half the ring (two blocks a unit where that fits):
+//    17 calls with K = L from 80 to 256 that were picked so take 0.80 to 1.02 of their time, 0.95 in the mean; causal
+//    40 x 333 x 1357, K = L = 80: 23 -> 20.5 us.  Not for three GEMMs (1.06), nor where two waves share a SIMD already.
+static int64_t padding_of(int64_t n, int64_t tn) { return (n + tn - 1) / tn * tn - n; }
+static bool built(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, int64_t tn_now, mcf_tiles *t) {
+    if (P > 0) {
+        const Variant *v = find_variant3(p->in_dtype, p->K, p->L, P, softmax, b_kcontig, t->mb, t->rg, t->ns, t->nj);
+        if (!v || !v->launch || v->scratch_bytes != 0 || lds_bytes_for(v) > kLdsBytesPerBlock) return false;
+    }
+    if (mcf_eval_tiles(p, softmax, t) != MCF_OK) return false;
+    const int64_t pad = padding_of(p->N, t->tn);
+    return 20 * pad < p->N || pad <= padding_of(p->N, tn_now); // Rule 3
+}
+static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mcf_tiles *t) {
+    if (t->tk < p->K) return; // a k loop: measured as it is
+    mcf_tiles w;
+    memset(&w, 0, sizeof(w));
+    w.mb = t->mb; w.rg = t->rg; w.ns = t->ns; w.tl = t->tl;
+    if (t->mb == 1 && t->rg == 4 && t->ns == 1 && t->nj == 1) {
+        w.ns = 2;
+        for (w.nj = 2; w.nj >= 1; --w.nj)
+            if (built(p, softmax, b_kcontig, P, t->tn, &w)) { *t = w; return; }
+    } else if (softmax && P == 0 && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2) {
+        const bool shared = pipe_stages(t->tk, t->tl, 1, t->rg, t->ns, 2, true) > 0 && pipe_waves_per_simd(t->tk, t->tl, 1, t->rg, t->ns, 2) >= 2;
+        w.nj = 1;
+        if (!shared && built(p, softmax, b_kcontig, P, t->tn, &w)) *t = w;
+    }
+}
+
+// Ranges of n of a call that may have a workspace and leaves the choice to the library.  They pay where
+// the blocks leave more than half of the compute units idle and each range is long enough: the second
+// kernel and its launch cost about 4 us, eight to ten ring items of a block (an n-tile; a k loop has K / T_K + 1 to
+// each n-tile), so the ranges have to shorten a block by ten of them at least, and hold two items each.
+// No more ranges than give every compute unit one block.  Measured over 373 calls drawn from the ranges of the chains,
+// 318 of them with 256 blocks or fewer: those that it splits run 1.05 to 5 times as fast and none slower than unsplit; with
+// eight items instead of ten the first lose (4 x [320,32].. with 11 n-tiles 6.7 -> 8.1 us).  32 rows against 8192 keys of 128:
+// 92 -> 33 us; 1 x [639,1024].[1024,664].[664,128]: 100 -> 19 us.
+static int64_t ranges_for(int64_t blocks, int64_t n_tiles, int64_t items_per_tile) {
+    if (blocks <= 0 || 2 * blocks > kComputeUnits) return 1;
+    const int64_t least = items_per_tile >= 2 ? 1 : 2; // n-tiles of a range
+    int64_t s = kComputeUnits / blocks;
+    if (s > n_tiles / least) s = n_tiles / least;
+    if (s < 2) return 1;
+    const int64_t per = (n_tiles + s - 1) / s;
+    return (n_tiles - per) * items_per_tile >= 10 ? s : 1;
+}
+
 // Validation, tile choice and kernel arguments of one call.  P == 0: the two-GEMM chain into
 // E[b, M, L].  P > 0: the three-GEMM chain; F[b, L, P] with strides f_stride (all zero = packed),
 // and E / e_stride describe the output [b, M, P].
@@ -196,6 +250,7 @@ int prepare(const mcf_call *call, Launch *o) {
     } else {
         st = ch3 ? pick3(p, softmax, lay.b_kcontig, P, &chosen) : mcf_pick_tiles(p, softmax, &chosen);
         if (st != MCF_OK) return st;
+        settle_tiles(p, softmax, lay.b_kcontig, P, &chosen);
     }
     const int64_t tl = ch3 ? p->L : (chosen.tl > 0 ? chosen.tl : p->L);
     if (p->L % tl != 0) return MCF_EINVAL;
@@ -255,7 +310,8 @@ int prepare(const mcf_call *call, Launch *o) {
 
     // n ranges of whole n-tiles, each a row of blocks of its own; more would leave some empty
     const int64_t tn = 32ll * v->ns * v->nj, n_tiles = (p->N + tn - 1) / tn;
-    int64_t n_split = call->n_split > 0 ? call->n_split : 1;
+    int64_t n_split = call->n_split;
+    if (n_split == 0) n_split = call->tiles ? 1 : ranges_for(k.n_blocks, n_tiles, v->ksplit ? k.k_chunks + 1 : 1);
     int64_t per = n_split < n_tiles ? (n_tiles + n_split - 1) / n_split : 1;
     n_split = n_tiles > 0 ? (n_tiles + per - 1) / per : 1;
     k.n_split = (int32_t)n_split;

@@ -113,8 +113,17 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
         st = mcf::prepare(&call, &l);
         if (st == MCF_OK) {
             // The workspace of split ranges comes from torch's allocator for the stream that the call runs
-            // on: freed here, it is only handed out again to later work of that stream.
-            void *ws = l.workspace_bytes > 0 ? c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)l.workspace_bytes, (hipStream_t)stream) : nullptr;
+            // on: freed here, it is only handed out again to later work of that stream.  Where there is no
+            // room for one, ranges that the library chose are not needed.
+            void *ws = nullptr;
+            try {
+                if (l.workspace_bytes > 0) ws = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)l.workspace_bytes, (hipStream_t)stream);
+            } catch (const c10::OutOfMemoryError &) {
+                if (n_split != 0) throw;
+                call.n_split = 1;
+                st = mcf::prepare(&call, &l);
+                if (st != MCF_OK) return fail_status(st);
+            }
             st = mcf::launch(&l, ws, l.workspace_bytes, stream);
             if (ws) c10::hip::HIPCachingAllocator::raw_delete(ws);
         }
