@@ -142,10 +142,12 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 //  * Where a ragged N pads least with it, it takes the narrowest n-tile.  Four waves with an n-tile of 32 columns
 //    give way to eight with 128 (or 64) on the same rows: 15 x [1635,64].[64,4048].[4048,128] 85 -> 40 us, softmax
 //    5 x 3887 x 2207, K = L = 64: 34 -> 24 us, three GEMMs 20 x [827,128].[128,1112].[1112,64].[64,64] 25 -> 15 us.
-//  * Among equal estimates it takes the wider n-tile.  A softmax chain of four waves a compute unit whose waves
-//    hold two slices each runs better with one slice and half the ring (two blocks a unit where that fits):
-//    17 calls with K = L from 80 to 256 that were picked so take 0.80 to 1.02 of their time, 0.95 in the mean; causal
-//    40 x 333 x 1357, K = L = 80: 23 -> 20.5 us.  Not for three GEMMs (1.06), nor where two waves share a SIMD already.
+//    A softmax chain with more blocks than compute units stays: two blocks of four waves share a unit as well
+//    (causal, 2376 blocks, K = L = 64: 1.10 of the time with eight).
+//  * Among equal estimates it takes the wider n-tile.  Softmax kernels of four waves whose rows are padded to the
+//    LDS pitch (K = 80, 96, 160, 192) spill scalar registers with two slices a wave, and run better with one: the calls
+//    of a sweep that were picked so take 0.80 to 1.02 of their time; causal 40 x 333 x 1357, K = L = 80: 23 -> 20.5 us.
+//    With K = 128 and 256 the two are level (0.97 to 1.09); for three GEMMs the wider is better (1.06).
 static int64_t padding_of(int64_t n, int64_t tn) { return (n + tn - 1) / tn * tn - n; }
 static bool built(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, int64_t tn_now, mcf_tiles *t) {
     if (P > 0) {
@@ -161,14 +163,13 @@ static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, int64
     mcf_tiles w;
     memset(&w, 0, sizeof(w));
     w.mb = t->mb; w.rg = t->rg; w.ns = t->ns; w.tl = t->tl;
-    if (t->mb == 1 && t->rg == 4 && t->ns == 1 && t->nj == 1) {
+    if (t->mb == 1 && t->rg == 4 && t->ns == 1 && t->nj == 1 && (!softmax || t->blocks <= kComputeUnits)) {
         w.ns = 2;
         for (w.nj = 2; w.nj >= 1; --w.nj)
             if (built(p, softmax, b_kcontig, P, t->tn, &w)) { *t = w; return; }
-    } else if (softmax && P == 0 && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2) {
-        const bool shared = pipe_stages(t->tk, t->tl, 1, t->rg, t->ns, 2, true) > 0 && pipe_waves_per_simd(t->tk, t->tl, 1, t->rg, t->ns, 2) >= 2;
+    } else if (softmax && P == 0 && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2 && pitch_elems(t->tk) != t->tk) {
         w.nj = 1;
-        if (!shared && built(p, softmax, b_kcontig, P, t->tn, &w)) *t = w;
+        if (built(p, softmax, b_kcontig, P, t->tn, &w)) *t = w;
     }
 }
 
