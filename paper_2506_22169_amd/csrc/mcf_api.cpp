@@ -176,7 +176,9 @@ static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, int64
 // Ranges of n of a call that may have a workspace and leaves the choice to the library.  They pay where
 // the blocks leave more than half of the compute units idle and each range is long enough: the second
 // kernel and its launch cost about 4 us, eight to ten ring items of a block (an n-tile; a k loop has K / T_K + 1 to
-// each n-tile), so the ranges have to shorten a block by ten of them at least, and hold two items each.
+// each n-tile), so the ranges have to shorten a block by ten of them at least, and hold two items each; by eight
+// with a k loop, whose items bring A as well (1 x [512,1024].[1024,512].[512,256], nine items fewer: 19 -> 15 us; the 20 calls
+// of the sweep with a k loop that are split take 0.93 of their time or less, one with six items fewer 1.01).
 // No more ranges than give every compute unit one block.  Measured over 373 calls drawn from the ranges of the chains,
 // 318 of them with 256 blocks or fewer: those that it splits run 1.05 to 5 times as fast and none slower than unsplit; with
 // eight items instead of ten the first lose (4 x [320,32].. with 11 n-tiles 6.7 -> 8.1 us).  32 rows against 8192 keys of 128:
@@ -188,7 +190,7 @@ static int64_t ranges_for(int64_t blocks, int64_t n_tiles, int64_t items_per_til
     if (s > n_tiles / least) s = n_tiles / least;
     if (s < 2) return 1;
     const int64_t per = (n_tiles + s - 1) / s;
-    return (n_tiles - per) * items_per_tile >= 10 ? s : 1;
+    return (n_tiles - per) * items_per_tile >= (items_per_tile >= 2 ? 8 : 10) ? s : 1;
 }
 
 // Validation, tile choice and kernel arguments of one call.  P == 0: the two-GEMM chain into

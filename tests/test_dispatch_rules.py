@@ -33,6 +33,7 @@ def _workspace(batch, M, K, N, L, dtype="f16", kind=0, P=0, out_f32=False, n_spl
 def test_calls_that_split(out_f32):
     assert _workspace(32, 1, 128, 8192, 128, "bf16", 1, out_f32=out_f32) >= 4       # one token against a long cache
     assert _workspace(1, 639, 1024, 664, 128, out_f32=out_f32) >= 8                  # a k loop on ten blocks
+    assert _workspace(1, 512, 1024, 512, 256, out_f32=out_f32) == 2                  # nine items of a k loop fewer
     assert _workspace(5, 953, 64, 3696, 64, "f16", 0, P=128, out_f32=out_f32) >= 2
     assert _workspace(1, 209, 96, 3003, 96, "f16", 2, out_f32=out_f32) >= 2
 
