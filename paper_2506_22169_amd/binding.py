@@ -211,6 +211,13 @@ def make_problem(batch, M, K, N, L, dtype, a_stride=None, b_stride=None, d_strid
     return p
 
 
+def _refuse_one_element(*tensors):
+    """A tensor whose every stride is zero would read as packed to the C ABI."""
+    for t in tensors:
+        if t.numel() > 1 and all(s == 0 for n, s in zip(t.shape, t.stride()) if n > 1):
+            raise McfError(2, "an operand is one element broadcast over all of its extent")
+
+
 def _problem_from_tensors(A, B, D, E):
     if A.dim() != 3 or B.dim() != 3 or D.dim() != 3 or E.dim() != 3:
         raise McfError(1, "A, B, D, E must be 3-d [batch, rows, cols]")
@@ -219,6 +226,7 @@ def _problem_from_tensors(A, B, D, E):
     b3, N2, L = D.shape
     if not (b == b2 == b3 and K == K2 and N == N2 and tuple(E.shape) == (b, M, L)):
         raise McfError(1, f"shape mismatch A{tuple(A.shape)} B{tuple(B.shape)} D{tuple(D.shape)} E{tuple(E.shape)}")
+    _refuse_one_element(A, B, D, E)
     import torch
     if not (A.dtype == B.dtype == D.dtype and E.dtype in (A.dtype, torch.float32)):
         raise McfError(1, "A, B, D must share one dtype; E has that dtype or float32")
@@ -403,6 +411,7 @@ def tune_tiles3(A, B, D, F, scale=None, out=None, launches=0, population=0, top_
     if F.dim() != 3 or F.shape[0] != A.shape[0] or F.shape[1] != D.shape[2]:
         raise McfError(1, f"F{tuple(F.shape)} does not continue D{tuple(D.shape)}")
     P = F.shape[2]
+    _refuse_one_element(F, *(() if out is None else (out,)))
     if out is None:
         out = torch.empty((A.shape[0], A.shape[1], P), dtype=A.dtype, device=A.device)
     if tuple(out.shape) != (A.shape[0], A.shape[1], P) or not (F.dtype == A.dtype and out.dtype in (A.dtype, torch.float32)) \

@@ -48,6 +48,14 @@ void strides3(const at::Tensor &t, int64_t s[3]) {
     if (n0 <= 1) s[0] = 0;
 }
 
+// One element broadcast over a whole tensor: every stride is zero, which the C ABI reads as "packed".
+bool one_element(const at::Tensor &t) {
+    if (t.layout() != at::kStrided || t.numel() <= 1) return false;
+    for (int64_t d = 0; d < t.dim(); ++d)
+        if (t.size(d) > 1 && t.stride(d) != 0) return false;
+    return true;
+}
+
 bool is_tensor(PyObject *o) { return THPVariable_Check(o); }
 
 // chain(kind, scale, causal_offset, A, B, D, F, out, tiles, stream, n_split) -> out
@@ -73,6 +81,8 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
     if (B.size(0) != b || D.size(0) != b || B.size(1) != K || D.size(1) != N) return fail(MCF_EINVAL, "the shapes of A, B and D do not form a chain");
     if (F && (F->dim() != 3 || F->size(0) != b || F->size(1) != L)) return fail(MCF_EINVAL, "F does not continue D");
     const int64_t cols = F ? F->size(2) : L;
+    if (one_element(A) || one_element(B) || one_element(D) || (F && one_element(*F)) || (arg[7] != Py_None && one_element(THPVariable_Unpack(arg[7]))))
+        return fail(MCF_EUNSUPPORTED, "an operand is one element broadcast over all of its extent");
     const at::ScalarType type = A.scalar_type();
     if (!A.is_cuda() || !B.is_cuda() || !D.is_cuda()) return fail(MCF_EINVAL, "A, B, D, E must be device tensors");
     if (type != at::kHalf && type != at::kBFloat16) return fail(MCF_EUNSUPPORTED, "unsupported dtype of A");
