@@ -785,10 +785,13 @@ void chain_kernel(const KParams p) {
                 }
             }
             top();
-            phase_g2_prefetch(stage_c * STAGE);
+            const int n0 = ct * TN + wn * (32 * NJ);
+            if (n0 < N) { // (a wave with no column of a ragged tile stays out: its P = 0 would meet the rows that D's row N - 1 stands in for, and 0 x Inf is NaN)
+                phase_g2_prefetch(stage_c * STAGE);
+                phase_sm(n0);
+                phase_g2();
+            }
             stage_c = next_stage(stage_c);
-            phase_sm(ct * TN + wn * (32 * NJ)); // (a wave with no column of a ragged tile: all of C^T masked)
-            phase_g2();
         }
     } else if constexpr (PIPE) {
         // Software pipeline over n-tiles (softmax chains; plain chains with K and L of 32, where a
