@@ -41,7 +41,7 @@
 #include "mcf_internal.h"
 
 // The reference maximum of the online softmax follows the running row maximum only once that
-// has grown by more than this many binary orders of magnitude (0: always).
+// has grown by more than this many binary orders of magnitude (0: always, in every loop).
 #ifndef MCF_LAZY_MAX
 #define MCF_LAZY_MAX 8
 #endif
@@ -825,6 +825,13 @@ void chain_kernel(const KParams p) {
         };
         const int ncol0 = wn * (32 * NJ);
         constexpr int STANDS = 0, LAZY = 1, EXACT = 2;
+        // Kernels whose reference stands between the first tile and the last (see the loop) let p grow by 16 binary orders
+        // before it has to move.  fp16: from 1 to the largest fp16 (a sum of p D is far from the end of fp32 then, D being
+        // fp16 as well).  bf16: from 2^-8 to 2^8, because D reaches to the end of fp32 itself: a larger p would overflow sums whose
+        // quotient by the row sum does not, a smaller one lose products of the smallest D.
+        constexpr bool STAND = MCF_LAZY_MAX > 0 && reference_stands(KD, LD, MB, RG, NS, NJ, SOFTMAX, F_EXTRA);
+        constexpr int P_SHIFT = std::is_same<T, _Float16>::value ? 0 : 8;
+        constexpr float P_MOST = std::is_same<T, _Float16>::value ? 65504.f : 256.f;
         f32x16 cc[2][NJ][MB]; // C^T of the tile in the softmax and of the tile GEMM 1 is producing
         float mx[MB], mneg[MB], corr[MB], sum0[MB], sum1[MB];
 
@@ -865,7 +872,7 @@ void chain_kernel(const KParams p) {
                         // (under a mask) a row that has seen no column yet keeps m = -inf: p = 0, nothing to rescale
                         const bool blind = m_new == -INFINITY;
                         corr[mb] = blind ? 1.0f : __builtin_amdgcn_exp2f((m_run[mb] - m_new) * c1);
-                        mneg[mb] = blind ? 0.f : -m_new * c1;
+                        mneg[mb] = blind ? 0.f : STAND && P_SHIFT > 0 ? __builtin_fmaf(-m_new, c1, -(float)P_SHIFT) : -m_new * c1;
                         pin(mneg[mb]);
                         pin(corr[mb]);
                         m_run[mb] = m_new;
@@ -994,11 +1001,11 @@ void chain_kernel(const KParams p) {
         };
         // After a tile whose reference stood: whether some row sum of the wave says that it must move
         // (also for a NaN); otherwise the row sums are taken over.  A lane's sum is at least each of its p, which
-        // so stay within the range of fp16.
+        // so stay within P_MOST.
         auto outgrown = [&]() __attribute__((always_inline)) -> bool {
             bool any = false;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) any = any || !(sum0[mb] + sum1[mb] <= 16384.f);
+            for (int mb = 0; mb < MB; ++mb) any = any || !(sum0[mb] + sum1[mb] <= P_MOST);
             if (__builtin_amdgcn_ballot_w64(any) != 0) return true;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) l_run[mb] += sum0[mb] + sum1[mb];
@@ -1055,7 +1062,7 @@ void chain_kernel(const KParams p) {
             softmax_only(Buf0{}, Lazy{}, 0);
             // iterations 1 .. last-1, the two C^T buffers swap roles at compile time
             int i = 1;
-            if constexpr (reference_stands(KD, LD, MB, RG, NS, NJ, SOFTMAX, F_EXTRA)) {
+            if constexpr (STAND) {
                 // The reference m of the exponentials only has to keep them in range, and after the first
                 // tile it hardly ever has to move.  So these iterations leave it where it stands and look for no row
                 // maximum (a fifth of the vector work, and a chain of operations that the first exponential waited
@@ -1063,9 +1070,10 @@ void chain_kernel(const KParams p) {
                 // wave had seen no column before, the scores of the tile are computed once more (its B is still in the
                 // ring) and go through the softmax with their exact maximum.  No barrier depends on it.
                 // Measured (us a call, before and after): 64 x 4096 x 4096, bf16, K = L = 128, (1,8,1,2): 506 and 483,
-                // causal 32 x 4096 x 4096: 147 and 137; 64 x 4096 x 4096, fp16, K = L = 64: 326 and 308.  Scores
-                // of a standard deviation of 16 whose largest come last take the second way often: 75 and 93 us for 32 x
-                // 2048 x 2048, K = L = 128.  With one wave on a SIMD nothing covers the check behind a tile
+                // causal 32 x 4096 x 4096: 147 and 137; 64 x 4096 x 4096, fp16, K = L = 64: 326 and 308.  Scores of a
+                // standard deviation of 4 do not notice (32 x 2048 x 2048, bf16, K = L = 128: 79 and 72); large ones take the
+                // second way often: of 8 81 and 82, of 16 81 and 91, and 82 and 95 where they grow along the keys (64 x 2048 x
+                // 2048, fp16, K = L = 64: 92 and 102, 90 and 116, 97 and 116).  With one wave on a SIMD nothing covers the check behind a tile
                 // ((1,2,2,1): 32 x 2048 x 2048, K = L = 80: 104 and 120; K = L = 128: 122 and 136), so
                 // those kernels keep the maximum.
                 using Stands = std::integral_constant<int, STANDS>;

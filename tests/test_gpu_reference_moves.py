@@ -73,3 +73,26 @@ def test_results_do_not_depend_on_the_other_rows():
     keep = np.arange(256) != 7
     # half an ulp of every p on either side, weighed with at most max|D|, and half an ulp of the result on either side
     assert np.max(np.abs(calm[0, keep] - wild[0, keep])) <= 2.0**-10 * (np.max(np.abs(x["D"])) + np.max(np.abs(calm)))
+
+
+@pytest.mark.parametrize("kernel", [k for k in KERNELS if k[1] == "bf16"], ids=str)
+@pytest.mark.parametrize("col", [140, 300, 530])
+@pytest.mark.parametrize("exponent", [117, -118])
+def test_sums_stay_within_fp32(kernel, col, exponent):
+    """One score 2^11 above the reference of the first tile, and D at 2^118: a sum of p D with p of 2^11 is
+    beyond fp32 while every result is at most max|D|.  p may not grow past 2^8.  And D at 2^-117: nor may
+    p be so small that the products are lost."""
+    K, dtype, tiles = kernel
+    w = mi.make_problem(1, 300, K, 531, K, dtype, True, "normal", seed=9650 + K)
+    x = mi.make_inputs(w)
+    a, b = np.zeros((1, 300, K)), np.zeros((1, 531, K))
+    a[:, :, 0], b[:, col, 0] = 8.0, 0.95
+    d = mi.from_bits(x["d_bits"], dtype)
+    d = np.clip(d, -2.0, 2.0) * 2.0**exponent
+    bits = {"a_bits": mi.to_bits(a, dtype), "b_bits": mi.to_bits(b, dtype), "d_bits": mi.to_bits(d, dtype)}
+    A, B, D = device_inputs(w, dict(x, **bits))
+    print("case fp32 range", kernel, col, exponent, flush=True)
+    got = to_host64(mcf.softmax_gemm_chain(A, B, D, 1.0, tiles=tiles), dtype)
+    ref = oracle.chain(*(mi.from_bits(bits[k], dtype) if k != "b_bits" else mi.from_bits(bits[k], dtype).transpose(0, 2, 1)
+                         for k in ("a_bits", "b_bits", "d_bits")), softmax=True, scale=1.0)
+    _compare(got, ref, (kernel, col, exponent))
