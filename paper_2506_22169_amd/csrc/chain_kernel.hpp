@@ -999,13 +999,13 @@ void chain_kernel(const KParams p) {
             });
             if constexpr (decltype(modec)::value != STANDS) settle();
         };
-        // After a tile whose reference stood: whether some row sum of the wave says that it must move
-        // (also for a NaN); otherwise the row sums are taken over.  A lane's sum is at least each of its p, which
-        // so stay within P_MOST.
+        // After a tile whose reference stood: whether some row sum of the wave says that it must move;
+        // otherwise the row sums are taken over.  A lane's sum is at least each of its p, which so stay within
+        // P_MOST (a row with a NaN score is NaN whatever its reference: it moves none).
         auto outgrown = [&]() __attribute__((always_inline)) -> bool {
             bool any = false;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) any = any || !(sum0[mb] + sum1[mb] <= P_MOST);
+            for (int mb = 0; mb < MB; ++mb) any = any || sum0[mb] + sum1[mb] > P_MOST;
             if (__builtin_amdgcn_ballot_w64(any) != 0) return true;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) l_run[mb] += sum0[mb] + sum1[mb];
@@ -1081,7 +1081,7 @@ void chain_kernel(const KParams p) {
                 auto blind = [&]() __attribute__((always_inline)) -> bool {
                     bool any = false;
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) any = any || m_run[mb] == -INFINITY;
+                    for (int mb = 0; mb < MB; ++mb) any = any || (m_run[mb] == -INFINITY && l_run[mb] == 0.f); // (a row of NaN scores: l = NaN)
                     return __builtin_amdgcn_ballot_w64(any) != 0;
                 };
                 bool some_blind = blind();

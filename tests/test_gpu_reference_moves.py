@@ -96,3 +96,20 @@ def test_sums_stay_within_fp32(kernel, col, exponent):
     ref = oracle.chain(*(mi.from_bits(bits[k], dtype) if k != "b_bits" else mi.from_bits(bits[k], dtype).transpose(0, 2, 1)
                          for k in ("a_bits", "b_bits", "d_bits")), softmax=True, scale=1.0)
     _compare(got, ref, (kernel, col, exponent))
+
+
+@pytest.mark.parametrize("kernel", KERNELS, ids=str)
+def test_nan_rows_stay_by_themselves(kernel):
+    """A row of NaN scores is NaN, and the other rows of its wave are what they are without it, to the bit: such
+    a row moves no other row's reference and costs no second pass over a tile."""
+    K, dtype, tiles = kernel
+    w = mi.make_problem(1, 256, K, 531, K, dtype, True, "normal", seed=9680 + K)
+    x = mi.make_inputs(w)
+    A, B, D = device_inputs(w, x)
+    calm = to_host64(mcf.softmax_gemm_chain(A, B, D, w.scale, tiles=tiles), dtype)
+    A[0, 9, 0] = float("nan")
+    print("case nan rows", kernel, flush=True)
+    got = to_host64(mcf.softmax_gemm_chain(A, B, D, w.scale, tiles=tiles), dtype)
+    keep = np.arange(256) != 9
+    assert np.isnan(got[0, 9]).all()
+    assert np.array_equal(got[0, keep], calm[0, keep])
