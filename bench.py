@@ -288,9 +288,10 @@ def main():
     # the tile pick on the host (what a step does before its launch): timed on its own
     tp0 = time.perf_counter()
     for _ in range(200):
-        picked_auto = mcf.pick_tiles(prob, w.softmax)
+        mcf.pick_tiles(prob, w.softmax)
     pick_us = (time.perf_counter() - tp0) / 200 * 1e6
-    picked = picked_auto if tiles is None else mcf.eval_tiles(prob, *tiles, softmax=w.softmax)
+    # what the timed calls run: the pick with its waves arranged as a call arranges them, and the ranges of n
+    picked, n_ranges = mcf.call_tiles(prob, w.softmax, P=P if args.chain3 else 0, tiles=tiles)
 
     m = Timer(torch, args.steps, args.warmup, args.eager, rotate=n_sets).measure(step)
     t_step, t_kernel = m["t_step"], m["t_kernel"]
@@ -367,7 +368,7 @@ def main():
         "config": {"workload": f"{w.name}: batch={w.batch} M={w.M} K={w.K} N={w.N} L={w.L} {w.dtype}"
                                f"{' softmax' if w.softmax else ''}{f' + third GEMM P={P}' if args.chain3 else ''}",
                    "tiles": {"mb": picked.mb, "rg": picked.rg, "ns": picked.ns, "nj": picked.nj, "tm": picked.tm,
-                             "tn": picked.tn, "tk": picked.tk, "tl": picked.tl, "stages": picked.stages},
+                             "tn": picked.tn, "tk": picked.tk, "tl": picked.tl, "stages": picked.stages, "n_ranges": n_ranges},
                    "buffer_sets": n_sets, "launch": "eager" if args.eager else "hip_graph",
                    "replays": m["replays"], "graph_steps": m["graph_steps"], "timed_steps": m["graph_steps"] * m["replays"],
                    "clock_ramp_launches": m["clock_ramp_launches"], "clock_ramp_ms": round(m["clock_ramp_ms"], 1),

@@ -121,7 +121,7 @@ int mcf_list_candidates(const mcf_problem *problem, int softmax, mcf_tiles *out,
 /*
  * E = (A . B) . D   (Sec. III-A).  Device pointers; tiles_or_null == NULL means
  * mcf_pick_tiles() decides (where it takes four waves with an n-tile of 32 columns, or a softmax chain of four waves
- * with two slices each, the rows stay and the waves are arranged as measured faster), otherwise only its mb, rg, ns, nj and
+ * with two slices each, the rows stay and the waves are arranged as measured faster: mcf_call_tiles says how), otherwise only its mb, rg, ns, nj and
  * tl (0 = L) fields are read.  hip_stream is a
  * hipStream_t (NULL = the default stream).  E must not overlap A, B or D.  batch, M or L of
  * zero is a no-op; N == 0 writes zeros.
@@ -198,8 +198,16 @@ typedef struct mcf_call {
 int mcf_call_workspace(const mcf_call *call, int64_t *bytes);
 int mcf_call_run(const mcf_call *call, void *workspace, int64_t workspace_bytes, void *hip_stream);
 
-/* The arrangement mcf_gemm_chain3 takes when given no tiles; the model terms in *out are those
- * of its two-GEMM part (problem->e_stride is not read).  MCF_EUNSUPPORTED: none built. */
+/*
+ * What mcf_call_run runs for a call: the arrangement with its model terms (with P > 0 those of the two-GEMM
+ * part, and the LDS of the three-GEMM kernel) and the ranges of n (1: not split; 0, with *tiles zeroed:
+ * nothing to compute).  The calls without a workspace run the same with n_split = 1.  Host only; the
+ * pointers of the call are compared and checked for alignment, never read.
+ */
+int mcf_call_tiles(const mcf_call *call, mcf_tiles *tiles, int32_t *n_split);
+
+/* The arrangement the model ranks best for a chain of three (mcf_call_tiles says what a call runs); the model terms in
+ * *out are those of its two-GEMM part (problem->e_stride is not read).  MCF_EUNSUPPORTED: none built. */
 int mcf_pick_tiles3(const mcf_problem *problem, int64_t P, int softmax, mcf_tiles *out);
 
 /* The (mb, rg, ns, nj) built for the three-GEMM chain of this shape, as mcf_list_variants. */

@@ -141,7 +141,8 @@ def load_library():
         f.restype = ctypes.c_int
     lib.mcf_call_workspace.argtypes = [ctypes.POINTER(Call), ctypes.POINTER(ctypes.c_int64)]
     lib.mcf_call_run.argtypes = [ctypes.POINTER(Call), vp, ctypes.c_int64, vp]
-    for f in (lib.mcf_call_workspace, lib.mcf_call_run):
+    lib.mcf_call_tiles.argtypes = [ctypes.POINTER(Call), ctypes.POINTER(Tiles), ctypes.POINTER(ctypes.c_int32)]
+    for f in (lib.mcf_call_workspace, lib.mcf_call_run, lib.mcf_call_tiles):
         f.restype = ctypes.c_int
     lib.mcf_probe_copy.argtypes = [vp, vp, ctypes.c_int64, vp]
     lib.mcf_probe_mfma.argtypes = [vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, vp]
@@ -301,6 +302,20 @@ def pick_tiles(problem, softmax=False):
     return t
 
 
+def call_tiles(problem, softmax=False, P=0, causal_offset=None, tiles=None, n_split=0):
+    """mcf_call_tiles: the (Tiles, ranges of n) that a chain call on this problem runs; host only.
+    P: columns of F (0: two GEMMs), causal_offset: not None for the causal mask."""
+    c = Call()
+    c.problem, c.P, c.scale, c.n_split = problem, int(P), 1.0, int(n_split)
+    c.softmax, c.causal, c.causal_offset = int(bool(softmax)), int(causal_offset is not None), int(causal_offset or 0)
+    c.A, c.B, c.D, c.F, c.E = (1 << 40, 1 << 41, 1 << 42, 1 << 43 if P else None, 1 << 44)  # compared, never read
+    t = None if tiles is None else tiles if isinstance(tiles, Tiles) else _make_tiles(tiles)
+    c.tiles = None if t is None else ctypes.addressof(t)
+    out, ranges = Tiles(), ctypes.c_int32()
+    _check(load_library().mcf_call_tiles(ctypes.byref(c), ctypes.byref(out), ctypes.byref(ranges)))
+    return out, ranges.value
+
+
 def eval_tiles(problem, mb, rg, ns, nj=1, tl=0, softmax=False):
     """mcf_eval_tiles: model terms of a caller-chosen wave arrangement (and T_L; 0 = L); host only."""
     t = Tiles()
@@ -456,7 +471,7 @@ class _MetaLike:
 
 
 def pick_tiles3(problem, P, softmax=False):
-    """mcf_pick_tiles3: the arrangement gemm_chain3 takes when given no tiles."""
+    """mcf_pick_tiles3: the arrangement the model ranks best (call_tiles: the one gemm_chain3 runs)."""
     lib = load_library()
     t = Tiles()
     _check(lib.mcf_pick_tiles3(ctypes.byref(problem), int(P), int(bool(softmax)), ctypes.byref(t)))

@@ -335,6 +335,7 @@ int prepare(const mcf_call *call, Launch *o) {
         if (c.rows * (c.L >> 2) / 256 >= (1ll << 31) - 1 || c.split_stride > (1ll << 40)) return MCF_EUNSUPPORTED;
     }
     o->v = v;
+    o->tiles.mb = v->mb; o->tiles.rg = v->rg; o->tiles.ns = v->ns; o->tiles.nj = v->nj; o->tiles.tl = (int32_t)tl;
     return MCF_OK;
 }
 
@@ -404,6 +405,28 @@ extern "C" int mcf_call_workspace(const mcf_call *call, int64_t *bytes) {
     const int st = mcf::prepare(call, &o);
     *bytes = st == MCF_OK ? o.workspace_bytes : 0;
     return st;
+}
+
+extern "C" int mcf_call_tiles(const mcf_call *call, mcf_tiles *tiles, int32_t *n_split) {
+    if (!tiles || !n_split) return MCF_EINVAL;
+    memset(tiles, 0, sizeof(*tiles));
+    *n_split = 0;
+    mcf::Launch o;
+    int st = mcf::prepare(call, &o);
+    if (st != MCF_OK || !o.v) return st;
+    mcf_problem p = call->problem;
+    if (call->P > 0) memset(p.e_stride, 0, sizeof(p.e_stride)); // they describe G there
+    memcpy(tiles, &o.tiles, sizeof(o.tiles));
+    st = mcf_eval_tiles(&p, o.softmax, tiles);
+    if (st != MCF_OK && st != MCF_EINVAL) return st; // (MCF_EINVAL: over a budget of the model, which given tiles may be)
+    if (call->P > 0) {
+        tiles->lds_bytes = mcf::lds_bytes_for(o.v);
+        tiles->stages = mcf::stages_for(o.v);
+        tiles->vgpr_used = o.v->vgprs;
+        tiles->scratch_bytes = o.v->scratch_bytes;
+    }
+    *n_split = o.k.n_split;
+    return MCF_OK;
 }
 
 extern "C" int mcf_call_run(const mcf_call *call, void *workspace, int64_t workspace_bytes, void *stream) {

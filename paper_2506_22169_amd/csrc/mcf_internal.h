@@ -133,6 +133,7 @@ struct Launch {
     CombineParams c;
     int64_t workspace_bytes;
     int32_t dtype, softmax;
+    mcf_tiles tiles; // mb, rg, ns, nj, tl of v
 };
 int prepare(const mcf_call *call, Launch *out); // MCF_OK or an error status; host only
 int launch(Launch *l, void *workspace, int64_t workspace_bytes, void *stream);

@@ -58,3 +58,53 @@ def test_ranges_fill_and_do_not_overfill(N, blocks):
     assert r <= n_tiles
     assert (r == 0) if 2 * blocks > 256 or N <= 10 * 32 else True
     assert t.blocks == blocks
+
+
+def _ran(batch, M, K, N, L, kind=0, P=0, dtype="f16", **kw):
+    p = make_problem(batch, M, K, N, L, dtype, b_stride=(N * K, 1, K) if kind else None)
+    t, ranges = mcf.call_tiles(p, kind > 0, P=P, causal_offset=N - M if kind == 2 else None, **kw)
+    return (t.mb, t.rg, t.ns, t.nj, t.tl), ranges, t
+
+
+def test_calls_say_what_they_run():
+    """mcf_call_tiles: the settled arrangement and the ranges, where they differ from the model's pick."""
+    # (the arrangement run, the pick): a ragged N that pads least with 32 columns, on eight waves
+    for shape, run, picked in (((15, 1635, 64, 4048, 128), (1, 4, 2, 2, 128), (1, 4, 1, 1)),
+                               ((128, 2881, 128, 976, 128), (1, 4, 2, 2, 128), (1, 4, 1, 1)),   # ... also with many blocks
+                               ((45, 2090, 80, 1248, 80), (1, 4, 2, 2, 80), (1, 4, 1, 1)),
+                               ((64, 512, 64, 512, 64), (1, 4, 2, 2, 64), (1, 4, 2, 2))):
+        got, ranges, t = _ran(*shape)
+        q = mcf.pick_tiles(make_problem(*shape, "f16"))
+        assert (got, ranges, (q.mb, q.rg, q.ns, q.nj)) == (run, 1, picked), shape
+        assert t.blocks == q.blocks and t.tm == q.tm and t.lds_bytes <= 160 * 1024
+    assert _ran(5, 3887, 64, 2207, 64, kind=1)[:2] == ((1, 4, 2, 2, 64), 1)
+    assert _ran(35, 1364, 128, 1096, 128, kind=1)[0][:4] == (1, 4, 1, 1)      # softmax, more blocks than compute units: stays
+    assert _ran(40, 333, 80, 1357, 80, kind=2)[:2] == ((1, 2, 2, 1, 80), 1)  # rows padded to the pitch: one slice a wave
+    assert _ran(32, 1, 128, 8192, 128, kind=1)[1] == 4
+    assert _ran(1, 512, 1024, 512, 256)[1] == 2
+    # given tiles and ranges are what runs; the calls without a workspace never split
+    assert _ran(32, 1, 128, 8192, 128, kind=1, tiles=(1, 1, 4, 1))[:2] == ((1, 1, 4, 1, 128), 1)
+    assert _ran(32, 1, 128, 8192, 128, kind=1, tiles=(1, 1, 4, 1, 64), n_split=3)[:2] == ((1, 1, 4, 1, 64), 3)
+    assert _ran(32, 1, 128, 8192, 128, kind=1, n_split=1)[1] == 1
+    assert _ran(0, 512, 64, 512, 64)[:2] == ((0, 0, 0, 0, 0), 0)             # nothing to compute
+
+
+def test_call_tiles_of_three_gemms_describe_that_kernel():
+    got, ranges, t = _ran(32, 2048, 128, 2048, 128, kind=1, P=128, dtype="bf16")
+    assert got == (1, 8, 1, 2, 128) and ranges == 1
+    q = mcf.pick_tiles3(make_problem(32, 2048, 128, 2048, 128, "bf16", b_stride=(2048 * 128, 1, 128)), 128, True)
+    assert (t.lds_bytes, t.blocks) == (q.lds_bytes, q.blocks)
+    with pytest.raises(mcf.McfError):
+        _ran(32, 512, 128, 512, 128, P=64)                                   # not built
+
+
+def test_call_tiles_refuses_what_the_call_refuses():
+    lib, t, r = binding.load_library(), binding.Tiles(), ctypes.c_int32(7)
+    c = binding.Call()
+    assert lib.mcf_call_tiles(None, ctypes.byref(t), ctypes.byref(r)) == 1
+    assert lib.mcf_call_tiles(ctypes.byref(c), None, ctypes.byref(r)) == 1
+    assert lib.mcf_call_tiles(ctypes.byref(c), ctypes.byref(t), None) == 1
+    c.problem, c.scale = make_problem(2, 64, 64, 64, 64, "f16"), 1.0
+    c.A, c.B, c.D, c.E = 1 << 40, 1 << 41, 1 << 42, 1 << 40                  # E aliases A
+    assert lib.mcf_call_tiles(ctypes.byref(c), ctypes.byref(t), ctypes.byref(r)) == 1
+    assert r.value == 0 and t.mb == 0
