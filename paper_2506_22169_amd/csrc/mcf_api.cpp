@@ -142,6 +142,8 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 //  * Where a ragged N pads least with it, it takes the narrowest n-tile.  Four waves with an n-tile of 32 columns
 //    give way to eight with 128 (or 64) on the same rows: 15 x [1635,64].[64,4048].[4048,128] 85 -> 40 us, softmax
 //    5 x 3887 x 2207, K = L = 64: 34 -> 24 us, three GEMMs 20 x [827,128].[128,1112].[1112,64].[64,64] 25 -> 15 us.
+//    Plain chains also with many blocks (45 drawn calls of 260 to 3300 blocks: where it acts 0.71 to 0.92 of the time, none
+//    slower; 32 x [2881,128].[128,976].[976,128], 736 blocks: 65 -> 56 us).
 //    A softmax chain with more blocks than compute units stays: two blocks of four waves share a unit as well
 //    (causal, 2376 blocks, K = L = 64: 1.10 of the time with eight).
 //  * Among equal estimates it takes the wider n-tile.  Softmax kernels of four waves whose rows are padded to the
