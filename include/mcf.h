@@ -180,6 +180,7 @@ int mcf_gemm_chain3(const mcf_problem *problem, int softmax, float scale, int64_
  *   P, f_stride, F  : as mcf_gemm_chain3; P = 0: a chain of two GEMMs (F is not read)
  *   softmax, causal : as the calls above (causal implies softmax; MCF_EUNSUPPORTED with P > 0)
  *   n_split         : ranges of n (cut to the number of n-tiles); 0: the library decides, which is 1 where tiles are given
+ *                     and with P > 0 (there every range rounds its part of E before the third GEMM, as a wave does)
  * mcf_call_workspace: the bytes such a call wants (0: it does not split n); host only.
  * mcf_call_run      : device pointer workspace (16-byte aligned, MCF_EINVAL if smaller than that, may be
  *                     NULL for 0 bytes), in use until the call's work on hip_stream is done.

@@ -141,7 +141,7 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 // a block beside its loads and flops (a barrier, an LDS round trip, the load latency a short ring leaves bare).
 //  * Where a ragged N pads least with it, it takes the narrowest n-tile.  Four waves with an n-tile of 32 columns
 //    give way to eight with 128 (or 64) on the same rows: 15 x [1635,64].[64,4048].[4048,128] 85 -> 40 us, softmax
-//    5 x 3887 x 2207, K = L = 64: 34 -> 24 us, three GEMMs 20 x [827,128].[128,1112].[1112,64].[64,64] 25 -> 15 us.
+//    5 x 3887 x 2207, K = L = 64: 34 -> 24 us.
 //    Plain chains also with many blocks (45 drawn calls of 260 to 3300 blocks: where it acts 0.71 to 0.92 of the time, none
 //    slower; 32 x [2881,128].[128,976].[976,128], 736 blocks: 65 -> 56 us).
 //    A softmax chain with more blocks than compute units stays: two blocks of four waves share a unit as well
@@ -149,18 +149,17 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 //  * Among equal estimates it takes the wider n-tile.  Softmax kernels of four waves whose rows are padded to the
 //    LDS pitch (K = 80, 96, 160, 192) spill scalar registers with two slices a wave, and run better with one: the calls
 //    of a sweep that were picked so take 0.80 to 1.02 of their time; causal 40 x 333 x 1357, K = L = 80: 23 -> 20.5 us.
-//    With K = 128 and 256 the two are level (0.97 to 1.09); for three GEMMs the wider is better (1.06).
+//    With K = 128 and 256 the two are level (0.97 to 1.09).
+// Chains of three GEMMs keep the pick: a wave that holds part of a row's n range rounds its part of E to 16 bits before the
+// third GEMM, which is the caller's or the model's choice and not one to be made behind it (parts that cancel, or that
+// leave fp16, are lost).
 static int64_t padding_of(int64_t n, int64_t tn) { return (n + tn - 1) / tn * tn - n; }
-static bool built(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, int64_t tn_now, mcf_tiles *t) {
-    if (P > 0) {
-        const Variant *v = find_variant3(p->in_dtype, p->K, p->L, P, softmax, b_kcontig, t->mb, t->rg, t->ns, t->nj);
-        if (!v || !v->launch || v->scratch_bytes != 0 || lds_bytes_for(v) > kLdsBytesPerBlock) return false;
-    }
+static bool built(const mcf_problem *p, int softmax, int64_t tn_now, mcf_tiles *t) {
     if (mcf_eval_tiles(p, softmax, t) != MCF_OK) return false;
     const int64_t pad = padding_of(p->N, t->tn);
     return 20 * pad < p->N || pad <= padding_of(p->N, tn_now); // Rule 3
 }
-static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mcf_tiles *t) {
+static void settle_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
     if (t->tk < p->K) return; // a k loop: measured as it is
     mcf_tiles w;
     memset(&w, 0, sizeof(w));
@@ -168,10 +167,10 @@ static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, int64
     if (t->mb == 1 && t->rg == 4 && t->ns == 1 && t->nj == 1 && (!softmax || t->blocks <= kComputeUnits)) {
         w.ns = 2;
         for (w.nj = 2; w.nj >= 1; --w.nj)
-            if (built(p, softmax, b_kcontig, P, t->tn, &w)) { *t = w; return; }
-    } else if (softmax && P == 0 && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2 && pitch_elems(t->tk) != t->tk) {
+            if (built(p, softmax, t->tn, &w)) { *t = w; return; }
+    } else if (softmax && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2 && pitch_elems(t->tk) != t->tk) {
         w.nj = 1;
-        if (built(p, softmax, b_kcontig, P, t->tn, &w)) *t = w;
+        if (built(p, softmax, t->tn, &w)) *t = w;
     }
 }
 
@@ -184,7 +183,8 @@ static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, int64
 // No more ranges than give every compute unit one block.  Measured over 373 calls drawn from the ranges of the chains,
 // 318 of them with 256 blocks or fewer: those that it splits run 1.05 to 5 times as fast and none slower than unsplit; with
 // eight items instead of ten the first lose (4 x [320,32].. with 11 n-tiles 6.7 -> 8.1 us).  32 rows against 8192 keys of 128:
-// 92 -> 33 us; 1 x [639,1024].[1024,664].[664,128]: 100 -> 19 us.
+// 92 -> 33 us; 1 x [639,1024].[1024,664].[664,128]: 100 -> 19 us.  Chains of three are not split unasked: each range would
+// round its part of E before the third GEMM.
 static int64_t ranges_for(int64_t blocks, int64_t n_tiles, int64_t items_per_tile) {
     if (blocks <= 0 || 2 * blocks > kComputeUnits) return 1;
     const int64_t least = items_per_tile >= 2 ? 1 : 2; // n-tiles of a range
@@ -255,7 +255,7 @@ int prepare(const mcf_call *call, Launch *o) {
     } else {
         st = ch3 ? pick3(p, softmax, lay.b_kcontig, P, &chosen) : mcf_pick_tiles(p, softmax, &chosen);
         if (st != MCF_OK) return st;
-        settle_tiles(p, softmax, lay.b_kcontig, P, &chosen);
+        if (!ch3) settle_tiles(p, softmax, &chosen);
     }
     const int64_t tl = ch3 ? p->L : (chosen.tl > 0 ? chosen.tl : p->L);
     if (p->L % tl != 0) return MCF_EINVAL;
@@ -316,7 +316,7 @@ int prepare(const mcf_call *call, Launch *o) {
     // n ranges of whole n-tiles, each a row of blocks of its own; more would leave some empty
     const int64_t tn = 32ll * v->ns * v->nj, n_tiles = (p->N + tn - 1) / tn;
     int64_t n_split = call->n_split;
-    if (n_split == 0) n_split = call->tiles ? 1 : ranges_for(k.n_blocks, n_tiles, v->ksplit ? k.k_chunks + 1 : 1);
+    if (n_split == 0) n_split = call->tiles || ch3 ? 1 : ranges_for(k.n_blocks, n_tiles, v->ksplit ? k.k_chunks + 1 : 1);
     int64_t per = n_split < n_tiles ? (n_tiles + n_split - 1) / n_split : 1;
     n_split = n_tiles > 0 ? (n_tiles + per - 1) / per : 1;
     k.n_split = (int32_t)n_split;

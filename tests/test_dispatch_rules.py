@@ -34,7 +34,6 @@ def test_calls_that_split(out_f32):
     assert _workspace(32, 1, 128, 8192, 128, "bf16", 1, out_f32=out_f32) >= 4       # one token against a long cache
     assert _workspace(1, 639, 1024, 664, 128, out_f32=out_f32) >= 8                  # a k loop on ten blocks
     assert _workspace(1, 512, 1024, 512, 256, out_f32=out_f32) == 2                  # nine items of a k loop fewer
-    assert _workspace(5, 953, 64, 3696, 64, "f16", 0, P=128, out_f32=out_f32) >= 2
     assert _workspace(1, 209, 96, 3003, 96, "f16", 2, out_f32=out_f32) >= 2
 
 
@@ -43,6 +42,8 @@ def test_calls_that_do_not_split():
     assert _workspace(1, 1024, 64, 128, 64) == 0            # one n-tile
     assert _workspace(4, 128, 64, 512, 64, "f16", 1) == 0   # nothing to win: a few n-tiles
     assert _workspace(32, 1, 128, 8192, 128, "bf16", 1, n_split=1) == 0
+    assert _workspace(5, 953, 64, 3696, 64, "f16", 0, P=128) == 0  # three GEMMs: a range would round its part of E
+    assert _workspace(5, 953, 64, 3696, 64, "f16", 0, P=128, n_split=3) == 3
     assert _workspace(32, 1, 128, 8192, 128, "bf16", 1, tiles=(1, 1, 4, 1)) == 0  # arrangement given
     assert _workspace(32, 1, 128, 8192, 128, "bf16", 1, tiles=(1, 1, 4, 1), n_split=4) == 4
 
@@ -96,6 +97,15 @@ def test_call_tiles_of_three_gemms_describe_that_kernel():
     assert (t.lds_bytes, t.blocks) == (q.lds_bytes, q.blocks)
     with pytest.raises(mcf.McfError):
         _ran(32, 512, 128, 512, 128, P=64)                                   # not built
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("M,N", [(827, 1112), (128, 4096), (1635, 4048), (64, 64)])
+def test_three_gemms_run_the_pick(kind, M, N):
+    """No wave or range gets a part of E to round that the model's pick does not give it."""
+    for K, L, P in ((64, 64, 64), (128, 64, 64), (64, 64, 128), (128, 128, 128)):
+        q = mcf.pick_tiles3(make_problem(3, M, K, N, L, "f16", b_stride=(N * K, 1, K) if kind else None), P, kind > 0)
+        assert _ran(3, M, K, N, L, kind=kind, P=P)[:2] == ((q.mb, q.rg, q.ns, q.nj, L), 1)
 
 
 def test_call_tiles_refuses_what_the_call_refuses():
