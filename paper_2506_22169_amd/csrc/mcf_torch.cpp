@@ -5,6 +5,7 @@
 #include <Python.h>
 
 #include <ATen/ops/empty.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -122,11 +123,13 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
         mcf::Launch l;
         st = mcf::prepare(&call, &l);
         if (st == MCF_OK) {
-            // The workspace of split ranges comes from torch's allocator for the stream that the call runs
-            // on: freed here, it is only handed out again to later work of that stream.  Where there is no
-            // room for one, ranges that the library chose are not needed.
+            // The workspace of split ranges comes from torch's allocator for the device of the operands (which need not
+            // be the current one) and the stream that the call runs on: freed here, it is only handed out again to later work of
+            // that stream.  Where there is no room for one, ranges that the library chose are not needed.
             void *ws = nullptr;
             try {
+                c10::OptionalDeviceGuard on;
+                if (l.workspace_bytes > 0) on.reset_device(A.device());
                 if (l.workspace_bytes > 0) ws = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)l.workspace_bytes, (hipStream_t)stream);
             } catch (const c10::OutOfMemoryError &) {
                 if (n_split != 0) throw;

@@ -105,3 +105,20 @@ def test_split_ranges_on_streams_and_in_graphs():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(E, alone)
+
+
+@pytest.mark.skipif(torch.cuda.device_count() < 2, reason="needs a second device")
+def test_workspace_lives_with_the_operands():
+    """Operands and stream of a device that is not the current one: so does the workspace."""
+    case = ("softmax", 4, 64, 64, 1000, 64, 0, "f16", 0, (1, 1, 4, 1), 4)
+    call, _, _ = _run(case)
+    alone = call(4)
+    with torch.cuda.device(1):
+        there, _, _ = _run(case, stream=torch.cuda.Stream())
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_stats(0)["allocation.all.allocated"]
+    print("case split on the second device", flush=True)
+    E = there(4)
+    torch.cuda.synchronize(1)
+    assert E.device.index == 1 and torch.equal(E.cpu(), alone.cpu())
+    assert torch.cuda.memory_stats(0)["allocation.all.allocated"] == before
