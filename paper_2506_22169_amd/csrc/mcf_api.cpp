@@ -359,6 +359,13 @@ int launch(Launch *o, void *workspace, int64_t workspace_bytes, void *stream) {
     return MCF_OK;
 }
 
+bool stream_capturing(void *stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError(); // (the default stream while another one is captured): the launch will say so itself
+    return false;
+}
+
 // The calls without a workspace: n is never split.
 static int run(const mcf_problem *p, int softmax, float scale, const void *A, const void *B, const void *D, void *E,
                const mcf_tiles *tiles, void *stream, int64_t P = 0, const int64_t *fstr = nullptr,

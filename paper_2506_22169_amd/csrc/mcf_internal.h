@@ -138,6 +138,8 @@ struct Launch {
 int prepare(const mcf_call *call, Launch *out); // MCF_OK or an error status; host only
 int launch(Launch *l, void *workspace, int64_t workspace_bytes, void *stream);
 
+bool stream_capturing(void *stream); // whether work on the stream is being recorded into a graph
+
 void set_last_error(const char *msg);
 
 } // namespace mcf

@@ -7,6 +7,7 @@
 #include <ATen/ops/empty.h>
 #include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPCachingAllocator.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -55,6 +56,23 @@ bool one_element(const at::Tensor &t) {
     for (int64_t d = 0; d < t.dim(); ++d)
         if (t.size(d) > 1 && t.stride(d) != 0) return false;
     return true;
+}
+
+// The workspace of a call from torch's allocator, for the device of its operands (which need not be the current one) and the
+// stream that the call runs on: given back right after the launches, it is only handed out again to later work of that
+// stream.  While the stream is captured it has to stay with the graph instead.  torch's own capture allocates from the graph's
+// pool, which does that; where someone else captures, memory given back would be used by others between the replays:
+// nullptr then (and in any capture nothing here may end it, so that an allocation is allowed to reach the driver).
+void *workspace(size_t bytes, hipStream_t stream, c10::Device device) {
+    namespace alloc = c10::hip::HIPCachingAllocator;
+    c10::DeviceGuard on(device);
+    if (!mcf::stream_capturing(stream)) return alloc::raw_alloc_with_stream(bytes, stream);
+    c10::hip::HIPStreamCaptureModeGuard allowed(hipStreamCaptureModeRelaxed);
+    void *ws = alloc::raw_alloc_with_stream(bytes, stream);
+    for (const auto &seg : alloc::snapshot().segments)
+        if ((size_t)ws - seg.address < seg.total_size && seg.owner_private_pool_id != c10::MempoolId_t(0, 0)) return ws;
+    alloc::raw_delete(ws);
+    return nullptr;
 }
 
 bool is_tensor(PyObject *o) { return THPVariable_Check(o); }
@@ -123,16 +141,15 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
         mcf::Launch l;
         st = mcf::prepare(&call, &l);
         if (st == MCF_OK) {
-            // The workspace of split ranges comes from torch's allocator for the device of the operands (which need not
-            // be the current one) and the stream that the call runs on: freed here, it is only handed out again to later work of
-            // that stream.  Where there is no room for one, ranges that the library chose are not needed.
+            // where there is no workspace to be had, ranges that the library chose are not needed
             void *ws = nullptr;
             try {
-                c10::OptionalDeviceGuard on;
-                if (l.workspace_bytes > 0) on.reset_device(A.device());
-                if (l.workspace_bytes > 0) ws = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)l.workspace_bytes, (hipStream_t)stream);
+                if (l.workspace_bytes > 0) ws = workspace((size_t)l.workspace_bytes, (hipStream_t)stream, A.device());
             } catch (const c10::OutOfMemoryError &) {
                 if (n_split != 0) throw;
+            }
+            if (l.workspace_bytes > 0 && !ws) {
+                if (n_split != 0) return fail(MCF_EUNSUPPORTED, "ranges of n in a graph that torch does not capture");
                 call.n_split = 1;
                 st = mcf::prepare(&call, &l);
                 if (st != MCF_OK) return fail_status(st);

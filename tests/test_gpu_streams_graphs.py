@@ -1,6 +1,9 @@
 """The launches are asynchronous on the caller's stream and allocate nothing, so they can be
 captured into a HIP graph and run on several streams at once.  Replays are checked against
 the eager result every time, with eager work and synchronisations between them."""
+import ctypes
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -73,3 +76,69 @@ def test_concurrent_streams():
         assert torch.equal(out, alone)
         ref = oracle.chain(x["A"], x["B"], x["D"], softmax=w.softmax, scale=w.scale)
         assert np.max(np.abs(to_host64(out, "bf16") - ref)) <= TOL * np.max(np.abs(ref))
+
+
+# calls whose n the library splits by itself: a softmax on few blocks, and a k loop
+SPLIT = [(4, 64, 64, 4096, 64, True), (1, 128, 1024, 1000, 128, False)]
+
+
+def _split_call(b, M, K, N, L, softmax):
+    w = mi.make_problem(b, M, K, N, L, "f16", softmax, "normal" if softmax else "uniform", seed=4400 + N)
+    A, B, D = device_inputs(w, mi.make_inputs(w))
+    problem = mcf.binding.make_problem(b, M, K, N, L, "f16", b_stride=(N * K, 1, K) if softmax else None)
+    assert mcf.call_tiles(problem, softmax)[1] > 1
+    code = 1 if softmax else 0
+    return lambda out=None, n_split=0, stream=None: mcf.binding._call(code, w.scale, 0, A, B, D, None, out, None, stream, n_split)
+
+
+@pytest.mark.parametrize("case", SPLIT, ids=str)
+def test_split_calls_captured_by_torch(case):
+    """The ranges are captured with a workspace of the graph's own: tensors that come and go between the
+    replays do not meet it."""
+    call = _split_call(*case)
+    split, whole = call(), call(n_split=1)
+    torch.cuda.synchronize()
+    assert not torch.equal(split, whole)      # two kernels and another order of the sums
+    E = torch.zeros_like(split)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(E)
+    for rep in range(4):
+        print(f"case split capture replay {rep}", case, flush=True)
+        E.fill_(-3.0)
+        junk = [torch.full((1 << k,), float("nan"), device="cuda") for k in range(10, 22)]
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(E, split)
+        del junk
+
+
+@pytest.mark.parametrize("case", SPLIT, ids=str)
+def test_calls_captured_by_others_are_not_split(case):
+    """A stream that the HIP runtime captures for someone else: torch's allocator knows nothing of the graph, so the call
+    takes no workspace from it and n stays whole, as one kernel."""
+    hip = ctypes.CDLL(re.search(r"\S*/libamdhip64\.so\S*", open("/proc/self/maps").read()).group())  # the one torch runs on
+    call = _split_call(*case)
+    whole = call(n_split=1)                   # eager: also sets the kernel's attributes before the capture
+    E, ref = torch.zeros_like(whole), whole.clone()
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    handle, graph, exe, n = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_size_t()
+    print("case foreign capture", case, flush=True)
+    assert hip.hipStreamBeginCapture(handle, 1) == 0          # thread-local mode
+    try:
+        call(E, stream=stream)
+        with pytest.raises(mcf.McfError) as refused:
+            call(E, n_split=2, stream=stream)
+    finally:
+        assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert refused.value.status == 2
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0 and n.value == 1
+    assert hip.hipGraphInstantiate(ctypes.byref(exe), graph, None, None, ctypes.c_size_t(0)) == 0
+    for rep in range(3):
+        E.fill_(-3.0)
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(exe, handle) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(E, ref)
+    assert hip.hipGraphExecDestroy(exe) == 0 and hip.hipGraphDestroy(graph) == 0
