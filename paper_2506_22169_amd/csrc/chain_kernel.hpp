@@ -872,8 +872,12 @@ void chain_kernel(const KParams p) {
                         // (under a mask) a row that has seen no column yet keeps m = -inf: p = 0, nothing to rescale
                         const bool blind = m_new == -INFINITY;
                         corr[mb] = blind ? 1.0f : __builtin_amdgcn_exp2f((m_run[mb] - m_new) * c1);
-                        mneg[mb] = blind ? 0.f : STAND && P_SHIFT > 0 ? __builtin_fmaf(-m_new, c1, -(float)P_SHIFT) : -m_new * c1;
+                        mneg[mb] = blind ? 0.f : -m_new * c1;
                         pin(mneg[mb]);
+                        if constexpr (STAND && P_SHIFT > 0) { // (behind the pin: fused with the product it costs registers, and K = L = 32 a block)
+                            mneg[mb] -= (float)P_SHIFT;
+                            pin(mneg[mb]);
+                        }
                         pin(corr[mb]);
                         m_run[mb] = m_new;
                         sum0[mb] = 0.f;

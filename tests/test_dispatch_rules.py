@@ -118,3 +118,19 @@ def test_call_tiles_refuses_what_the_call_refuses():
     c.A, c.B, c.D, c.E = 1 << 40, 1 << 41, 1 << 42, 1 << 40                  # E aliases A
     assert lib.mcf_call_tiles(ctypes.byref(c), ctypes.byref(t), ctypes.byref(r)) == 1
     assert r.value == 0 and t.mb == 0
+
+
+# Kernels that stand at the edge of a block more or less per compute unit: K, L, P, softmax, B as [b,N,K], arrangement, blocks
+RESIDENT = [(32, 32, 0, 1, 0, (1, 4, 1, 1), 5), (32, 32, 0, 1, 1, (1, 2, 2, 1), 5)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("kernel", RESIDENT, ids=str)
+def test_blocks_a_compute_unit_holds(kernel, dtype):
+    """Registers (allocated by eight, 512 a lane and SIMD) and LDS (160 KiB) leave room for that many blocks,
+    and nothing spills in a loop."""
+    K, L, P, softmax, nk, tiles, blocks = kernel
+    p = make_problem(64, 512, K, 512, L, dtype, b_stride=(512 * K, 1, K) if nk else None)
+    t, _ = mcf.call_tiles(p, bool(softmax), P=P, tiles=tiles)
+    waves = 512 // ((t.vgpr_used + 7) // 8 * 8)
+    assert min(4 * waves // t.waves, 160 * 1024 // t.lds_bytes) >= blocks and t.scratch_bytes == 0
