@@ -137,8 +137,16 @@ template <int N> static __device__ __forceinline__ void wait_vm() {
 // PD > 0: chain of three GEMMs.  After the n loop the block multiplies its E tile (still in
 // registers) by F[L x PD], which waits in LDS from the prologue on, and stores that product
 // instead of E.  The rows of E must then be complete within a wave: NS = 1.
-// Waves per SIMD the compiler is to leave room for (pipelined softmax kernels that can have two
-// blocks resident; everything else: what the block size itself implies).
+// LDS bytes of an instantiation.
+template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD>
+constexpr int kernel_lds_bytes() {
+    constexpr int S = ring_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD > 0 ? chain3_f_bytes(LD, PD) + 1024 : 0);
+    if constexpr (PD > 0) return chain3_lds_bytes(KD, LD, PD, MB, RG, NS, NJ, S);
+    else return total_lds_bytes(KD, LD, MB, RG, NS, NJ, S, KSPLIT);
+}
+
+// Waves per SIMD the compiler is to leave room for (kernels that can have two blocks resident; everything
+// else: what the block size itself implies).
 template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD> constexpr int waves_per_simd() {
     constexpr int extra = PD > 0 ? chain3_f_bytes(LD, PD) + 1024 : 0;
     if (pipe_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, extra) > 0) return pipe_waves_per_simd(KD, LD, MB, RG, NS, NJ, extra);
@@ -147,6 +155,13 @@ template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSP
     // operands and load offsets (with all of it the compiler keeps accumulators in the accumulation half
     // and moves them out and back; with fewer left it spills)
     if (KSPLIT && MB * h_blocks(LD) * 16 + NJ * MB * (16 + 8) + 150 <= 256) return per_block > 2 ? per_block : 2;
+    // a block of 8 waves that is not pipelined: room for a second one where two fit the LDS and the tiles a lane must hold leave
+    // it 24 of 128 registers.  Left alone the compiler takes 127 to 133 for the kernels at that edge, and three registers
+    // too many are a block: plain K = L = 64, (1,4,2,2): 160 x 512 x 512 18.7 -> 16.4 us, 300 x 512 x 1024 46.4 -> 40.6
+    // us; three GEMMs of that size 20.3 -> 17.2 us.
+    if (!KSPLIT && per_block == 2 && 2 * kernel_lds_bytes<KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD>() <= 160 * 1024 &&
+        MB * (KD / 16) * 4 + MB * h_blocks(LD) * 16 + NJ * MB * (16 + 8) + 24 <= 512 / (2 * per_block))
+        return 2 * per_block;
     return per_block;
 }
 template <typename T, int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool BKC, bool KSPLIT = false, int PD = 0>
@@ -1465,14 +1480,6 @@ void chain_kernel(const KParams p) {
 }
 
 // Host-side launcher of one instantiation.
-// LDS bytes of an instantiation.
-template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD>
-constexpr int kernel_lds_bytes() {
-    constexpr int S = ring_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD > 0 ? chain3_f_bytes(LD, PD) + 1024 : 0);
-    if constexpr (PD > 0) return chain3_lds_bytes(KD, LD, PD, MB, RG, NS, NJ, S);
-    else return total_lds_bytes(KD, LD, MB, RG, NS, NJ, S, KSPLIT);
-}
-
 template <typename T, int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool BKC, bool KSPLIT = false, int PD = 0>
 int launch_chain(const KParams &p, void *stream) {
     constexpr int lds = kernel_lds_bytes<KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD>();

@@ -121,7 +121,9 @@ def test_call_tiles_refuses_what_the_call_refuses():
 
 
 # Kernels that stand at the edge of a block more or less per compute unit: K, L, P, softmax, B as [b,N,K], arrangement, blocks
-RESIDENT = [(32, 32, 0, 1, 0, (1, 4, 1, 1), 5), (32, 32, 0, 1, 1, (1, 2, 2, 1), 5)]
+RESIDENT = [(32, 32, 0, 1, 0, (1, 4, 1, 1), 5), (32, 32, 0, 1, 1, (1, 2, 2, 1), 5), (64, 64, 0, 0, 0, (1, 4, 2, 2), 2),
+            (64, 128, 0, 0, 0, (1, 8, 1, 1), 2), (64, 128, 0, 0, 1, (1, 8, 1, 1), 2), (64, 64, 64, 0, 0, (1, 4, 2, 2), 2),
+            (64, 64, 0, 1, 1, (1, 4, 2, 1), 2), (64, 64, 0, 1, 1, (1, 8, 1, 1), 2)]
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
