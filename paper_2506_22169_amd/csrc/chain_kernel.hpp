@@ -1213,8 +1213,10 @@ void chain_kernel(const KParams p) {
                     phase_g2();
                 }
             };
-            top(0);
-            if (ncol0 < N) phase_g1(0);
+            if (n_iters > 0) { // (no n-tile, as where a mask hides a whole range: the other group meets no barrier either)
+                top(0);
+                if (ncol0 < N) phase_g1(0);
+            }
             for (int i = 1; i < n_iters; ++i) {
                 top(i);
                 finish_tile(i - 1);

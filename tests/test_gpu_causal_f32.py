@@ -148,3 +148,20 @@ def test_fp32_output_three_gemm_chain_and_causal():
         ref = oracle.chain3(x["A"], x["B"], x["D"], F.double().cpu().numpy(), softmax=scale is not None, scale=w.scale)
         assert np.max(np.abs(G32.double().cpu().numpy() - ref)) <= TOL * np.max(np.abs(ref))
     _check_causal(w, x, 136 - 200, out_dtype=torch.float32)
+
+
+@pytest.mark.parametrize("K,L,tiles", [(128, 64, (1, 4, 2, 2)), (128, 64, (2, 2, 4, 1)), (64, 128, (1, 4, 2, 2))])
+@pytest.mark.parametrize("ranges", [1, 3])
+def test_blocks_without_an_n_tile_in_the_phase_offset_loop(K, L, tiles, ranges):
+    """The loop of the softmax kernels whose four stages do not fit runs its wave groups a phase apart: blocks
+    whose rows see nothing, and ranges that a mask hides, leave both groups without a tile."""
+    w = mi.make_problem(2, 700, K, 460, L, "f16", True, "normal", seed=8400 + K)
+    x = mi.make_inputs(w)
+    A, B, D = device_inputs(w, x)
+    for off in (-300, -10**6, 0):
+        print(f"case phase offset K={K} tiles={tiles} ranges={ranges} off={off}", flush=True)
+        E = mcf.binding._call(2, w.scale, off, A, B, D, None, None, tiles, None, ranges)
+        got = to_host64(E, "f16")
+        ref = oracle.chain_causal(x["A"], x["B"], x["D"], scale=w.scale, causal_offset=off)
+        assert np.max(np.abs(got - ref)) <= TOL * max(np.max(np.abs(ref)), 1e-30)
+        assert not got[:, np.arange(700) + off < 0].any()
