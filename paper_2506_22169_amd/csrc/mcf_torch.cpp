@@ -75,6 +75,43 @@ void *workspace(size_t bytes, hipStream_t stream, c10::Device device) {
     return nullptr;
 }
 
+// Lays a call out and launches it; touches nothing of Python's.
+int run(mcf_call &call, void *stream, c10::Device device) {
+    mcf::Launch l;
+    int st = mcf::prepare(&call, &l);
+    if (st != MCF_OK) return st;
+    void *ws = nullptr;
+    if (l.workspace_bytes > 0) {
+        // where there is no workspace to be had, ranges that the library chose are not needed
+        try {
+            ws = workspace((size_t)l.workspace_bytes, (hipStream_t)stream, device);
+        } catch (const c10::OutOfMemoryError &) {
+            if (call.n_split != 0) throw;
+        }
+        if (!ws) {
+            if (call.n_split != 0) {
+                mcf::set_last_error("ranges of n in a graph that torch does not capture");
+                return MCF_EUNSUPPORTED;
+            }
+            call.n_split = 1;
+            st = mcf::prepare(&call, &l);
+            if (st != MCF_OK) return st;
+        }
+    }
+    st = mcf::launch(&l, ws, l.workspace_bytes, stream);
+    if (ws) c10::hip::HIPCachingAllocator::raw_delete(ws);
+    return st;
+}
+
+// The interpreter lock is let go while a call allocates and launches, both of which may wait for the device
+// (and work that is queued may wait for a Python thread); costs 0.1 us a call.
+struct NoGil {
+    PyThreadState *state = PyEval_SaveThread();
+    NoGil() = default;
+    NoGil(const NoGil &) = delete;
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+
 bool is_tensor(PyObject *o) { return THPVariable_Check(o); }
 
 // chain(kind, scale, causal_offset, A, B, D, F, out, tiles, stream, n_split) -> out
@@ -109,7 +146,10 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
     if (B.device() != A.device() || D.device() != A.device()) return fail(MCF_EINVAL, "A, B, D, E must live on one device");
     if (F && (F->scalar_type() != type || F->device() != A.device())) return fail(MCF_EINVAL, "F must match A in dtype and device");
     at::Tensor made;
-    if (arg[7] == Py_None) made = at::empty({b, M, cols}, A.options());
+    if (arg[7] == Py_None) {
+        const NoGil released;
+        made = at::empty({b, M, cols}, A.options());
+    }
     const at::Tensor &E = arg[7] == Py_None ? made : THPVariable_Unpack(arg[7]);
     if (arg[7] != Py_None) {
         if (E.dim() != 3 || E.size(0) != b || E.size(1) != M || E.size(2) != cols) return fail(MCF_EINVAL, "the output has the wrong shape");
@@ -134,29 +174,10 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
     call.A = A.data_ptr(); call.B = B.data_ptr(); call.D = D.data_ptr(); call.F = F ? F->data_ptr() : nullptr; call.E = E.data_ptr();
     call.tiles = tiles;
     if (arg[9] == Py_None) stream = (void *)c10::hip::getCurrentHIPStream().stream();
-    int st;
-    if (F && cols == 0) {
-        st = MCF_OK; // no output columns: nothing to do
-    } else {
-        mcf::Launch l;
-        st = mcf::prepare(&call, &l);
-        if (st == MCF_OK) {
-            // where there is no workspace to be had, ranges that the library chose are not needed
-            void *ws = nullptr;
-            try {
-                if (l.workspace_bytes > 0) ws = workspace((size_t)l.workspace_bytes, (hipStream_t)stream, A.device());
-            } catch (const c10::OutOfMemoryError &) {
-                if (n_split != 0) throw;
-            }
-            if (l.workspace_bytes > 0 && !ws) {
-                if (n_split != 0) return fail(MCF_EUNSUPPORTED, "ranges of n in a graph that torch does not capture");
-                call.n_split = 1;
-                st = mcf::prepare(&call, &l);
-                if (st != MCF_OK) return fail_status(st);
-            }
-            st = mcf::launch(&l, ws, l.workspace_bytes, stream);
-            if (ws) c10::hip::HIPCachingAllocator::raw_delete(ws);
-        }
+    int st = MCF_OK;
+    if (!F || cols > 0) { // (no output columns: nothing to do)
+        const NoGil released;
+        st = run(call, stream, A.device());
     }
     if (st != MCF_OK) return fail_status(st);
     if (arg[7] == Py_None) return THPVariable_Wrap(std::move(made));

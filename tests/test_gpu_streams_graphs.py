@@ -3,6 +3,9 @@ captured into a HIP graph and run on several streams at once.  Replays are check
 the eager result every time, with eager work and synchronisations between them."""
 import ctypes
 import re
+import sys
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -142,3 +145,38 @@ def test_calls_captured_by_others_are_not_split(case):
         torch.cuda.synchronize()
         assert torch.equal(E, ref)
     assert hip.hipGraphExecDestroy(exe) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+@pytest.mark.parametrize("case", SPLIT[:1] + [(1, 128, 64, 128, 64, False)], ids=str)
+def test_other_threads_run_during_calls(case):
+    """A call lets the interpreter lock go: with a switch interval that never ends, another thread only runs
+    when the calling one does so."""
+    b, M, K, N, L, softmax = case
+    w = mi.make_problem(b, M, K, N, L, "f16", softmax, "normal" if softmax else "uniform", seed=4500)
+    A, B, D = device_inputs(w, mi.make_inputs(w))
+    run = lambda: mcf.softmax_gemm_chain(A, B, D, w.scale) if softmax else mcf.gemm_chain(A, B, D)
+    run()
+    torch.cuda.synchronize()
+    ticks, stop = [0], threading.Event()
+
+    def tick():
+        while not stop.is_set():
+            ticks[0] += 1
+            time.sleep(0)     # gives the lock back
+
+    other, interval = threading.Thread(target=tick), sys.getswitchinterval()
+    print("case threads", case, flush=True)
+    other.start()
+    try:
+        time.sleep(0.05)
+        sys.setswitchinterval(60.0)
+        before = ticks[0]
+        for _ in range(300):
+            run()
+        during = ticks[0] - before
+    finally:
+        sys.setswitchinterval(interval)
+        stop.set()
+        other.join()
+    torch.cuda.synchronize()
+    assert during >= 100
