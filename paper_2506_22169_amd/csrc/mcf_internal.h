@@ -138,6 +138,7 @@ struct Launch {
 int prepare(const mcf_call *call, Launch *out); // MCF_OK or an error status; host only
 int launch(Launch *l, void *workspace, int64_t workspace_bytes, void *stream);
 
+bool longest_first(int64_t M, int64_t N, int64_t tm, int64_t causal_off); // order of the blocks of a masked call
 bool stream_capturing(void *stream); // whether work on the stream is being recorded into a graph
 
 void set_last_error(const char *msg);

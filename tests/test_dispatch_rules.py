@@ -1,6 +1,7 @@
 """What a call without an arrangement runs, on the host: which calls split n, into how much, and
 that a split call asks for the workspace its ranges need."""
 import ctypes
+import random
 
 import pytest
 
@@ -136,3 +137,22 @@ def test_blocks_a_compute_unit_holds(kernel, dtype):
     t, _ = mcf.call_tiles(p, bool(softmax), P=P, tiles=tiles)
     waves = 512 // ((t.vgpr_used + 7) // 8 * 8)
     assert min(4 * waves // t.waves, 160 * 1024 // t.lds_bytes) >= blocks and t.scratch_bytes == 0
+
+
+def test_longest_first_only_where_blocks_differ():
+    """The order of a masked call's blocks (an internal rule): longest first where the longest is at least an eighth longer
+    than the mean, counted here block by block."""
+    rule = binding.load_library()._ZN3mcf13longest_firstEllll
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_int64] * 4
+    rng = random.Random(3)
+    seen = [0, 0]
+    for _ in range(4000):
+        M, N, tm = rng.randint(1, rng.choice([40, 4000])), rng.randint(1, rng.choice([40, 9000])), rng.choice([32, 64, 128, 256])
+        off = rng.choice([0, N - M, N, N - 1, -M // 2, N // 2, rng.randint(-M, N)])
+        columns = [min(max(tm * (m + 1) + off, 0), N) for m in range(-(-M // tm))]
+        longest = min(max(M + off, 0), N)
+        want = sum(columns) > 0 and 8 * longest * len(columns) >= 9 * sum(columns)
+        assert rule(M, N, tm, off) == want, (M, N, tm, off)
+        seen[want] += 1
+    assert min(seen) > 500
+    assert not rule(704, 3200, 64, 3200) and not rule(538, 6145, 32, 6145 - 538) and rule(4096, 4096, 256, 0)
