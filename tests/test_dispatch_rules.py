@@ -156,3 +156,15 @@ def test_longest_first_only_where_blocks_differ():
         seen[want] += 1
     assert min(seen) > 500
     assert not rule(704, 3200, 64, 3200) and not rule(538, 6145, 32, 6145 - 538) and rule(4096, 4096, 256, 0)
+
+
+def test_ranges_of_what_a_mask_leaves():
+    """Under a mask the ranges are those of the columns that the last row sees."""
+    def ranges(b, M, K, N, off):
+        p = make_problem(b, M, K, N, K, "f16", b_stride=(N * K, 1, K))
+        return mcf.call_tiles(p, True, causal_offset=off)[1]
+    assert ranges(33, 7, 192, 6282, 0) == ranges(5, 11, 96, 4305, -6) == ranges(23, 1, 64, 4604, -1) == ranges(3, 686, 192, 2789, -343) == 1
+    assert ranges(33, 7, 192, 6282, 6282 - 7) == ranges(33, 7, 192, 6282, 10**6) > 1     # hides little, hides nothing
+    for off in range(0, 8192, 317):                                                       # as for the columns alone
+        assert ranges(32, 1, 128, 8192, off) == ranges(32, 1, 128, off + 1, off), off
+    assert ranges(32, 1, 128, 8192, -5) == 1 and ranges(32, 1, 128, 8192, -10**6) == 1

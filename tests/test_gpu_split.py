@@ -107,6 +107,19 @@ def test_split_ranges_on_streams_and_in_graphs():
         assert torch.equal(E, alone)
 
 
+@pytest.mark.parametrize("b,M,K,N,off", [(32, 1, 128, 8192, 5000), (3, 70, 64, 6000, 4000), (2, 33, 96, 4097, 4096 - 32), (9, 200, 64, 5000, 2049)])
+def test_ranges_end_with_what_a_mask_leaves(b, M, K, N, off):
+    """Ranges that the library chooses under a mask stop at the columns the last row sees."""
+    w = mi.make_problem(b, M, K, N, K, "f16", True, "normal", seed=9150 + off)
+    x = mi.make_inputs(w)
+    A, B, D = device_inputs(w, x)
+    assert mcf.call_tiles(binding.make_problem(b, M, K, N, K, "f16", b_stride=(N * K, 1, K)), True, causal_offset=off)[1] > 1
+    print("case masked ranges", b, M, K, N, off, flush=True)
+    got = to_host64(mcf.causal_softmax_gemm_chain(A, B, D, w.scale, off), "f16")
+    ref = oracle.chain_causal(x["A"], x["B"], x["D"], scale=w.scale, causal_offset=off)
+    assert np.max(np.abs(got - ref)) <= TOL * np.max(np.abs(ref))
+
+
 @pytest.mark.skipif(torch.cuda.device_count() < 2, reason="needs a second device")
 def test_workspace_lives_with_the_operands():
     """Operands and stream of a device that is not the current one: so does the workspace."""
