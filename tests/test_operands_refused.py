@@ -45,3 +45,15 @@ def test_other_views_get_past_the_check():
         with pytest.raises(mcf.McfError) as e:
             mcf.gemm_chain(A, B, D)
         assert e.value.status == MCF_EINVAL and "device" in str(e.value)
+
+
+@pytest.mark.parametrize("scale", ["0.125", 0.125, torch.tensor(0.125), 1])
+@pytest.mark.parametrize("offset", [2**63, -2**70, 10**30, 0])
+def test_scales_and_offsets_of_any_kind(scale, offset):
+    """What float() takes is a scale and any integer an offset: such calls get as far as the device check."""
+    z = lambda *s: torch.zeros(s, dtype=torch.float16)
+    for call in (lambda: mcf.softmax_gemm_chain(z(1, 64, 64), z(1, 64, 96), z(1, 96, 64), scale),
+                 lambda: mcf.causal_softmax_gemm_chain(z(1, 64, 64), z(1, 64, 96), z(1, 96, 64), scale, offset)):
+        with pytest.raises(mcf.McfError) as e:
+            call()
+        assert e.value.status == MCF_EINVAL and "device" in str(e.value)
