@@ -131,12 +131,6 @@ template <int N> static __device__ __forceinline__ void wait_vm() {
     static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// KSPLIT: KD is the chunk T_K of a k loop inside the block (K = k_chunks * KD); the A chunk of
-// every k step travels through the LDS ring with the B chunk instead of the whole A tile living
-// in registers.
-// PD > 0: chain of three GEMMs.  After the n loop the block multiplies its E tile (still in
-// registers) by F[L x PD], which waits in LDS from the prologue on, and stores that product
-// instead of E.  The rows of E must then be complete within a wave: NS = 1.
 // LDS bytes of an instantiation.
 template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD>
 constexpr int kernel_lds_bytes() {
@@ -145,6 +139,12 @@ constexpr int kernel_lds_bytes() {
     else return total_lds_bytes(KD, LD, MB, RG, NS, NJ, S, KSPLIT);
 }
 
+// KSPLIT: KD is the chunk T_K of a k loop inside the block (K = k_chunks * KD); the A chunk of
+// every k step travels through the LDS ring with the B chunk instead of the whole A tile living
+// in registers.
+// PD > 0: chain of three GEMMs.  After the n loop the block multiplies its E tile (still in
+// registers) by F[L x PD], which waits in LDS from the prologue on, and stores that product
+// instead of E.  The rows of E must then be complete within a wave: NS = 1.
 // Waves per SIMD the compiler is to leave room for (kernels that can have two blocks resident; everything
 // else: what the block size itself implies).
 template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD> constexpr int waves_per_simd() {
@@ -233,7 +233,7 @@ void chain_kernel(const KParams p) {
     // 8 XCDs (each with its own L2); give every XCD a contiguous range of logical blocks, a batch's
     // tiles in a row, so that they re-read that batch's B and D from one L2.
     // Under a causal mask the m-tiles of a batch differ in length, from one n-tile to all of them, and
-    // in that order the longest block of the last batch starts last.  Where the blocks do not all
+    // in that order the longest block of the last batch starts last.  Where they differ enough and do not all
     // start at once (p.lpt) they come longest first instead, over all batches: the last m-tile of
     // every batch, then the last but one, ...  Measured: 32 x 4096 x 4096, K = L = 128, 512 blocks: 193 -> 139 us
     // (dealing whole batches out to the XCDs: the same); 96 x 1024 x 1024, K = L = 64: 36.5 -> 26.3 us.
@@ -1097,13 +1097,15 @@ void chain_kernel(const KParams p) {
                 // those kernels keep the maximum.
                 using Stands = std::integral_constant<int, STANDS>;
                 using Exact = std::integral_constant<int, EXACT>;
+                // (a row of NaN scores has l = NaN; a row whose part of the wave's first tile a mask hides sees none of the others either:
+                // 170 x 256 x 640, K = L = 64, offset -1: 10.9 -> 9.8 us)
                 auto blind = [&]() __attribute__((always_inline)) -> bool {
                     bool any = false;
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) any = any || (m_run[mb] == -INFINITY && l_run[mb] == 0.f); // (a row of NaN scores: l = NaN)
+                    for (int mb = 0; mb < MB; ++mb) any = any || (m_run[mb] == -INFINITY && l_run[mb] == 0.f && sees(wrow0 + 32 * mb + c) > ncol0);
                     return __builtin_amdgcn_ballot_w64(any) != 0;
                 };
-                bool some_blind = blind();
+                bool some_blind = last > 1 && blind();
                 auto one = [&](auto curc, int t) __attribute__((always_inline)) {
                     top(t);
                     steady(curc, Stands{}, t);
