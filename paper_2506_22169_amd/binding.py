@@ -287,13 +287,15 @@ def gemm_chain(A, B, D, out=None, tiles=None, stream=None):
 
 def softmax_gemm_chain(A, B, D, scale, out=None, tiles=None, stream=None):
     """mcf_softmax_gemm_chain: E = softmax_rows(scale * A . B) . D."""
-    return _call(1, float(scale), 0, A, B, D, None, out, tiles, stream)
+    return _call(1, scale, 0, A, B, D, None, out, tiles, stream)
 
 
 def causal_softmax_gemm_chain(A, B, D, scale, causal_offset=0, out=None, tiles=None, stream=None):
     """mcf_causal_softmax_gemm_chain: the softmax chain with row i seeing the columns n <= i + causal_offset."""
-    offset = max(-2**63, min(2**63 - 1, int(causal_offset)))   # (beyond 64 bits: hides nothing, or everything)
-    return _call(2, float(scale), offset, A, B, D, None, out, tiles, stream)
+    offset = int(causal_offset)
+    if offset.bit_length() > 62:      # hides nothing, or everything
+        offset = 2**62 if offset > 0 else -2**62
+    return _call(2, scale, offset, A, B, D, None, out, tiles, stream)
 
 
 def pick_tiles(problem, softmax=False):

@@ -121,7 +121,13 @@ bool is_tensor(PyObject *o) { return THPVariable_Check(o); }
 PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
     if (n != 11) return PyErr_Format(PyExc_TypeError, "chain takes 11 arguments");
     const long kind = PyLong_AsLong(arg[0]);
-    const double scale = PyFloat_AsDouble(arg[1]);
+    double scale = 0.0;
+    if (PyFloat_CheckExact(arg[1])) {
+        scale = PyFloat_AS_DOUBLE(arg[1]);
+    } else if (PyObject *f = PyNumber_Float(arg[1])) { // what float() takes
+        scale = PyFloat_AsDouble(f);
+        Py_DECREF(f);
+    }
     const long long causal_offset = PyLong_AsLongLong(arg[2]);
     const mcf_tiles *tiles = (const mcf_tiles *)PyLong_AsVoidPtr(arg[8]);
     void *stream = arg[9] == Py_None ? nullptr : PyLong_AsVoidPtr(arg[9]);
@@ -145,13 +151,10 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
     if (B.scalar_type() != type || D.scalar_type() != type) return fail(MCF_EINVAL, "A, B, D must share one dtype; E has that dtype or float32");
     if (B.device() != A.device() || D.device() != A.device()) return fail(MCF_EINVAL, "A, B, D, E must live on one device");
     if (F && (F->scalar_type() != type || F->device() != A.device())) return fail(MCF_EINVAL, "F must match A in dtype and device");
+    const bool make = arg[7] == Py_None;
     at::Tensor made;
-    if (arg[7] == Py_None) {
-        const NoGil released;
-        made = at::empty({b, M, cols}, A.options());
-    }
-    const at::Tensor &E = arg[7] == Py_None ? made : THPVariable_Unpack(arg[7]);
-    if (arg[7] != Py_None) {
+    const at::Tensor &E = make ? made : THPVariable_Unpack(arg[7]);
+    if (!make) {
         if (E.dim() != 3 || E.size(0) != b || E.size(1) != M || E.size(2) != cols) return fail(MCF_EINVAL, "the output has the wrong shape");
         if (E.scalar_type() != type && E.scalar_type() != at::kFloat) return fail(MCF_EINVAL, "A, B, D must share one dtype; E has that dtype or float32");
         if (!E.is_cuda() || E.device() != A.device()) return fail(MCF_EINVAL, "A, B, D, E must live on one device");
@@ -160,27 +163,32 @@ PyObject *chain(PyObject *, PyObject *const *arg, Py_ssize_t n) {
     mcf_problem &p = call.problem;
     p.batch = b; p.M = M; p.K = K; p.N = N; p.L = L;
     p.in_dtype = type == at::kHalf ? MCF_F16 : MCF_BF16;
-    p.out_dtype = E.scalar_type() == at::kFloat ? MCF_F32 : p.in_dtype;
+    p.out_dtype = !make && E.scalar_type() == at::kFloat ? MCF_F32 : p.in_dtype;
     strides3(A, p.a_stride);
     strides3(B, p.b_stride);
     strides3(D, p.d_stride);
-    strides3(E, p.e_stride);
+    if (make) memset(p.e_stride, 0, sizeof(p.e_stride)); // packed
+    else strides3(E, p.e_stride);
     call.P = F ? cols : 0;
     if (F) strides3(*F, call.f_stride);
     else memset(call.f_stride, 0, sizeof(call.f_stride));
     call.softmax = kind != 0; call.causal = kind == 2;
     call.scale = (float)scale; call.causal_offset = causal_offset;
     call.n_split = (int32_t)n_split;
-    call.A = A.data_ptr(); call.B = B.data_ptr(); call.D = D.data_ptr(); call.F = F ? F->data_ptr() : nullptr; call.E = E.data_ptr();
+    call.A = A.data_ptr(); call.B = B.data_ptr(); call.D = D.data_ptr(); call.F = F ? F->data_ptr() : nullptr; call.E = make ? nullptr : E.data_ptr();
     call.tiles = tiles;
     if (arg[9] == Py_None) stream = (void *)c10::hip::getCurrentHIPStream().stream();
     int st = MCF_OK;
-    if (!F || cols > 0) { // (no output columns: nothing to do)
+    {
         const NoGil released;
-        st = run(call, stream, A.device());
+        if (make) {
+            made = at::empty({b, M, cols}, A.options());
+            call.E = made.data_ptr();
+        }
+        if (!F || cols > 0) st = run(call, stream, A.device()); // (no output columns: nothing to do)
     }
     if (st != MCF_OK) return fail_status(st);
-    if (arg[7] == Py_None) return THPVariable_Wrap(std::move(made));
+    if (make) return THPVariable_Wrap(std::move(made));
     Py_INCREF(arg[7]);
     return arg[7];
 }
