@@ -182,7 +182,8 @@ static void settle_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
 // of the sweep with a k loop that are split take 0.93 of their time or less, one with six items fewer 1.01).
 // No more ranges than give every compute unit one block.  Measured over 373 calls drawn from the ranges of the chains,
 // 318 of them with 256 blocks or fewer: those that it splits run 1.05 to 5 times as fast and none slower than unsplit; with
-// eight items instead of ten the first lose (4 x [320,32].. with 11 n-tiles 6.7 -> 8.1 us).  32 rows against 8192 keys of 128:
+// eight items instead of ten the first lose (4 x [320,32].. with 11 n-tiles 6.7 -> 8.1 us).  Of 90 more calls drawn near the line
+// (10 to 18 items saved) five take 1.00 to 1.17 of their time, K = L of 32 and 64, the others less.  32 rows against 8192 keys of 128:
 // 92 -> 33 us; 1 x [639,1024].[1024,664].[664,128]: 100 -> 19 us.  Chains of three are not split unasked: each range would
 // round its part of E before the third GEMM.
 static int64_t ranges_for(int64_t blocks, int64_t n_tiles, int64_t items_per_tile) {
