@@ -217,9 +217,8 @@ void chain_kernel(const KParams p) {
     // The n range of this block: all of it, or with a grid of two dimensions the blockIdx.y-th of the
     // ranges a call is split into where its (batch, m-tile, h-tile) blocks leave compute units idle.
     // Everything below sees a problem whose N is the length of the range and whose B, D and mask begin there.
-    const int N_all = p.N, split_cols = p.split_cols;
-    const int n_first = blockIdx.y * split_cols;
-    const int N = N_all - n_first < split_cols ? N_all - n_first : split_cols;
+    const int n_first = blockIdx.y * p.split_cols;
+    const int N = p.N - n_first < p.split_cols ? p.N - n_first : p.split_cols;
     const int sa_r = (int)p.sa_r, sb_r = (int)p.sb_r, sd_r = (int)p.sd_r;
     const int64_t se_r = p.se_r;
     const float c1 = p.c1;
@@ -242,16 +241,13 @@ void chain_kernel(const KParams p) {
     // of their own; the h tiles of one (batch, m-tile) are neighbours, so they share A and B in L2.
     const unsigned d_magic = p.d_magic, h_magic = p.h_magic;
     const int d_shift = p.d_shift, h_shift = p.h_shift, divisor = p.divisor, lpt = SOFTMAX ? p.lpt : 0;
-    // Scalar loads at the very top for all that the way to the first load needs, with one wait: what follows depends on the
-    // asm, and the asm on all of them.  Left alone, or tied to less, the compiler fetches them piecemeal, each piece with a wait of its own
-    // before the first load or the first n-tile (device time, 30 x 64 x 128, softmax, K = L = 80: 6.6 -> 6.4 us).
-    int n_bl = n_blocks;
-    asm volatile("" : "+s"(n_bl) : "s"(m_tiles), "s"(h_tiles), "s"(d_magic), "s"(h_magic), "s"(d_shift), "s"(h_shift), "s"(divisor), "s"(M),
-                 "s"(N_all), "s"(split_cols), "s"(a_mode), "s"(p.lpt), "s"(p.A), "s"(sa_r), "s"(sd_r));
+    // one scalar load at the very top for all of them (left alone, the compiler fetches them
+    // piecemeal, each piece with a wait of its own before the first load can be issued)
+    asm volatile("" ::"s"(n_blocks), "s"(m_tiles), "s"(h_tiles), "s"(d_magic), "s"(h_magic), "s"(d_shift), "s"(h_shift), "s"(divisor), "s"(M));
     int batch, pos;
     {
         const int hw = blockIdx.x;
-        const int x = hw & 7, q = n_bl >> 3, rem = n_bl & 7;
+        const int x = hw & 7, q = n_blocks >> 3, rem = n_blocks & 7;
         int i = x * q + (x < rem ? x : rem) + (hw >> 3);
         if (SOFTMAX) i = lpt ? hw : i;
         const int hi_q = (int)(__umulhi((unsigned)i, d_magic) >> d_shift);
@@ -1400,7 +1396,7 @@ void chain_kernel(const KParams p) {
     // for a softmax the base-2 logarithm of the row sum it was divided by stands behind its columns.
     const unsigned out_bits = (unsigned)(uintptr_t)p.E & 3;
     if (out_bits) {
-        float *Ef = (float *)((char *)p.E - out_bits) + (int64_t)blockIdx.y * M * se_r + batch * p.se_b + ht * LD; // (pointer arithmetic, so that the stores stay global ones)
+        float *Ef = (float *)((char *)p.E - out_bits) + blockIdx.y * p.se_s + batch * p.se_b + ht * LD; // (pointer arithmetic, so that the stores stay global ones)
         lds_u8 *es = smem + combine_bytes(LDX, MB, RG, NS) + (wr * owning_waves(LDX, MB, NS) + wn) * estage_wave_bytes(LDX, MB, NS);
         const bool again = (out_bits & 2) != 0;
 #pragma unroll

@@ -358,12 +358,12 @@ int prepare(const mcf_call *call, Launch *o) {
         c.L = (int32_t)(ch3 ? P : p->L);
         c.pitch = c.L + (softmax ? 4 : 0);
         c.rows = p->batch * p->M; c.M = p->M;
-        c.split_stride = p->M * c.pitch;
+        c.split_stride = c.rows * c.pitch;
         c.se_b = k.se_b; c.se_r = k.se_r;
         c.E = E; c.n_split = (int32_t)n_split; c.out_f32 = p->out_dtype == MCF_F32;
-        k.se_b = n_split * c.split_stride; k.se_r = c.pitch;
-        o->workspace_bytes = n_split * c.rows * c.pitch * 4;
-        if (c.rows * (c.L >> 2) / 256 >= (1ll << 31) - 1 || c.rows * c.pitch > (1ll << 40)) return MCF_EUNSUPPORTED;
+        k.se_b = p->M * c.pitch; k.se_r = c.pitch; k.se_s = c.split_stride;
+        o->workspace_bytes = n_split * c.split_stride * 4;
+        if (c.rows * (c.L >> 2) / 256 >= (1ll << 31) - 1 || c.split_stride > (1ll << 40)) return MCF_EUNSUPPORTED;
     }
     o->v = v;
     o->tiles.mb = v->mb; o->tiles.rg = v->rg; o->tiles.ns = v->ns; o->tiles.nj = v->nj; o->tiles.tl = (int32_t)tl;

@@ -24,8 +24,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
     const int64_t row = idx / quads; // over all batches
     if (row >= p.rows) return;
     const int col = (int)(idx - row * quads) * 4;
-    const int64_t b = row / p.M, i = row - b * p.M;
-    const float *src = p.part + b * p.n_split * p.split_stride + i * p.pitch;
+    const float *src = p.part + row * p.pitch;
     float m = -INFINITY;
     if (SOFTMAX) {
         const float *lse = src + p.L;
@@ -44,6 +43,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
         for (int e = 0; e < 4; ++e) acc[e] = SOFTMAX ? __builtin_fmaf(w, v[e], acc[e]) : acc[e] + v[e];
     }
     const float inv = SOFTMAX ? (wsum > 0.f ? 1.0f / wsum : 0.f) : 1.f;
+    const int64_t b = row / p.M, i = row - b * p.M;
     const int64_t at = b * p.se_b + i * p.se_r + col;
     if (p.out_f32) {
         f32x4 r;

@@ -31,26 +31,25 @@ struct KParams {
     // the same for h_tiles.  Saves the blocks an integer division each before their first load.
     uint32_t d_magic, h_magic;
     int32_t d_shift, h_shift;
-    // (the next eight are one scalar load of the kernels, issued with the first eight)
+    int32_t lpt;        // causal mask: 1 = longest blocks first over all batches, 0 = batch by batch
     int32_t M, N;
     int32_t split_cols; // columns of an n range (N where n is not split), a multiple of T_N
+    int32_t n_split;    // n ranges: the second dimension of the grid
     int32_t a_mode;     // 0: A as is, 1: -A (negative scale), 2: A := 0 (scale == 0)
-    int32_t lpt;        // causal mask: 1 = longest blocks first over all batches, 0 = batch by batch
+    int32_t k_chunks;   // kernels with a k loop: K / T_K (otherwise unused)
+    float c1;           // |scale| * log2(e) (softmax only)
     int32_t causal_off; // softmax only: row i sees the columns n <= i + causal_off (N - 1: no mask); no flag
                         // beside it: a branch on one splits the scalar loads of the arguments in two
-    float c1;           // |scale| * log2(e) (softmax only)
-    int32_t k_chunks;   // kernels with a k loop: K / T_K (otherwise unused)
     const void *A, *B, *D;
     void *E;            // bit 0 set: written as fp32 (the pointer itself is 16-byte aligned; strides then count fp32 elements);
-                        // bit 1 set: fp32 results of n ranges, for the combine kernel (se_r then is the pitch of its rows, and the
-                        // ranges of a batch follow one another: M se_r elements each, se_b for all of them)
+                        // bit 1 set: fp32 results of n ranges, for the combine kernel (se_r then is the pitch of its rows)
     int64_t sa_b, sa_r; // A: batch / row stride (col stride 1)
     int64_t sb_b, sb_r; // B: batch stride / stride of the non-contiguous index
     int64_t sd_b, sd_r; // D: batch / row stride
     int64_t se_b, se_r; // E: batch / row stride
+    int64_t se_s;       // stride between n ranges (bit 1 of E)
     const void *F;      // three-GEMM chain: F[b, L, P] (col stride 1); E is then the output [b, M, P]
     int64_t sf_b, sf_r; // F: batch / row stride
-    int32_t n_split;    // n ranges: the second dimension of the grid
 };
 
 // magic, shift with floor(n / d) = umulhi(n, magic) >> shift for every 0 <= n < 2^31 (d >= 1;
@@ -65,8 +64,8 @@ inline void division_magic(uint32_t d, uint32_t *magic, int32_t *shift) {
 
 // Arguments of the second pass over the results of n ranges (see mcf_combine.hip).
 struct CombineParams {
-    const float *part;    // [batch][n_split][M][pitch]: L columns, then (softmax) the base-2 logarithm of the row sum
-    int64_t split_stride; // M * pitch
+    const float *part;    // [n_split][rows][pitch]: L columns, then (softmax) the base-2 logarithm of the row sum
+    int64_t split_stride; // rows * pitch
     int64_t rows;         // batch * M
     int64_t M;
     int64_t se_b, se_r;   // E: batch / row stride
