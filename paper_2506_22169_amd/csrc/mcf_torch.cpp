@@ -62,7 +62,7 @@ bool one_element(const at::Tensor &t) {
 // stream that the call runs on: given back right after the launches, it is only handed out again to later work of that
 // stream.  While the stream is captured it has to stay with the graph instead.  torch's own capture allocates from the graph's
 // pool, which does that; where someone else captures, memory given back would be used by others between the replays:
-// nullptr then (and in any capture nothing here may end it, so that an allocation is allowed to reach the driver).
+// nullptr then (and in any capture nothing here may end it, so that an allocation may go past the allocator's cache).
 void *workspace(size_t bytes, hipStream_t stream, c10::Device device) {
     namespace alloc = c10::hip::HIPCachingAllocator;
     c10::DeviceGuard on(device);

@@ -107,6 +107,33 @@ def test_split_ranges_on_streams_and_in_graphs():
         assert torch.equal(E, alone)
 
 
+# kind, batch, M, K, N, L, dtype: calls that the library splits, and calls whose waves it arranges behind the model's pick
+CHOSEN = [("softmax", 8, 1, 128, 2500, 128, "bf16"), ("softmax", 2, 70, 64, 3001, 64, "f16"), ("plain", 1, 300, 512, 1000, 128, "f16"),
+          ("plain", 2, 129, 64, 2056, 256, "bf16"), ("plain", 15, 610, 64, 736, 128, "bf16"), ("plain", 6, 1635, 64, 800, 128, "bf16"),
+          ("softmax", 6, 1718, 64, 735, 128, "f16"), ("softmax", 12, 687, 80, 66, 80, "bf16")]
+
+
+@pytest.mark.parametrize("case", CHOSEN, ids=str)
+def test_calls_without_tiles_match_the_oracle(case):
+    """The path a program takes: neither tiles nor ranges given."""
+    kind, b, M, K, N, L, dtype = case
+    softmax = kind == "softmax"
+    w = mi.make_problem(b, M, K, N, L, dtype, softmax, "normal" if softmax else "uniform", seed=9170 + N)
+    x = mi.make_inputs(w)
+    A, B, D = device_inputs(w, x)
+    problem = binding.make_problem(b, M, K, N, L, dtype, b_stride=(N * K, 1, K) if softmax else None)
+    t, ranges = mcf.call_tiles(problem, softmax)
+    q = mcf.pick_tiles(problem, softmax)
+    assert ranges > 1 or (t.ns, t.nj) != (q.ns, q.nj)
+    print("case chosen", case, (t.mb, t.rg, t.ns, t.nj, t.tl), ranges, flush=True)
+    for out_dtype in (None, torch.float32):
+        out = None if out_dtype is None else torch.empty((b, M, L), dtype=out_dtype, device="cuda")
+        E = mcf.softmax_gemm_chain(A, B, D, w.scale, out=out) if softmax else mcf.gemm_chain(A, B, D, out=out)
+        got = E.double().cpu().numpy() if out_dtype else to_host64(E, dtype)
+        ref = oracle.chain(x["A"], x["B"], x["D"], softmax=softmax, scale=w.scale)
+        assert np.max(np.abs(got - ref)) <= TOL * np.max(np.abs(ref))
+
+
 @pytest.mark.parametrize("b,M,K,N,off", [(32, 1, 128, 8192, 5000), (3, 70, 64, 6000, 4000), (2, 33, 96, 4097, 4096 - 32), (9, 200, 64, 5000, 2049)])
 def test_ranges_end_with_what_a_mask_leaves(b, M, K, N, off):
     """Ranges that the library chooses under a mask stop at the columns the last row sees."""
