@@ -178,7 +178,7 @@ void chain_kernel(const KParams p) {
     constexpr int KS = KD / 16;          // MFMA k-steps of GEMM 1
     constexpr int HB = h_blocks(LD);     // 32-wide h blocks of GEMM 2 (the last may be partial)
     constexpr int KCH = KD / 8, LCH = LD / 8;                  // 16-byte chunks in a row of K / L elements
-    constexpr bool KPAD = pitch_elems(KD) != KD, LPAD = pitch_elems(LD) != LD; // rows padded to a power-of-two pitch
+    constexpr bool KPAD = pitch_elems(KD) != KD, LPAD = pitch_elems(LD) != LD; // rows padded to the LDS pitch
     constexpr int F_EXTRA = CH3 ? chain3_f_bytes(LD, PD) + 1024 : 0;
     constexpr int S = ring_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, F_EXTRA); // depth of the LDS ring
     // softmax chains: software pipeline over three consecutive n-tiles (see the loop)
@@ -545,13 +545,16 @@ void chain_kernel(const KParams p) {
     // chunk) is computed once, here; per n-tile the ring slot's base is added (one VALU add per
     // distinct swizzle pattern), and everything else -- slice j, row steps -- is a compile-time
     // constant in the offset field of the LDS instruction.
-    constexpr int NBV = BKC ? KS : NJ; // B operand: one pattern per k-step (K-contiguous B) or per slice
-    unsigned bvo[NBV], dvo[HB];        // D operand: one pattern per h block
+    // B operand: one pattern per k-step of a span of the swizzle (K-contiguous B) or per slice; D operand: one per h block of a span
+    constexpr int BSP = swz_span(RBB), KSP = BSP / 32;
+    constexpr int DSP = swz_span(RBD), HSP = DSP / 64;
+    constexpr int NBV = BKC ? (KS < KSP ? KS : KSP) : NJ, NDV = HB < HSP ? HB : HSP;
+    unsigned bvo[NBV], dvo[NDV];
 #pragma unroll
     for (int i = 0; i < NBV; ++i) bvo[i] = (unsigned)(b_off ^ (BKC ? 32 * i : 64 * i));
 #pragma unroll
-    for (int hb = 0; hb < HB; ++hb) dvo[hb] = (unsigned)(d_off ^ (64 * hb));
-    unsigned bb[NBV], dd[HB]; // the same plus the base of the ring slot in use
+    for (int i = 0; i < NDV; ++i) dvo[i] = (unsigned)(d_off ^ (64 * i));
+    unsigned bb[NBV], dd[NDV]; // the same plus the base of the ring slot in use
     auto set_b_slot = [&](unsigned slot_off) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NBV; ++i) {
@@ -561,14 +564,14 @@ void chain_kernel(const KParams p) {
     };
     auto set_d_slot = [&](unsigned slot_off) __attribute__((always_inline)) {
 #pragma unroll
-        for (int hb = 0; hb < HB; ++hb) {
-            dd[hb] = dvo[hb] + slot_off;
-            asm volatile("" : "+v"(dd[hb]));
+        for (int i = 0; i < NDV; ++i) {
+            dd[i] = dvo[i] + slot_off;
+            asm volatile("" : "+v"(dd[i]));
         }
     };
     auto load_b = [&](int j, int ks) __attribute__((always_inline)) -> v8 {
         if (BKC) {
-            return __builtin_bit_cast(v8, *(const lds_u32x4 *)(smem + bb[ks] + 32 * j * RBB));
+            return __builtin_bit_cast(v8, *(const lds_u32x4 *)(smem + bb[ks % NBV] + (ks / KSP) * BSP + 32 * j * RBB));
         } else {
             const lds_u8 *src = smem + bb[j] + (16 * ks) * RBB;
             i16x4 lo = lds_read_tr(src);
@@ -577,7 +580,7 @@ void chain_kernel(const KParams p) {
         }
     };
     auto load_d = [&](int j, int hb, int qp) __attribute__((always_inline)) -> v8 {
-        const lds_u8 *src = smem + dd[hb] + (32 * j + 16 * qp) * RBD;
+        const lds_u8 *src = smem + dd[hb % NDV] + (hb / HSP) * DSP + (32 * j + 16 * qp) * RBD;
         i16x4 lo = lds_read_tr(src);
         i16x4 hi = lds_read_tr(src + 8 * RBD);
         return __builtin_bit_cast(v8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -1438,7 +1441,7 @@ void chain_kernel(const KParams p) {
         constexpr int HPW = BPWX < HBX ? BPWX : HBX;     // h blocks per owned row set
         constexpr int MPW = BPWX < HBX ? 1 : BPWX / HBX; // row sets (of 32 rows) owned
         constexpr int RBS = estage_row_bytes(LDX, MB, NS); // staged row bytes: HPW * 64, rounded up to a power of two
-        constexpr bool EPAD = RBS != HPW * 64 || pitch_elems(LDX) != LDX; // some staged pieces are padding or lie beyond the last column
+        constexpr bool EPAD = RBS != HPW * 64 || 32 * HBX != LDX || HBX % HPW != 0; // some staged pieces are padding or lie beyond the last column
         const int mb0 = blk0x / HBX, h0 = blk0x % HBX;
         lds_u8 *es = smem + combine_bytes(LDX, MB, RG, NS) + (wr * owning_waves(LDX, MB, NS) + wn) * estage_wave_bytes(LDX, MB, NS);
 #pragma unroll

@@ -146,6 +146,9 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 //    slower; 32 x [2881,128].[128,976].[976,128], 736 blocks: 65 -> 56 us).
 //    A softmax chain with more blocks than compute units stays: two blocks of four waves share a unit as well
 //    (causal, 2376 blocks, K = L = 64: 1.10 of the time with eight).
+//    Plain chains in eight waves across m take two slices a wave for one, where that pads N by an eighth of it at most (one n-tile
+//    of 64 columns costs a block less than two of 32): 40 x [1000,96].[96,776].[776,96] 21.0 -> 17.9 us, the same with K = L = 64
+//    14.7 -> 13.4 and with 128 22.4 -> 21.5; 80 x [500,64].[64,520].[520,128] 15.4 -> 13.9 us.
 //  * Among equal estimates it takes the wider n-tile.  Softmax kernels of four waves whose rows are padded to the
 //    LDS pitch (K = 80, 96, 160, 192) spill scalar registers with two slices a wave, and run better with one: the calls
 //    of a sweep that were picked so take 0.80 to 1.02 of their time; causal 40 x 333 x 1357, K = L = 80: 23 -> 20.5 us.
@@ -168,6 +171,9 @@ static void settle_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
         w.ns = 2;
         for (w.nj = 2; w.nj >= 1; --w.nj)
             if (built(p, softmax, t->tn, &w)) { *t = w; return; }
+    } else if (!softmax && t->mb == 1 && t->rg == 8 && t->ns == 1 && t->nj == 1) {
+        w.nj = 2;
+        if (mcf_eval_tiles(p, softmax, &w) == MCF_OK && 8 * padding_of(p->N, w.tn) <= p->N) *t = w;
     } else if (softmax && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2 && pitch_elems(t->tk) != t->tk) {
         w.nj = 1;
         if (built(p, softmax, t->tn, &w)) *t = w;

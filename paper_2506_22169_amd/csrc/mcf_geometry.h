@@ -4,27 +4,44 @@
 
 namespace mcf {
 
-// All LDS tiles keep their natural row pitch (row bytes RB, a power of two >= 64) and are
+// All LDS tiles keep their natural row pitch (row bytes RB, a multiple of 64) and are
 // filled by direct global->LDS loads in units of 16-byte chunks; bank conflicts are avoided
-// by XOR-ing the chunk index within a row with a function of the row.
+// by XOR-ing the chunk index within a row with a function of the row.  The XOR stays within the
+// largest power of two that divides RB (256 bytes, the LDS line, at most), so that rows need not be powers of two.
 //
+// Bytes within which the swizzles permute the chunks of a row: a lane's address of a later chunk of its row is an XOR
+// within a span and a constant beyond it.
+constexpr int swz_span(int row_bytes) { return row_bytes % 256 == 0 ? 256 : row_bytes & -row_bytes; }
 // Tiles read with plain 128-bit reads (A tile; B tile when K is contiguous): 16 consecutive
 // rows are read at the same logical chunk, so consecutive rows must land on distinct 16-byte
-// bank groups of the 256-byte LDS line.
+// bank groups of the 256-byte LDS line.  Rows of 192 and 320 bytes step through four 64-byte groups of the line by
+// themselves, of 384 through two of 128.
 constexpr int swz_b128(int row_bytes, int row) {
-    return row_bytes == 64 ? ((row >> 2) & 3) : row_bytes == 128 ? ((row >> 1) & 7) : (row & 15);
+    switch (swz_span(row_bytes)) {
+    case 64: return (row >> 2) & 3;
+    case 128: return (row >> 1) & 7;
+    default: return row & 15;
+    }
 }
 // Tiles read with the transposing 64-bit read (D tile; B tile when N is contiguous): half a
 // wave reads 4 consecutive rows x 64 bytes, so the four rows must land on distinct 64-byte
 // groups.  Returned as a chunk mask (multiple of 4 chunks = 64 bytes).
 constexpr int swz_tr(int row_bytes, int row) {
-    return row_bytes == 64 ? 0 : row_bytes == 128 ? 4 * ((row >> 1) & 1) : 4 * (row & 3);
+    switch (swz_span(row_bytes)) {
+    case 64: return 0;
+    case 128: return 4 * ((row >> 1) & 1);
+    default: return 4 * (row & 3);
+    }
 }
 
-// K and L need not be powers of two (K a multiple of 16, L of 8): rows of the LDS tiles are
-// then laid out with the next power-of-two pitch (the swizzles want one); the chunks beyond
-// K or L in a row are loaded from valid memory and never reach a result that is stored.
-constexpr int pitch_elems(int x) { return x <= 32 ? 32 : x <= 64 ? 64 : x <= 128 ? 128 : x <= 256 ? 256 : 512; }
+// Pitch of the LDS rows in elements (K a multiple of 16, L of 8): rows of whole 64-byte groups lie as they are; others (80)
+// take the next power of two, and the chunks beyond K or L in a row are loaded from valid memory and never reach a
+// result that is stored.  (96, 160 and 192 took the next power of two before: a quarter to three eighths more LDS and loads, which
+// left most of their kernels a ring of two and 160 and 192 no softmax pipeline of 8 waves.  us a call, before and after:
+// softmax 20 x 2048 x 2048, K = L = 160: 120 and 63, 192: 150 and 134; causal 11 x 2852 x 3733, 160: 104 and 82; plain
+// 14 x 1088 x 3840, 160: 58 and 51, 40 x 1024 x 1024, 192: 59 and 53.)
+constexpr int pitch_elems(int x) { return x % 32 == 0 && x <= 256 ? x : x <= 32 ? 32 : x <= 64 ? 64 : x <= 128 ? 128 : x <= 256 ? 256 : 512; }
+constexpr int pow2_pitch_elems(int x) { return x <= 32 ? 32 : x <= 64 ? 64 : x <= 128 ? 128 : x <= 256 ? 256 : 512; }
 constexpr int h_blocks(int L) { return (L + 31) / 32; } // 32-wide column blocks of E (the last may be partial)
 
 constexpr int a_tile_bytes(int K, int mb, int rg) { return 32 * mb * rg * pitch_elems(K) * 2; }
@@ -56,7 +73,7 @@ constexpr int combine_bytes(int L, int mb, int rg, int ns) {
 constexpr int estage_row_bytes(int L, int mb, int ns) {
     const int hb = h_blocks(L), bpw = blocks_per_wave(L, mb, ns);
     const int hpw = bpw < hb ? bpw : hb;
-    return 2 * pitch_elems(32 * hpw);
+    return 2 * pow2_pitch_elems(32 * hpw);
 }
 constexpr int estage_wave_bytes(int L, int mb, int ns) {
     const int hb = h_blocks(L), bpw = blocks_per_wave(L, mb, ns);
