@@ -92,49 +92,46 @@ static bool overlaps(const void *x, int64_t xe, int64_t xs, const void *y, int64
 }
 
 // Variant of the three-GEMM chain for (dtype, K, L, P) and an arrangement, or nullptr.
-static const Variant *find_variant3(int dtype, int64_t K, int64_t L, int64_t P, int softmax, int b_kcontig, int mb, int rg,
+static const Built *find_variant3(int dtype, int64_t K, int64_t L, int64_t P, int softmax, int b_kcontig, int mb, int rg,
                                     int ns, int nj) {
-    int n = 0;
-    const Variant *v = variants3(&n);
     const Group *g = group3(dtype, K, L, P);
-    for (int i = g ? g->begin : 0; g && i < g->end; ++i)
-        if (v[i].softmax == softmax && v[i].b_kcontig == b_kcontig && v[i].mb == mb && v[i].rg == rg && v[i].ns == ns && v[i].nj == nj)
-            return &v[i];
+    if (!g) return nullptr;
+    for (const Built *v : g->of[softmax][b_kcontig])
+        if (v->mb == mb && v->rg == rg && v->ns == ns && v->nj == nj) return v;
     return nullptr;
 }
 
 // The arrangements built for the three-GEMM chain on (dtype, K, L, P, layout of B), each with
 // the model terms of its two-GEMM part (the third GEMM adds the same work to all of them) and
 // the LDS bytes of the three-GEMM kernel, in registry order.
-int candidates3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, std::vector<mcf_tiles> *out) {
-    int n = 0;
-    const Variant *v = variants3(&n);
-    out->clear();
+template <typename F> static int each_candidate3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, F &&f) {
     const Group *g = group3(p->in_dtype, p->K, p->L, P);
-    for (int i = g ? g->begin : 0; g && i < g->end; ++i) {
-        if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != b_kcontig || v[i].scratch_bytes != 0) continue;
-        mcf_tiles t;
-        memset(&t, 0, sizeof(t));
-        t.mb = v[i].mb; t.rg = v[i].rg; t.ns = v[i].ns; t.nj = v[i].nj;
-        const int st = mcf_eval_tiles(p, softmax, &t);
-        if (st != MCF_OK && st != MCF_EINVAL) continue;
-        t.lds_bytes = lds_bytes_for(&v[i]); // with the F tile
-        out->push_back(t);
-    }
-    return out->empty() ? MCF_EUNSUPPORTED : MCF_OK;
+    bool any = false;
+    if (g)
+        for (const Built *v : g->of[softmax != 0][b_kcontig]) {
+            if (v->scratch_bytes != 0 || !v->two) continue;
+            mcf_tiles t;
+            eval_model(p, v->two, &t);
+            t.lds_bytes = v->lds_bytes; // with the F tile
+            any = true;
+            f(t);
+        }
+    return any ? MCF_OK : MCF_EUNSUPPORTED;
+}
+int candidates3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, std::vector<mcf_tiles> *out) {
+    out->clear();
+    return each_candidate3(p, softmax, b_kcontig, P, [&](const mcf_tiles &t) { out->push_back(t); });
 }
 
 // Tile choice for the three-GEMM chain: the arrangement (among those built for it) whose
 // two-GEMM part the model ranks best (ties broken as for the two-GEMM chain); the third GEMM
 // adds the same work to each of them.
 static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mcf_tiles *out) {
-    std::vector<mcf_tiles> c;
-    const int st = candidates3(p, softmax, b_kcontig, P, &c);
-    if (st != MCF_OK) return st;
-    *out = c[0];
-    for (const mcf_tiles &t : c)
-        if (better(t, *out)) *out = t;
-    return MCF_OK;
+    bool first = true;
+    return each_candidate3(p, softmax, b_kcontig, P, [&](const mcf_tiles &t) {
+        if (first || better(t, *out)) *out = t;
+        first = false;
+    });
 }
 
 // The arrangement a call without one runs, from the model's pick.  The model does not see what an n-tile costs
@@ -157,12 +154,12 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 // third GEMM, which is the caller's or the model's choice and not one to be made behind it (parts that cancel, or that
 // leave fp16, are lost).
 static int64_t padding_of(int64_t n, int64_t tn) { return (n + tn - 1) / tn * tn - n; }
-static bool built(const mcf_problem *p, int softmax, int64_t tn_now, mcf_tiles *t) {
-    if (mcf_eval_tiles(p, softmax, t) != MCF_OK) return false;
+static bool built(const mcf_problem *p, int softmax, int b_kcontig, int64_t tn_now, mcf_tiles *t) {
+    if (eval_tiles(p, softmax, b_kcontig, t) != MCF_OK) return false;
     const int64_t pad = padding_of(p->N, t->tn);
     return 20 * pad < p->N || pad <= padding_of(p->N, tn_now); // Rule 3
 }
-static void settle_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
+static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *t) {
     if (t->tk < p->K) return; // a k loop: measured as it is
     mcf_tiles w;
     memset(&w, 0, sizeof(w));
@@ -170,13 +167,13 @@ static void settle_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
     if (t->mb == 1 && t->rg == 4 && t->ns == 1 && t->nj == 1 && (!softmax || t->blocks <= kComputeUnits)) {
         w.ns = 2;
         for (w.nj = 2; w.nj >= 1; --w.nj)
-            if (built(p, softmax, t->tn, &w)) { *t = w; return; }
+            if (built(p, softmax, b_kcontig, t->tn, &w)) { *t = w; return; }
     } else if (!softmax && t->mb == 1 && t->rg == 8 && t->ns == 1 && t->nj == 1) {
         w.nj = 2;
-        if (mcf_eval_tiles(p, softmax, &w) == MCF_OK && 8 * padding_of(p->N, w.tn) <= p->N) *t = w;
+        if (eval_tiles(p, softmax, b_kcontig, &w) == MCF_OK && 8 * padding_of(p->N, w.tn) <= p->N) *t = w;
     } else if (softmax && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2 && pitch_elems(t->tk) != t->tk) {
         w.nj = 1;
-        if (built(p, softmax, t->tn, &w)) *t = w;
+        if (built(p, softmax, b_kcontig, t->tn, &w)) *t = w;
     }
 }
 
@@ -278,14 +275,14 @@ int prepare(const mcf_call *call, Launch *o) {
     if (call->tiles) {
         chosen = *call->tiles;
     } else {
-        st = ch3 ? pick3(p, softmax, lay.b_kcontig, P, &chosen) : mcf_pick_tiles(p, softmax, &chosen);
+        st = ch3 ? pick3(p, softmax, lay.b_kcontig, P, &chosen) : pick_tiles(p, softmax, lay.b_kcontig, &chosen);
         if (st != MCF_OK) return st;
-        if (!ch3) settle_tiles(p, softmax, &chosen);
+        if (!ch3) settle_tiles(p, softmax, lay.b_kcontig, &chosen);
     }
     const int64_t tl = ch3 ? p->L : (chosen.tl > 0 ? chosen.tl : p->L);
     if (p->L % tl != 0) return MCF_EINVAL;
     const int nj_ = chosen.nj > 0 ? chosen.nj : 1;
-    const Variant *v = ch3 ? find_variant3(p->in_dtype, p->K, p->L, P, softmax, lay.b_kcontig, chosen.mb, chosen.rg, chosen.ns, nj_)
+    const Built *v = ch3 ? find_variant3(p->in_dtype, p->K, p->L, P, softmax, lay.b_kcontig, chosen.mb, chosen.rg, chosen.ns, nj_)
                            : find_variant(p->in_dtype, p->K, tl, softmax, lay.b_kcontig, chosen.mb, chosen.rg, chosen.ns, nj_);
     if (!v) {
         if (!ch3) return call->tiles ? MCF_EINVAL : MCF_EUNSUPPORTED;
@@ -293,7 +290,7 @@ int prepare(const mcf_call *call, Launch *o) {
         mcf_tiles any;
         return pick3(p, softmax, lay.b_kcontig, P, &any) == MCF_OK ? MCF_EINVAL : MCF_EUNSUPPORTED;
     }
-    if (lds_bytes_for(v) > kLdsBytesPerBlock)
+    if (v->lds_bytes > kLdsBytesPerBlock)
         return MCF_EINVAL; // more LDS than a compute unit has
 
     const int64_t tm = 32ll * v->mb * v->rg;
@@ -464,8 +461,8 @@ extern "C" int mcf_call_tiles(const mcf_call *call, mcf_tiles *tiles, int32_t *n
     st = mcf_eval_tiles(&p, o.softmax, tiles);
     if (st != MCF_OK && st != MCF_EINVAL) return st; // (MCF_EINVAL: over a budget of the model, which given tiles may be)
     if (call->P > 0) {
-        tiles->lds_bytes = mcf::lds_bytes_for(o.v);
-        tiles->stages = mcf::stages_for(o.v);
+        tiles->lds_bytes = o.v->lds_bytes;
+        tiles->stages = o.v->stages;
         tiles->vgpr_used = o.v->vgprs;
         tiles->scratch_bytes = o.v->scratch_bytes;
     }
@@ -517,13 +514,12 @@ extern "C" int mcf_list_variants3(const mcf_problem *p, int64_t P, int softmax, 
     mcf_problem pc = *p;
     memset(pc.e_stride, 0, sizeof(pc.e_stride));
     if (mcf::decode_layout(&pc, &lay) != MCF_OK) return 0;
-    int n = 0, total = 0;
-    const mcf::Variant *v = mcf::variants3(&n);
+    int total = 0;
     const mcf::Group *g = mcf::group3(p->in_dtype, p->K, p->L, P);
-    for (int i = g ? g->begin : 0; g && i < g->end; ++i) {
-        if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig) continue;
+    if (!g) return 0;
+    for (const mcf::Built *v : g->of[softmax != 0][lay.b_kcontig]) {
         if (out && total < cap) {
-            out[4 * total] = v[i].mb; out[4 * total + 1] = v[i].rg; out[4 * total + 2] = v[i].ns; out[4 * total + 3] = v[i].nj;
+            out[4 * total] = v->mb; out[4 * total + 1] = v->rg; out[4 * total + 2] = v->ns; out[4 * total + 3] = v->nj;
         }
         ++total;
     }

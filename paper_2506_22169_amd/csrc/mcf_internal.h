@@ -88,20 +88,23 @@ struct Variant {
                            // where the compiler only parks a few registers in scratch across the n loop, outside of it
 };
 
-// Registry of every built kernel variant (defined in mcf_registry.cpp): the two-GEMM chain ...
-const Variant *variants(int *count);
-// ... and the three-GEMM chain (P > 0).
-const Variant *variants3(int *count);
+// A variant in the registry (mcf_registry.cpp), with what the picker asks of every variant of a group on every call.
+struct Built : Variant {
+    int32_t stages, lds_bytes, vgpr_est;
+    bool fits;        // eq. (1) and no spills in loops: a candidate
+    const Built *two; // three-GEMM chain: the variant of its two-GEMM part, which the model ranks (or nullptr)
+};
 // The kernel group that serves a problem's (dtype, K, L): the group with T_K = K if it is built,
-// otherwise a group with a k loop whose chunk divides K; nullptr if there is neither.  Its variants are
-// [begin, end) of the table; K is that of the variants, ksplit whether they loop over k.
+// otherwise a group with a k loop whose chunk divides K; nullptr if there is neither.  K is that of the variants, ksplit
+// whether they loop over k.
 struct Group {
-    int32_t dtype, K, L, ksplit, P, begin, end;
+    int32_t dtype, K, L, ksplit, P;
+    std::vector<const Built *> of[2][2]; // those with (softmax, b_kcontig), in table order
 };
 const Group *resolve_group(int dtype, int64_t K, int64_t L);
 const Group *group3(int dtype, int64_t K, int64_t L, int64_t P); // the same in the table of the three-GEMM chain
 // Variant of that group with the given arrangement (K is the problem's K), or nullptr.
-const Variant *find_variant(int dtype, int64_t K, int64_t L, int softmax, int b_kcontig, int mb, int rg, int ns, int nj);
+const Built *find_variant(int dtype, int64_t K, int64_t L, int softmax, int b_kcontig, int mb, int rg, int ns, int nj);
 
 // Layout decoded from an mcf_problem.
 struct Layout {
@@ -110,9 +113,12 @@ struct Layout {
 };
 int decode_layout(const mcf_problem *p, Layout *out); // MCF_OK or an error status
 
-// Ring depth and LDS bytes of a variant; register estimate per lane.
-int stages_for(const Variant *v);
-int lds_bytes_for(const Variant *v);
+// Ring depth, LDS bytes and register estimate of a variant, and whether it can be a candidate.
+void describe(Built *v);
+// mcf_pick_tiles and mcf_eval_tiles on a problem whose layout has been decoded, and the model terms of one variant.
+int pick_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *out);
+int eval_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *t);
+void eval_model(const mcf_problem *p, const Built *v, mcf_tiles *t);
 bool better(const mcf_tiles &a, const mcf_tiles &b); // the picker's order: estimate, then the tie-breaks
 int vgpr_estimate(int K, int L, int mb, int rg, int ns, int nj, int softmax, int ksplit);
 
@@ -128,7 +134,7 @@ int candidates3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, std
 // One call, validated and laid out: the kernel with its arguments, and with n_split > 1 the second
 // pass and the workspace between the two.  v == nullptr: nothing to compute.
 struct Launch {
-    const Variant *v;
+    const Built *v;
     KParams k;
     CombineParams c;
     int64_t workspace_bytes;

@@ -38,15 +38,6 @@
 
 namespace mcf {
 
-int stages_for(const Variant *v) {
-    return ring_stages(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0,
-                       v->P > 0 ? chain3_f_bytes(v->L, v->P) + 1024 : 0);
-}
-int lds_bytes_for(const Variant *v) {
-    if (v->P > 0) return chain3_lds_bytes(v->K, v->L, v->P, v->mb, v->rg, v->ns, v->nj, stages_for(v));
-    return total_lds_bytes(v->K, v->L, v->mb, v->rg, v->ns, v->nj, stages_for(v), v->ksplit != 0);
-}
-
 // Registers per lane (eq. (1) restricted to the register-resident tiles, in 32-bit registers):
 // A tile (mb * K/16 operands of 4), E accumulators (mb * L/32 * 16), nj C accumulators and
 // their 16-bit copies per mb (16 + 8; a pipelined softmax chain: two C tiles and the 16-bit
@@ -73,37 +64,49 @@ int vgpr_estimate(int K, int L, int mb, int rg, int ns, int nj, int softmax, int
 // it, and a block of w waves puts ceil(w/4) waves on each SIMD.
 static int vgpr_cap(int waves) { return kVgprBudget / ((waves + 3) / 4); }
 
+void describe(Built *v) {
+    v->stages = ring_stages(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0,
+                            v->P > 0 ? chain3_f_bytes(v->L, v->P) + 1024 : 0);
+    v->lds_bytes = v->P > 0 ? chain3_lds_bytes(v->K, v->L, v->P, v->mb, v->rg, v->ns, v->nj, v->stages)
+                            : total_lds_bytes(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->stages, v->ksplit != 0);
+    v->vgpr_est = vgpr_estimate(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax, v->ksplit);
+    v->fits = v->lds_bytes <= kLdsBytesPerBlock && v->vgpr_est <= vgpr_cap(v->rg * v->ns) && v->scratch_bytes == 0;
+    v->two = nullptr;
+}
+
 static bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
+// ceil(dim / tile) of an extent (below 2^31: decode_layout)
+static int64_t tiles_of(int64_t dim, int tile) { return ((uint32_t)dim + (uint32_t)tile - 1) / (uint32_t)tile; }
 
 // Rule 3: a power-of-two dimension takes no padding; otherwise the padding ratio stays < 0.05.
-static bool padding_ok(int64_t dim, int64_t tile) {
-    const int64_t padded = (dim + tile - 1) / tile * tile;
+static bool padding_ok(int64_t dim, int tile) {
+    const int64_t padded = tiles_of(dim, tile) * tile;
     if (is_pow2(dim)) return padded == dim;
     return (double)(padded - dim) < 0.05 * (double)dim;
 }
 
-static void eval_model(const mcf_problem *p, int softmax, const Variant *v, mcf_tiles *t) {
+void eval_model(const mcf_problem *p, const Built *v, mcf_tiles *t) {
     const int mb = v->mb, rg = v->rg, ns = v->ns, nj = v->nj;
     memset(t, 0, sizeof(*t));
     t->mb = mb; t->rg = rg; t->ns = ns; t->nj = nj;
     t->tm = 32 * mb * rg; t->tn = 32 * ns * nj; t->tk = v->K; t->tl = v->L;
     t->waves = rg * ns;
-    t->stages = stages_for(v);
-    t->lds_bytes = lds_bytes_for(v);
-    t->vgpr_est = vgpr_estimate(v->K, v->L, mb, rg, ns, nj, softmax, v->ksplit);
+    t->stages = v->stages;
+    t->lds_bytes = v->lds_bytes;
+    t->vgpr_est = v->vgpr_est;
     t->vgpr_used = v->vgprs;
     t->scratch_bytes = v->scratch_bytes;
     const int64_t es = 2; // bytes per element, fp16 / bf16
-    const int64_t m = (p->M + t->tm - 1) / t->tm, n = (p->N + t->tn - 1) / t->tn;
+    const int64_t m = tiles_of(p->M, t->tm), n = tiles_of(p->N, t->tn);
     // T_L < L: h is a second block dimension (deep expression m h n k): every h tile repeats
     // L_A, L_B and C_C of its (batch, m-tile)
-    const int64_t h = p->L / t->tl;
+    const int64_t h = (uint32_t)p->L / (uint32_t)t->tl;
     t->blocks = p->batch * m * h;
     // N_block of eq. (5) counted in SIMDs taken, against the machine's SIMDs (below)
     const int64_t units = t->blocks * (t->waves < kWaveUnitsPerBlock ? t->waves : kWaveUnitsPerBlock);
     t->compulsory_bytes = es * p->batch * (p->M * p->K + p->K * p->N + p->N * p->L + p->M * p->L);
     // with a live k loop (T_K < K) inside n, L_A is no longer hoisted out of n: trips m * n * k
-    const int64_t k = (p->K + t->tk - 1) / t->tk;
+    const int64_t k = tiles_of(p->K, t->tk);
     const int64_t la = (int64_t)t->tm * t->tk * es * p->batch * m * h * (k > 1 ? n * k : 1);
     const int64_t lb = (int64_t)t->tk * t->tn * es * p->batch * m * h * n * k;
     const int64_t ld = (int64_t)t->tn * t->tl * es * p->batch * m * h * n;
@@ -116,10 +119,6 @@ static void eval_model(const mcf_problem *p, int softmax, const Variant *v, mcf_
     const int64_t rounds = (units + kWaveUnits - 1) / kWaveUnits;
     t->alpha = units > 0 ? (double)(rounds * kWaveUnits) / (double)units : 1.0;
     t->t_est_s = (t->t_mem_s + t->t_comp_s) * t->alpha;
-}
-
-static bool feasible(const mcf_tiles &t) {
-    return t.lds_bytes <= kLdsBytesPerBlock && t.vgpr_est <= vgpr_cap(t.waves) && t.scratch_bytes == 0;
 }
 
 // Strict ordering of candidates: smaller estimate first; among equal estimates (the model
@@ -150,18 +149,25 @@ using namespace mcf;
 extern "C" int mcf_list_variants(const mcf_problem *p, int softmax, int32_t *out, int cap) {
     Layout lay;
     if (check_problem(p, &lay) != MCF_OK) return 0;
-    int n = 0, total = 0;
+    int total = 0;
     const Group *g = resolve_group(p->in_dtype, p->K, p->L);
     if (!g) return 0;
-    const Variant *v = variants(&n);
-    for (int i = g->begin; i < g->end; ++i) {
-        if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig) continue;
+    for (const Built *v : g->of[softmax != 0][lay.b_kcontig]) {
         if (out && total < cap) {
-            out[4 * total] = v[i].mb; out[4 * total + 1] = v[i].rg; out[4 * total + 2] = v[i].ns; out[4 * total + 3] = v[i].nj;
+            out[4 * total] = v->mb; out[4 * total + 1] = v->rg; out[4 * total + 2] = v->ns; out[4 * total + 3] = v->nj;
         }
         ++total;
     }
     return total;
+}
+
+int mcf::eval_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *t) {
+    const int64_t tl = t->tl > 0 ? t->tl : p->L;
+    if (tl != p->L && p->L % tl != 0) return MCF_EUNSUPPORTED;
+    const Built *v = find_variant(p->in_dtype, p->K, tl, softmax != 0, b_kcontig, t->mb, t->rg, t->ns, t->nj > 0 ? t->nj : 1);
+    if (!v) return MCF_EUNSUPPORTED;
+    eval_model(p, v, t);
+    return v->fits ? MCF_OK : MCF_EINVAL;
 }
 
 extern "C" int mcf_eval_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
@@ -169,13 +175,7 @@ extern "C" int mcf_eval_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
     if (!t) return MCF_EINVAL;
     int st = check_problem(p, &lay);
     if (st != MCF_OK) return st;
-    const int mb = t->mb, rg = t->rg, ns = t->ns, nj = t->nj > 0 ? t->nj : 1;
-    const int64_t tl = t->tl > 0 ? t->tl : p->L;
-    if (p->L % tl != 0) return MCF_EUNSUPPORTED;
-    const Variant *v = find_variant(p->in_dtype, p->K, tl, softmax != 0, lay.b_kcontig, mb, rg, ns, nj);
-    if (!v) return MCF_EUNSUPPORTED;
-    eval_model(p, softmax != 0, v, t);
-    return feasible(*t) ? MCF_OK : MCF_EINVAL;
+    return eval_tiles(p, softmax, lay.b_kcontig, t);
 }
 
 // The candidates the picker and the search choose from: for T_L = L and then for every smaller
@@ -183,28 +183,24 @@ extern "C" int mcf_eval_tiles(const mcf_problem *p, int softmax, mcf_tiles *t) {
 // Rule 3; if Rule 3 leaves nothing (e.g. M smaller than every tile) it is dropped so that a
 // feasible variant is always found when one covers the shape.
 // f(candidate) for each of them.
-template <typename F> static int each_candidate(const mcf_problem *p, int softmax, F &&f) {
-    Layout lay;
-    int st = check_problem(p, &lay);
-    if (st != MCF_OK) return st;
-    int n = 0;
-    const Variant *v = variants(&n);
+// (Every call without tiles runs this, and it is most of what the library costs the caller of a short chain: variants that cannot
+// be candidates are left out before the model is evaluated.)
+template <typename F> static int each_candidate(const mcf_problem *p, int softmax, int b_kcontig, F &&f) {
     // T_L options, the full L first, then descending (L is at most 256 where there are kernels)
     const Group *g[256];
     int n_g = 0;
     if (!(g[n_g++] = resolve_group(p->in_dtype, p->K, p->L))) return MCF_EUNSUPPORTED;
-    for (int tl = (int)p->L / 2; tl >= 32 && n_g < 256; --tl)
-        if (p->L % tl == 0 && (g[n_g] = resolve_group(p->in_dtype, p->K, tl))) ++n_g;
+    for (int parts = 2; p->L / parts >= 32; ++parts)
+        if (p->L % parts == 0 && (g[n_g] = resolve_group(p->in_dtype, p->K, p->L / parts))) ++n_g;
     bool any = false;
     for (int pass = 0; pass < 2 && !any; ++pass)
         for (int q = 0; q < n_g; ++q)
-            for (int i = g[q]->begin; i < g[q]->end; ++i) {
-                if (v[i].softmax != (softmax != 0) || v[i].b_kcontig != lay.b_kcontig) continue;
-                mcf_tiles t;
-                eval_model(p, softmax != 0, &v[i], &t);
-                if (!feasible(t)) continue;
-                if (pass == 0 && p->M > 0 && p->N > 0 && !(padding_ok(p->M, t.tm) && padding_ok(p->N, t.tn))) continue;
+            for (const Built *v : g[q]->of[softmax != 0][b_kcontig]) {
+                if (!v->fits) continue;
+                if (pass == 0 && p->M > 0 && p->N > 0 && !(padding_ok(p->M, 32 * v->mb * v->rg) && padding_ok(p->N, 32 * v->ns * v->nj))) continue;
                 any = true;
+                mcf_tiles t;
+                eval_model(p, v, &t);
                 f(t);
             }
     return any ? MCF_OK : MCF_EUNSUPPORTED;
@@ -212,7 +208,9 @@ template <typename F> static int each_candidate(const mcf_problem *p, int softma
 
 int mcf::feasible_candidates(const mcf_problem *p, int softmax, std::vector<mcf_tiles> *out) {
     out->clear();
-    return each_candidate(p, softmax, [&](const mcf_tiles &t) { out->push_back(t); });
+    Layout lay;
+    const int st = check_problem(p, &lay);
+    return st != MCF_OK ? st : each_candidate(p, softmax, lay.b_kcontig, [&](const mcf_tiles &t) { out->push_back(t); });
 }
 
 extern "C" int mcf_list_candidates(const mcf_problem *p, int softmax, mcf_tiles *out, int cap) {
@@ -222,11 +220,17 @@ extern "C" int mcf_list_candidates(const mcf_problem *p, int softmax, mcf_tiles 
     return (int)cands.size();
 }
 
-extern "C" int mcf_pick_tiles(const mcf_problem *p, int softmax, mcf_tiles *out) {
-    if (!out) return MCF_EINVAL;
+int mcf::pick_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *out) {
     bool first = true;
-    return each_candidate(p, softmax, [&](const mcf_tiles &t) {
+    return each_candidate(p, softmax, b_kcontig, [&](const mcf_tiles &t) {
         if (first || better(t, *out)) *out = t;
         first = false;
     });
+}
+
+extern "C" int mcf_pick_tiles(const mcf_problem *p, int softmax, mcf_tiles *out) {
+    if (!out) return MCF_EINVAL;
+    Layout lay;
+    const int st = check_problem(p, &lay);
+    return st != MCF_OK ? st : pick_tiles(p, softmax, lay.b_kcontig, out);
 }
