@@ -131,14 +131,6 @@ template <int N> static __device__ __forceinline__ void wait_vm() {
     static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// LDS bytes of an instantiation.
-template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD>
-constexpr int kernel_lds_bytes() {
-    constexpr int S = ring_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD > 0 ? chain3_f_bytes(LD, PD) + 1024 : 0);
-    if constexpr (PD > 0) return chain3_lds_bytes(KD, LD, PD, MB, RG, NS, NJ, S);
-    else return total_lds_bytes(KD, LD, MB, RG, NS, NJ, S, KSPLIT);
-}
-
 // KSPLIT: KD is the chunk T_K of a k loop inside the block (K = k_chunks * KD); the A chunk of
 // every k step travels through the LDS ring with the B chunk instead of the whole A tile living
 // in registers.
@@ -148,8 +140,7 @@ constexpr int kernel_lds_bytes() {
 // Waves per SIMD the compiler is to leave room for (kernels that can have two blocks resident; everything
 // else: what the block size itself implies).
 template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSPLIT, int PD> constexpr int waves_per_simd() {
-    constexpr int extra = PD > 0 ? chain3_f_bytes(LD, PD) + 1024 : 0;
-    if (pipe_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, extra) > 0) return pipe_waves_per_simd(KD, LD, MB, RG, NS, NJ, extra);
+    if (pipelined(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD)) return pipe_waves_per_simd(KD, LD, MB, RG, NS, NJ, SOFTMAX, PD);
     constexpr int per_block = RG * NS >= 4 ? RG * NS / 4 : 1;
     // a k loop: half the register file at most where the tiles a lane must hold leave it 150 registers for the
     // operands and load offsets (with all of it the compiler keeps accumulators in the accumulation half
@@ -159,7 +150,7 @@ template <int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool KSP
     // it 24 of 128 registers.  Left alone the compiler takes 127 to 133 for the kernels at that edge, and three registers
     // too many are a block: plain K = L = 64, (1,4,2,2): 160 x 512 x 512 18.7 -> 16.4 us, 300 x 512 x 1024 46.4 -> 40.6
     // us; three GEMMs of that size 20.3 -> 17.2 us.
-    if (!KSPLIT && per_block == 2 && 2 * kernel_lds_bytes<KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD>() <= 160 * 1024 &&
+    if (!KSPLIT && per_block == 2 && 2 * block_lds_bytes(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD) <= 160 * 1024 &&
         MB * (KD / 16) * 4 + MB * h_blocks(LD) * 16 + NJ * MB * (16 + 8) + 24 <= 512 / (2 * per_block))
         return 2 * per_block;
     return per_block;
@@ -179,12 +170,10 @@ void chain_kernel(const KParams p) {
     constexpr int HB = h_blocks(LD);     // 32-wide h blocks of GEMM 2 (the last may be partial)
     constexpr int KCH = KD / 8, LCH = LD / 8;                  // 16-byte chunks in a row of K / L elements
     constexpr bool KPAD = pitch_elems(KD) != KD, LPAD = pitch_elems(LD) != LD; // rows padded to the LDS pitch
-    constexpr int F_EXTRA = CH3 ? chain3_f_bytes(LD, PD) + 1024 : 0;
-    constexpr int S = ring_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, F_EXTRA); // depth of the LDS ring
+    constexpr int S = ring_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD); // depth of the LDS ring
     // softmax chains: software pipeline over three consecutive n-tiles (see the loop)
-    constexpr bool PIPE = pipe_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, F_EXTRA) > 0;
-    constexpr int PRE = PIPE ? S - 2 : S - 1; // n-tiles requested before the loop
-    constexpr int RBA = 2 * pitch_elems(KD);                // row bytes of the A tile (rows m)
+    constexpr bool PIPE = pipelined(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD);
+        constexpr int RBA = 2 * pitch_elems(KD);                // row bytes of the A tile (rows m)
     constexpr int RBB = BKC ? 2 * pitch_elems(KD) : 2 * TN; // row bytes of the B tile (rows n / rows k)
     constexpr int RBD = 2 * pitch_elems(LD);                // row bytes of the D tile (rows n)
     constexpr int B_BYTES = b_tile_bytes(KD, TN);
@@ -192,9 +181,14 @@ void chain_kernel(const KParams p) {
     // Without a k loop a ring slot holds [B tile | D tile] and the A tile borrows the last slot
     // once; with one, a slot holds either [A chunk | B chunk] or [D tile].
     constexpr int STAGE = KSPLIT ? ksplit_slot_bytes(KD, LD, MB, RG, TN) : stage_bytes(KD, LD, TN);
-    constexpr int A_LDS = KSPLIT ? 0 : (S - 1) * STAGE; // offset of the A tile (chunk: within its slot)
-    constexpr int B_LDS = KSPLIT ? A_BYTES : 0;         // offset of the B tile within its slot
-    constexpr int D_LDS = KSPLIT ? 0 : B_BYTES;         // offset of the D tile within its slot
+    // A pipelined kernel has the first D tile, a ring of B tiles and behind it the other D tiles, and borrows what lies behind the
+    // first B tiles.
+    constexpr PipeRing R = PIPE ? pipe_ring(KD, LD, MB, RG, NS, NJ, SOFTMAX, PD) : PipeRing{};
+    constexpr int D_BYTES = d_tile_bytes(LD, TN);
+    constexpr int A_LDS = KSPLIT ? 0 : PIPE ? R.a_offset : (S - 1) * STAGE; // offset of the A tile (chunk: within its slot)
+    constexpr int B_LDS = KSPLIT ? A_BYTES : PIPE ? R.b_offset : 0;         // offset of the B tile within its slot
+    constexpr int D_LDS = KSPLIT || PIPE ? 0 : B_BYTES;                     // offset of the D tile within its slot
+    constexpr int PRE = PIPE ? 2 + R.ahead : S - 1; // n-tiles requested before the loop
     // 1 KiB wave-loads per tile and per wave
     constexpr int CA = A_BYTES / 1024;
     constexpr int CB = B_BYTES / 1024, CD = d_tile_bytes(LD, TN) / 1024;
@@ -203,10 +197,10 @@ void chain_kernel(const KParams p) {
     constexpr int P = (CT + W - 1) / W;
     // three-GEMM chain: the F tile [LD rows x PD] behind everything else
     constexpr int RBF = 2 * pitch_elems(CH3 ? PD : 32);
-    constexpr int F_LDS = CH3 ? chain3_f_offset(KD, LD, PD, MB, RG, NS, NJ, S) : 0;
+    constexpr int F_LDS = CH3 ? f_lds_offset(KD, LD, MB, RG, NS, NJ, SOFTMAX, PD) : 0;
     constexpr int CF = CH3 ? chain3_f_bytes(LD, PD) / 1024 : 0;
     constexpr int PFW = (CF + W - 1) / W; // wave-loads of F per wave
-    static_assert((S - 1) * P <= 63, "too many loads in flight for the 6-bit vmcnt counter");
+    static_assert((PIPE ? PRE : S - 1) * P <= 63, "too many loads in flight for the 6-bit vmcnt counter");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_generic[];
     lds_u8 *smem = (lds_u8 *)smem_generic;
@@ -337,6 +331,42 @@ void chain_kernel(const KParams p) {
             }
         }
     };
+
+    // Pipelined kernels: requests the next B tile (tb, if WB) and the next D tile (td, if WD), each where there is such a tile, into
+    // the slots at these offsets of their rings.  Their addresses are carried along: what stands between a barrier and the
+    // first MFMA behind it, all waves of a block wait for.
+    constexpr bool EVEN = CB % W == 0 && CD % W == 0; // no wave-load of a wave is of B for some waves and of D for others
+    const char *b_src = (const char *)Bg, *d_src = (const char *)Dg;
+    const unsigned b_step = 2u * TN * (BKC ? (unsigned)sb_r : 1u), d_step = 2u * TN * (unsigned)sd_r;
+    const unsigned dst_wave = uniform(lds0 + wave * 1024);
+    const int n_whole = n_full < n_iters ? n_full : n_iters; // (a mask may end the loop before the last column)
+    auto request = [&](auto wbc, auto wdc, int tb, unsigned b_slot, int td, unsigned d_slot) __attribute__((always_inline)) {
+        constexpr bool WB = decltype(wbc)::value, WD = decltype(wdc)::value;
+        const char *const bs = b_src, *const ds = d_src; // (selected below as values: selected as variables, some kernels kept them in scratch)
+        const unsigned bdst = dst_wave + B_LDS + b_slot, ddst = dst_wave - B_BYTES + d_slot;
+        const bool whole = (WB ? tb : td) < n_whole; // (D runs behind B)
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            const int j = wave + u * W; // wave-uniform
+            const bool of_b = EVEN ? u * W < CB : j < CB;
+            if ((!WB && of_b) || (!WD && !of_b) || ((u + 1) * W > CT && j >= CT)) continue;
+            if (whole) dma16((of_b ? bdst : ddst) + u * W * 1024, voff[u], of_b ? bs : ds);
+        }
+        if (!whole) {
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const int j = wave + u * W;
+                const bool of_b = EVEN ? u * W < CB : j < CB;
+                if ((!WB && of_b) || (!WD && !of_b) || ((u + 1) * W > CT && j >= CT)) continue;
+                const int t = of_b ? tb : td;
+                if (t < n_iters) dma16((of_b ? bdst : ddst) + u * W * 1024, t < n_full ? voff[u] : bd_offset(u, t * TN, true), of_b ? bs : ds);
+            }
+        }
+        if (WB) b_src = bs + b_step;
+        if (WD) d_src = ds + d_step;
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
 
     // ---- kernels with a k loop: the items that travel through the ring ----------------------
     // Item r of n-tile t: r < KC is the A chunk + B chunk of k step r ([A | B] in the slot),
@@ -473,7 +503,12 @@ void chain_kernel(const KParams p) {
     if constexpr (KSPLIT) {
         for (int q = 0; q < n_pre; ++q) issue_item(q / (KC + 1), q % (KC + 1), q);
     } else {
-        for (int t = 0; t < n_pre; ++t) issue_tile(t, t);
+        for (int t = 0; t < n_pre; ++t) {
+            if constexpr (PIPE) request(Yes{}, No{}, t, t * B_BYTES, 0, 0);
+            else issue_tile(t, t);
+        }
+        if constexpr (PIPE)
+            for (int t = 0; t < R.d_first && t < n_pre; ++t) request(No{}, Yes{}, 0, 0, t, t * D_BYTES);
     }
 
     // ---- L_A: A tile in LDS -> registers, as the second MFMA operand A^T[k][m] (with a k loop the
@@ -498,8 +533,9 @@ void chain_kernel(const KParams p) {
         }
     };
     if constexpr (!KSPLIT) {
-        // the A loads are older than the n_pre tile groups
-        if (n_pre == PRE) wait_vm<PRE * P>();
+        // the A loads are older than the n_pre tile groups (a pipelined kernel: the waves' shares of the first tiles)
+        constexpr int YOUNGER = PIPE ? (EVEN ? (PRE * CB + R.d_first * CD) / W : 0) : PRE * P;
+        if (n_pre == PRE) wait_vm<YOUNGER>();
         else wait_vm<0>();
         __syncthreads();
         load_a(A_LDS);
@@ -826,9 +862,10 @@ void chain_kernel(const KParams p) {
         //   steps [TA, TT)       p = exp2(c1 * s - m) in place, row-sum partials
         //   steps [T2, TT)       conversion of finished p to 16 bit (the operand GEMM 2 of tile
         //                        i-1 has read by then is overwritten)
-        // Tile t lives in ring slot t % S; tile i+S-2 is requested at the top of iteration i,
-        // into the slot tile i-2 left in iteration i-1.  One block barrier per iteration.
-        static_assert(S >= 4, "three live tiles and one landing");
+        // B and D have rings of their own (see PipeRing for why): at the top of iteration i B of tile i+2 is requested,
+        // into the slot that tile i or i-1 left in iteration i-1, and D of tile i, into that of tile i-2; both are
+        // needed in iteration i+1.  (With one tile ahead B of tile i+3 and D of tile i+1, needed in iteration i+2.)  One block
+        // barrier per iteration.
         constexpr int NE = 16 * NJ;       // elements of S per lane and row set in one n-tile
         constexpr int TT = T2 + T1;       // MFMA steps of an iteration
         constexpr int TA = TT >= 12 ? TT / 6 : (TT >= 6 ? 2 : 1);
@@ -847,7 +884,7 @@ void chain_kernel(const KParams p) {
         // before it has to move.  fp16: from 1 to the largest fp16 (a sum of p D is far from the end of fp32 then, D being
         // fp16 as well).  bf16: from 2^-8 to 2^8, because D reaches to the end of fp32 itself: a larger p would overflow sums whose
         // quotient by the row sum does not, a smaller one lose products of the smallest D.
-        constexpr bool STAND = MCF_LAZY_MAX > 0 && reference_stands(KD, LD, MB, RG, NS, NJ, SOFTMAX, F_EXTRA);
+        constexpr bool STAND = MCF_LAZY_MAX > 0 && reference_stands(KD, LD, MB, RG, NS, NJ, SOFTMAX, PD);
         constexpr int P_SHIFT = std::is_same<T, _Float16>::value ? 0 : 8;
         constexpr float P_MOST = std::is_same<T, _Float16>::value ? 65504.f : 256.f;
         f32x16 cc[2][NJ][MB]; // C^T of the tile in the softmax and of the tile GEMM 1 is producing
@@ -934,7 +971,23 @@ void chain_kernel(const KParams p) {
                 }
             }
         };
-        auto ring_off = [&](int t) __attribute__((always_inline)) { return (unsigned)((t % S) * STAGE); }; // t >= 0
+        // offsets of the slots of B of tiles i, i+1, ... and of D of tiles i-1, i, ... in iteration i
+        constexpr int SB = R.b_slots, SD = R.d_slots;
+        unsigned b_at[SB], d_at[SD];
+        auto d_slot = [](int s) constexpr { return (unsigned)(s * D_BYTES + (s >= R.d_first ? R.d_rest : 0)); };
+#pragma unroll
+        for (int s = 0; s < SB; ++s) b_at[s] = s * B_BYTES;
+#pragma unroll
+        for (int s = 0; s < SD; ++s) d_at[s] = d_slot((s + SD - 1) % SD);
+        auto turn = [&]() __attribute__((always_inline)) { // to the next iteration
+            const unsigned b0 = b_at[0], d0 = d_at[0];
+#pragma unroll
+            for (int s = 0; s + 1 < SB; ++s) b_at[s] = b_at[s + 1];
+            b_at[SB - 1] = b0;
+#pragma unroll
+            for (int s = 0; s + 1 < SD; ++s) d_at[s] = d_at[s + 1];
+            d_at[SD - 1] = d0;
+        };
         auto g2_step = [&](auto tc, auto mbc, const v8 &x) __attribute__((always_inline)) {
             constexpr int t = decltype(tc)::value, j = t / (2 * HB), hb = (t / 2) % HB, qp = t % 2, mb = decltype(mbc)::value;
             accE[mb][hb] = M_::run(x, pop[j][mb][qp], accE[mb][hb]);
@@ -958,9 +1011,9 @@ void chain_kernel(const KParams p) {
             constexpr int t = decltype(tc)::value;
             return load_b(t / KS, t % KS);
         };
-        // GEMM 2 of tile t alone / GEMM 1 of tile t alone (the ends of the pipeline)
-        auto g2_only = [&](int t) __attribute__((always_inline)) {
-            set_d_slot(ring_off(t));
+        // GEMM 2 / GEMM 1 of the tile in a slot alone (the ends of the pipeline)
+        auto g2_only = [&](unsigned slot) __attribute__((always_inline)) {
+            set_d_slot(slot);
             v8 op[T2];
             static_for<0, (PF < T2 ? PF : T2)>([&](auto tc) { op[decltype(tc)::value] = fetch_d(tc); });
             static_for<0, T2>([&](auto tc) {
@@ -970,8 +1023,8 @@ void chain_kernel(const KParams p) {
                 __builtin_amdgcn_sched_barrier(0x406);
             });
         };
-        auto g1_only = [&](auto nxtc, int t) __attribute__((always_inline)) {
-            set_b_slot(ring_off(t));
+        auto g1_only = [&](auto nxtc, unsigned b_slot) __attribute__((always_inline)) {
+            set_b_slot(b_slot);
             v8 op[T1];
             static_for<0, (PF < T1 ? PF : T1)>([&](auto tc) { op[decltype(tc)::value] = fetch_b(tc); });
             static_for<0, T1>([&](auto tc) {
@@ -1000,8 +1053,8 @@ void chain_kernel(const KParams p) {
         auto steady = [&](auto curc, auto modec, int i) __attribute__((always_inline)) {
             constexpr int CUR = decltype(curc)::value;
             const int n0 = i * TN + ncol0;
-            set_d_slot(ring_off(i - 1));
-            set_b_slot(ring_off(i + 1));
+            set_d_slot(d_at[0]);
+            set_b_slot(b_at[1]);
             v8 op[TT];
             auto fetch = [&](auto tc) __attribute__((always_inline)) {
                 constexpr int t = decltype(tc)::value;
@@ -1056,32 +1109,39 @@ void chain_kernel(const KParams p) {
                             for (int e = 0; e < 8; ++e) pop[j][mb][qp][e] = (T)0.f;
             }
         };
-        int slot_l = PRE; // ring slot the next requested tile goes to
-        // top of iteration i: tile i+1 (if any) has landed, tile i+S-2 is requested
-        auto top = [&](int i) __attribute__((always_inline)) {
-            // at most the S-4 requests younger than tile i+1 may still be in flight
-            if (i + S - 3 <= n_iters - 1) wait_vm<(S - 4) * P>();
-            else wait_vm<0>();
-            __syncthreads(); // tile i+1 is complete for every wave; the slot of tile i-2 is free
-            if (i + S - 2 < n_iters) {
-                issue_tile(i + S - 2, slot_l);
-                slot_l = slot_l + 1 == S ? 0 : slot_l + 1;
+        // top of iteration i: B of tile i+1 (if any) and D of tile i-1 have landed; the next of both are requested
+        auto landed = [&](int i) __attribute__((always_inline)) {
+            // what has been requested ahead may still be in flight (before iteration 0: the prologue's last B and its D tiles; before
+            // iteration 1 no D has been requested but those)
+            if (R.ahead > 0 && i + 1 + R.ahead < n_iters) {
+                if (i > 1) wait_vm<R.ahead * P>();
+                else if (i == 1) wait_vm<(EVEN ? CB / W : 0)>();
+                else wait_vm<(EVEN ? (R.ahead * CB + R.d_first * CD) / W : 0)>();
+            } else {
+                wait_vm<0>();
             }
+            __syncthreads(); // what has landed is complete for every wave; the slots requested next are free
+        };
+        auto top = [&](int i) __attribute__((always_inline)) {
+            landed(i);
+            if (i + R.ahead >= R.d_first) request(Yes{}, Yes{}, i + 2 + R.ahead, b_at[(2 + R.ahead) % SB], i + R.ahead, d_at[1 + R.ahead]);
+            else request(Yes{}, No{}, i + 2 + R.ahead, b_at[(2 + R.ahead) % SB], 0, 0); // (its D came with the prologue)
         };
         if (n_iters > 0) {
             const int last = n_iters - 1;
-            // tile 0 (requested in the prologue, like tiles 1 .. PRE-1): GEMM 1 alone
-            if (n_pre == PRE) wait_vm<(PRE - 1) * P>();
+            // tile 0 (whose B was requested in the prologue, like that of tile 1): GEMM 1 alone
+            if (n_pre == PRE) wait_vm<(EVEN ? ((PRE - 1) * CB + R.d_first * CD) / W : 0)>();
             else wait_vm<0>();
             __syncthreads();
-            g1_only(std::integral_constant<int, 0>{}, 0);
+            g1_only(std::integral_constant<int, 0>{}, b_at[0]);
             // iteration 0: no tile before it
             top(0);
-            if (last >= 1) g1_only(std::integral_constant<int, 1>{}, 1);
+            if (last >= 1) g1_only(std::integral_constant<int, 1>{}, b_at[1]);
             using Lazy = std::integral_constant<int, LAZY>;
             using Buf0 = std::integral_constant<int, 0>;
             using Buf1 = std::integral_constant<int, 1>;
             softmax_only(Buf0{}, Lazy{}, 0);
+            turn();
             // iterations 1 .. last-1, the two C^T buffers swap roles at compile time
             int i = 1;
             if constexpr (STAND) {
@@ -1113,11 +1173,12 @@ void chain_kernel(const KParams p) {
                     top(t);
                     steady(curc, Stands{}, t);
                     if (__builtin_expect(some_blind || outgrown(), 0)) {
-                        g1_only(curc, t);
+                        g1_only(curc, b_at[0]);
                         __builtin_amdgcn_sched_barrier(0);
                         softmax_only(curc, Exact{}, t);
                         some_blind = blind();
                     }
+                    turn();
                 };
                 for (; i + 1 <= last - 1; i += 2) {
                     one(Buf1{}, i);
@@ -1127,13 +1188,16 @@ void chain_kernel(const KParams p) {
                 for (; i + 1 <= last - 1; i += 2) {
                     top(i);
                     steady(Buf1{}, Lazy{}, i);
+                    turn();
                     top(i + 1);
                     steady(Buf0{}, Lazy{}, i + 1);
+                    turn();
                 }
             }
             if (i <= last - 1) {
                 top(i);
                 steady(Buf1{}, Lazy{}, i);
+                turn();
             }
             // iteration `last` (if it is not iteration 0): GEMM 2 of the tile before, softmax of the
             // last, which is moved to the first C^T buffer if it sits in the second (two copies of
@@ -1146,11 +1210,15 @@ void chain_kernel(const KParams p) {
                         for (int mb = 0; mb < MB; ++mb) cc[0][j][mb] = cc[1][j][mb];
                 }
                 top(last);
-                g2_only(last - 1);
+                g2_only(d_at[0]);
                 softmax_only(Buf0{}, Lazy{}, last);
             }
             // GEMM 2 of the last tile
-            g2_only(last);
+            if (R.ahead == 0 && last >= R.d_first) { // (whose D was requested at the top of this iteration)
+                wait_vm<0>();
+                __syncthreads();
+            }
+            g2_only(last > 0 ? d_at[1] : d_slot(0));
         }
     } else if constexpr (!SKEW) {
         int stage_c = 0;     // ring slot of the tile being consumed
@@ -1489,7 +1557,7 @@ void chain_kernel(const KParams p) {
 // Host-side launcher of one instantiation.
 template <typename T, int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool BKC, bool KSPLIT = false, int PD = 0>
 int launch_chain(const KParams &p, void *stream) {
-    constexpr int lds = kernel_lds_bytes<KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD>();
+    constexpr int lds = block_lds_bytes(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD);
     auto kern = chain_kernel<T, KD, LD, MB, RG, NS, NJ, SOFTMAX, BKC, KSPLIT, PD>;
     // More than 64 KiB of dynamic LDS has to be allowed per function and device, once.  (A race
     // between two threads sets the attribute twice, which is harmless.)
@@ -1513,7 +1581,7 @@ int launch_chain(const KParams &p, void *stream) {
 // wave's run of accumulator blocks would straddle row sets.  Such kernels are not compiled.
 template <typename T, int KD, int LD, int MB, int RG, int NS, int NJ, bool SOFTMAX, bool BKC, bool KSPLIT = false, int PD = 0>
 constexpr LaunchFn launcher_or_null() {
-    if constexpr (kernel_lds_bytes<KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD>() <= kLdsBytesPerBlock &&
+    if constexpr (block_lds_bytes(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD) <= kLdsBytesPerBlock &&
                   combine_runs_ok(LD, MB, NS) && (PD == 0 || NS == 1 || PD == LD))
         return &launch_chain<T, KD, LD, MB, RG, NS, NJ, SOFTMAX, BKC, KSPLIT, PD>;
     else

@@ -129,7 +129,7 @@ int candidates3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, std
 static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mcf_tiles *out) {
     bool first = true;
     return each_candidate3(p, softmax, b_kcontig, P, [&](const mcf_tiles &t) {
-        if (first || better(t, *out)) *out = t;
+        if (first || better(t, *out, softmax, p->K, chain3_f_bytes((int)p->L, (int)P))) *out = t;
         first = false;
     });
 }
@@ -145,7 +145,8 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 //    (causal, 2376 blocks, K = L = 64: 1.10 of the time with eight).
 //    Plain chains in eight waves across m take two slices a wave for one, where that pads N by an eighth of it at most (one n-tile
 //    of 64 columns costs a block less than two of 32): 40 x [1000,96].[96,776].[776,96] 21.0 -> 17.9 us, the same with K = L = 64
-//    14.7 -> 13.4 and with 128 22.4 -> 21.5; 80 x [500,64].[64,520].[520,128] 15.4 -> 13.9 us.
+//    14.7 -> 13.4 and with 128 22.4 -> 21.5; 80 x [500,64].[64,520].[520,128] 15.4 -> 13.9 us.  Not with more blocks than compute
+//    units, where the registers of one slice let two blocks share one: 70 x [2707,96].[96,2464].[2464,96] 173 against 188 us.
 //  * Among equal estimates it takes the wider n-tile.  Softmax kernels of four waves whose rows are padded to the
 //    LDS pitch (K = 80, 96, 160, 192) spill scalar registers with two slices a wave, and run better with one: the calls
 //    of a sweep that were picked so take 0.80 to 1.02 of their time; causal 40 x 333 x 1357, K = L = 80: 23 -> 20.5 us.
@@ -168,7 +169,7 @@ static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_t
         w.ns = 2;
         for (w.nj = 2; w.nj >= 1; --w.nj)
             if (built(p, softmax, b_kcontig, t->tn, &w)) { *t = w; return; }
-    } else if (!softmax && t->mb == 1 && t->rg == 8 && t->ns == 1 && t->nj == 1) {
+    } else if (!softmax && t->mb == 1 && t->rg == 8 && t->ns == 1 && t->nj == 1 && t->blocks <= kComputeUnits) {
         w.nj = 2;
         if (eval_tiles(p, softmax, b_kcontig, &w) == MCF_OK && 8 * padding_of(p->N, w.tn) <= p->N) *t = w;
     } else if (softmax && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2 && pitch_elems(t->tk) != t->tk) {

@@ -103,17 +103,6 @@ constexpr int total_lds_bytes(int K, int L, int mb, int rg, int ns, int nj, int 
     const int c = combine_bytes(L, mb, rg, ns) + estage_bytes(L, mb, rg, ns);
     return s > c ? s : c;
 }
-// Three-GEMM chain (E . F with F[L x P] after the loop): the F tile sits behind everything else
-// for the whole life of the block; the output tile is combined and staged like E.
-constexpr int chain3_f_bytes(int L, int P) { return L * pitch_elems(P) * 2; }
-constexpr int chain3_f_offset(int K, int L, int P, int mb, int rg, int ns, int nj, int stages) {
-    const int t = total_lds_bytes(K, L, mb, rg, ns, nj, stages);
-    const int e = combine_bytes(P, mb, rg, ns) + estage_bytes(P, mb, rg, ns);
-    return ((t > e ? t : e) + 1023) / 1024 * 1024;
-}
-constexpr int chain3_lds_bytes(int K, int L, int P, int mb, int rg, int ns, int nj, int stages) {
-    return chain3_f_offset(K, L, P, mb, rg, ns, nj, stages) + chain3_f_bytes(L, P);
-}
 // Largest ring depth (2..4) that keeps a block within `budget` bytes of LDS.
 constexpr int pick_stages(int K, int L, int mb, int rg, int ns, int nj, int budget, bool ksplit = false) {
     int s = 4;
@@ -127,51 +116,131 @@ constexpr int pick_stages(int K, int L, int mb, int rg, int ns, int nj, int budg
 constexpr int kLdsRingBudget = 80 * 1024;
 // Softmax chains (and the plain chains named below) run a software pipeline over three consecutive n-tiles: in iteration i a wave
 // issues the MFMAs of GEMM 2 of tile i-1 and of GEMM 1 of tile i+1 with the softmax arithmetic of
-// tile i spread between them, so tiles i-1, i and i+1 are live and tile i+2 is landing: a ring of
-// 4 (measured: a deeper one is slower, by up to a fifth on the short attention shapes).
-// 0 = the arrangement cannot be pipelined because four stages do not fit the compute unit (its
-// softmax loop then runs the phases one after the other, see skewed_groups).  `extra` = LDS held
-// beside the ring (the F tile of a three-GEMM chain).
-constexpr int pipe_stages(int K, int L, int mb, int rg, int ns, int nj, bool softmax, bool ksplit = false, int extra = 0) {
-    if (ksplit) return 0;
-    // plain chains: only where K and L are 32, in blocks of 8 waves that own at most two row sets
-    // each (measured on 16 x [4096,32].[32,1024].[1024,32]: 3-4 % faster for (1,8,1,2) and (2,4,2,2),
-    // no change for (1,4,2,2), a third slower for (4,2,4,1); with K = L = 64 slower throughout)
-    if (!softmax && !(K <= 32 && L <= 32 && mb <= 2 && rg * ns == 8)) return 0;
-    return total_lds_bytes(K, L, mb, rg, ns, nj, 4) + extra <= 160 * 1024 ? 4 : 0;
+// tile i spread between them.  It reads B two tiles ahead of D, so the two have rings of their own: D of tiles i-1 and i
+// (landing), B of tiles i+1 and i+2 (landing) and, for a softmax that may have to form the scores of tile i again, of tile i.
+// That is two to two and a half tiles where one ring of B + D tiles took four, at the same distance between a request and
+// its use; what it leaves is a second block per compute unit, a wider n-tile, the F tile of a three-GEMM chain, rows
+// of 160 and 192, or one more tile of each in flight (`ahead`).  The first tiles are requested before the loop, with the A tile
+// behind them.
+struct PipeRing {
+    int ahead;   // tiles of B and of D in flight beyond those an iteration waits for
+    int d_first; // D tiles requested before the loop
+    int b_slots, d_slots;
+    int d_rest, b_offset, a_offset; // offsets of D slots d_first .. (less that of slot d_first in a plain row of slots), the B ring, the A tile
+    int bytes;
+};
+constexpr PipeRing pipe_ring_with(int K, int L, int mb, int rg, int ns, int nj, bool stands, int ahead, int d_first) {
+    const int b = b_tile_bytes(K, 32 * ns * nj), d = d_tile_bytes(L, 32 * ns * nj);
+    PipeRing r = {};
+    r.ahead = ahead;
+    r.d_first = d_first;
+    r.b_slots = ahead + (stands ? 3 : 2);
+    r.d_slots = ahead + 2;
+    r.b_offset = d_first * d;
+    r.d_rest = r.b_slots * b;
+    r.a_offset = r.b_offset + (2 + ahead) * b;
+    const int ring = r.b_slots * b + r.d_slots * d, first = r.a_offset + a_tile_bytes(K, mb, rg);
+    const int c = combine_bytes(L, mb, rg, ns) + estage_bytes(L, mb, rg, ns);
+    r.bytes = ring > first ? ring : first;
+    r.bytes = r.bytes > c ? r.bytes : c;
+    return r;
+}
+// Three-GEMM chain (E . F with F[L x P] after the loop): the F tile sits behind everything else
+// (`below` bytes and the combined and staged output tile) for the whole life of the block.
+constexpr int chain3_f_bytes(int L, int P) { return P > 0 ? L * pitch_elems(P) * 2 : 0; }
+constexpr int chain3_f_offset(int below, int P, int mb, int rg, int ns) {
+    const int e = combine_bytes(P, mb, rg, ns) + estage_bytes(P, mb, rg, ns);
+    return ((below > e ? below : e) + 1023) / 1024 * 1024;
+}
+constexpr int with_f_tile(int below, int L, int P, int mb, int rg, int ns) {
+    return P > 0 ? chain3_f_offset(below, P, mb, rg, ns) + chain3_f_bytes(L, P) : below;
 }
 // Waves per SIMD a pipelined softmax kernel is compiled for.  A block brings rg*ns/4 of them; a
 // second resident block hides the block's barriers and the ends of its pipeline (measured: a
 // third to a half faster on the short attention shapes), but the compiler only keeps to the
 // registers that leaves a wave (512 / waves) when told so, otherwise it drifts a few registers
-// over.  Asked for when two blocks fit the LDS and the tiles a lane must hold (the E
-// accumulators, two C^T tiles, P packed to 16 bit) leave some 56 registers for operands,
-// addresses and the softmax state.
-constexpr int pipe_waves_per_simd(int K, int L, int mb, int rg, int ns, int nj, int extra = 0) {
+// over.  Asked for when two blocks fit the LDS and the registers hold what a lane must: the E
+// accumulators, two C^T tiles, P packed to 16 bit, the A operands, and 40 for the LDS operands in flight, addresses and the
+// softmax state, more with a second row set (16) or slice (20).  (Asked for with fewer, they spill: K = 128, L = 64, (1,8,1,1).)
+constexpr int pipe_needs(int K, int L, int mb, int nj) {
+    return mb * h_blocks(L) * 16 + 2 * nj * mb * 16 + nj * mb * 8 + mb * (K / 16) * 4 + 4 + 16 * mb + 20 * nj;
+}
+constexpr int pipe_lds_least(int K, int L, int mb, int rg, int ns, int nj, int P, bool stands) {
+    return with_f_tile(pipe_ring_with(K, L, mb, rg, ns, nj, stands, 0, 0).bytes, L, P, mb, rg, ns);
+}
+constexpr int pipe_waves_with(int K, int L, int mb, int rg, int ns, int nj, int P, bool stands) {
     const int per_block = rg * ns >= 4 ? rg * ns / 4 : 1;
-    if (2 * (total_lds_bytes(K, L, mb, rg, ns, nj, 4) + extra) > 160 * 1024) return per_block;
-    const int held = mb * h_blocks(L) * 16 + 2 * nj * mb * 16 + nj * mb * 8;
-    return held + 56 <= 512 / (2 * per_block) ? 2 * per_block : per_block;
+    if (mb * rg == 1) return per_block; // m-tiles of 32 rows: calls of few blocks, for which loads in flight count more
+    if (2 * pipe_lds_least(K, L, mb, rg, ns, nj, P, stands) > 160 * 1024) return per_block;
+    return pipe_needs(K, L, mb, nj) <= 512 / (2 * per_block) ? 2 * per_block : per_block;
 }
 // Whether a pipelined softmax kernel leaves the reference of its exponentials where it stands between the
-// first tile and the last (see the loop): with two waves on a SIMD or more, and 72 registers beside the held tiles,
-// which the way back from an outgrown reference needs (with 56 the 8-wave kernels of K = L = 64 spill in the loop).
-constexpr bool reference_stands(int K, int L, int mb, int rg, int ns, int nj, bool softmax, int extra = 0) {
-    const int waves = pipe_waves_per_simd(K, L, mb, rg, ns, nj, extra);
-    const int held = mb * h_blocks(L) * 16 + 2 * nj * mb * 16 + nj * mb * 8;
-    return softmax && waves >= 2 && held + 72 <= 512 / waves;
+// first tile and the last (see the loop): with two waves on a SIMD or more, and 16 registers more,
+// which the way back from an outgrown reference needs (without them the 8-wave kernels of K = L = 64 spill in the loop).
+constexpr bool reference_stands(int K, int L, int mb, int rg, int ns, int nj, bool softmax, int P) {
+    const int waves = pipe_waves_with(K, L, mb, rg, ns, nj, P, true);
+    return softmax && waves >= 2 && pipe_needs(K, L, mb, nj) + 16 <= 512 / waves && pipe_lds_least(K, L, mb, rg, ns, nj, P, true) <= 2 * kLdsRingBudget;
+}
+constexpr int pipe_waves_per_simd(int K, int L, int mb, int rg, int ns, int nj, bool softmax, int P) {
+    // (K = L = 32 in blocks of four waves: five blocks; 95 to 97 registers when not told, and 97 cost the fifth)
+    if (K <= 32 && L <= 32 && mb == 1 && nj == 1 && rg > 1 && rg * ns == 4) return 5;
+    return pipe_waves_with(K, L, mb, rg, ns, nj, P, reference_stands(K, L, mb, rg, ns, nj, softmax, P));
+}
+// The rings of a pipelined kernel, where they cost none of the blocks that the registers let a compute unit hold.  The first D tile
+// is requested before the loop: a block of a few n-tiles otherwise waits for a load latency more than it has tiles (9 x 640 x
+// 128, K = L = 64: 5.8 -> 6.6 us).  With one wave on a SIMD, whose blocks are few and wait for their loads, so is the second
+// (17 x 163 x 167, K = L = 80: 7.6 -> 9.4 us without), and one more tile of B and D is in flight throughout (25 x 1 x 515, K = L =
+// 128: 10.2 -> 8.7 us; with two waves 1 % slower, 96 x 512 x 512, K = L = 64: 12.8 -> 13.0).
+constexpr PipeRing pipe_ring(int K, int L, int mb, int rg, int ns, int nj, bool softmax, int P) {
+    const bool stands = reference_stands(K, L, mb, rg, ns, nj, softmax, P);
+    const int waves = rg * ns, by_registers = 512 / pipe_needs(K, L, mb, nj) * 4 / waves;
+    int blocks = 160 * 1024 / pipe_lds_least(K, L, mb, rg, ns, nj, P, stands);
+    blocks = blocks < by_registers ? blocks : by_registers > 1 ? by_registers : 1;
+    const bool one_wave = pipe_waves_per_simd(K, L, mb, rg, ns, nj, softmax, P) == 1;
+    if (mb * rg == 1) blocks = 1;
+    // (one more in flight is counted in loads of a wave, which must then be as many for every wave)
+    const bool counted = stage_bytes(K, L, 32 * ns * nj) / 1024 % waves == 0;
+    for (int q = one_wave ? (counted ? 0 : 1) : 2; q < 3; ++q) { // (ahead, d_first): (1, 2), (0, 2), (0, 1)
+        const PipeRing r = pipe_ring_with(K, L, mb, rg, ns, nj, stands, q == 0 ? 1 : 0, q < 2 ? 2 : 1);
+        if (blocks * with_f_tile(r.bytes, L, P, mb, rg, ns) <= 160 * 1024) return r;
+    }
+    return pipe_ring_with(K, L, mb, rg, ns, nj, stands, 0, 0);
+}
+// Whether an arrangement is pipelined (P: columns of F, 0 without a third GEMM): where it fits the LDS of a compute unit and its
+// registers (blocks of four waves: the half of the file that vector instructions reach, and a little of the other; beyond that
+// they spill).  The softmax loop of the others runs the phases one after the other, see skewed_groups.
+constexpr bool pipelined(int K, int L, int mb, int rg, int ns, int nj, bool softmax, bool ksplit, int P) {
+    if (ksplit) return false;
+    // plain chains: only where K and L are 32, in blocks of 8 waves that own at most two row sets
+    // each (measured on 16 x [4096,32].[32,1024].[1024,32]: 3-4 % faster for (1,8,1,2) and (2,4,2,2),
+    // no change for (1,4,2,2), a third slower for (4,2,4,1); with K = L = 64 slower throughout)
+    if (!softmax && !(K <= 32 && L <= 32 && mb <= 2 && rg * ns == 8)) return false;
+    if (softmax && pipe_needs(K, L, mb, nj) > (rg * ns > 4 ? 256 : 320)) return false;
+    return pipe_lds_least(K, L, mb, rg, ns, nj, P, reference_stands(K, L, mb, rg, ns, nj, softmax, P)) <= 2 * kLdsRingBudget;
 }
 // Softmax chains that cannot be pipelined, in blocks of 8 waves, run their two wave groups a
 // phase apart, which keeps two n-tiles live: their ring is at least 3 deep.
 constexpr bool skewed_groups(int rg, int ns, bool softmax, bool ksplit = false) { return softmax && rg * ns == 8 && !ksplit; }
-constexpr int ring_stages(int K, int L, int mb, int rg, int ns, int nj, bool softmax, bool ksplit = false, int extra = 0) {
+// Depth of the ring of B + D tiles (k loop: of its items); a pipelined kernel holds two tiles whole.
+constexpr int ring_stages(int K, int L, int mb, int rg, int ns, int nj, bool softmax, bool ksplit, int P) {
     // the items of a k loop are small and many, and the shapes that need one rarely fill the
     // machine: as deep as the whole LDS allows, to keep as many loads in flight as possible
     if (ksplit) return pick_stages(K, L, mb, rg, ns, nj, 2 * kLdsRingBudget, true);
-    const int ps = pipe_stages(K, L, mb, rg, ns, nj, softmax, ksplit, extra);
-    if (ps) return ps;
+    if (pipelined(K, L, mb, rg, ns, nj, softmax, ksplit, P)) return 2;
     const int s = pick_stages(K, L, mb, rg, ns, nj, kLdsRingBudget);
     return (skewed_groups(rg, ns, softmax) && s < 3) ? 3 : s;
+}
+// LDS bytes of a kernel without the F tile of a three-GEMM chain, offset of that tile, and all of them.
+constexpr int ring_lds_bytes(int K, int L, int mb, int rg, int ns, int nj, bool softmax, bool ksplit, int P) {
+    if (pipelined(K, L, mb, rg, ns, nj, softmax, ksplit, P)) return pipe_ring(K, L, mb, rg, ns, nj, softmax, P).bytes;
+    return total_lds_bytes(K, L, mb, rg, ns, nj, ring_stages(K, L, mb, rg, ns, nj, softmax, ksplit, P), ksplit);
+}
+constexpr int f_lds_offset(int K, int L, int mb, int rg, int ns, int nj, bool softmax, int P) {
+    return chain3_f_offset(ring_lds_bytes(K, L, mb, rg, ns, nj, softmax, false, P), P, mb, rg, ns);
+}
+constexpr int block_lds_bytes(int K, int L, int mb, int rg, int ns, int nj, bool softmax, bool ksplit, int P) {
+    if (P > 0) return f_lds_offset(K, L, mb, rg, ns, nj, softmax, P) + chain3_f_bytes(L, P);
+    return ring_lds_bytes(K, L, mb, rg, ns, nj, softmax, ksplit, P);
 }
 
 } // namespace mcf

@@ -54,7 +54,7 @@ int vgpr_estimate(int K, int L, int mb, int rg, int ns, int nj, int softmax, int
     const int hb = h_blocks(L);
     // a pipelined chain holds C of two consecutive n-tiles and the 16-bit P of one
     // (and fetches its LDS operands two MFMA steps ahead instead of a GEMM at a time)
-    const bool piped = pipe_stages(K, L, mb, rg, ns, nj, softmax != 0, ksplit != 0) > 0;
+    const bool piped = pipelined(K, L, mb, rg, ns, nj, softmax != 0, ksplit != 0, 0);
     const int c_tiles = piped ? nj * mb * (16 + 16 + 8) : nj * mb * (16 + 8);
     const int operands = piped ? 16 : (K / 16) * 4 + hb * 8;
     return mb * (K / 16) * 4 + mb * hb * 16 + c_tiles + operands + loads + 24 + (softmax ? 16 : 0);
@@ -65,10 +65,8 @@ int vgpr_estimate(int K, int L, int mb, int rg, int ns, int nj, int softmax, int
 static int vgpr_cap(int waves) { return kVgprBudget / ((waves + 3) / 4); }
 
 void describe(Built *v) {
-    v->stages = ring_stages(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0,
-                            v->P > 0 ? chain3_f_bytes(v->L, v->P) + 1024 : 0);
-    v->lds_bytes = v->P > 0 ? chain3_lds_bytes(v->K, v->L, v->P, v->mb, v->rg, v->ns, v->nj, v->stages)
-                            : total_lds_bytes(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->stages, v->ksplit != 0);
+    v->stages = ring_stages(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0, v->P);
+    v->lds_bytes = block_lds_bytes(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0, v->P);
     v->vgpr_est = vgpr_estimate(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax, v->ksplit);
     v->fits = v->lds_bytes <= kLdsBytesPerBlock && v->vgpr_est <= vgpr_cap(v->rg * v->ns) && v->scratch_bytes == 0;
     v->two = nullptr;
@@ -123,13 +121,17 @@ void eval_model(const mcf_problem *p, const Built *v, mcf_tiles *t) {
 
 // Strict ordering of candidates: smaller estimate first; among equal estimates (the model
 // does not see how the waves of a block are arranged) more waves per block, then a block
-// whose LDS leaves room for a second one on the compute unit, then fewer waves across n (less
+// whose LDS leaves room for a second one on the compute unit (softmax: counted as a ring of four whole tiles), then fewer waves across n (less
 // to combine), then more column slices per wave, then fewer rows per wave.
-bool better(const mcf_tiles &a, const mcf_tiles &b) {
+static bool two_resident(const mcf_tiles &t, int softmax, int64_t K, int extra) {
+    const int lds = softmax && t.tk == K ? total_lds_bytes(t.tk, t.tl, t.mb, t.rg, t.ns, t.nj, 4) : t.lds_bytes;
+    return 2 * (softmax ? lds + extra : lds) <= kLdsBytesPerBlock;
+}
+bool better(const mcf_tiles &a, const mcf_tiles &b, int softmax, int64_t K, int extra) {
     if (a.t_est_s != b.t_est_s) return a.t_est_s < b.t_est_s;
     if (a.tl != b.tl) return a.tl > b.tl;
     if (a.waves != b.waves) return a.waves > b.waves;
-    const bool a2 = 2 * a.lds_bytes <= kLdsBytesPerBlock, b2 = 2 * b.lds_bytes <= kLdsBytesPerBlock;
+    const bool a2 = two_resident(a, softmax, K, extra), b2 = two_resident(b, softmax, K, extra);
     if (a2 != b2) return a2;
     if (a.ns != b.ns) return a.ns < b.ns;
     if (a.nj != b.nj) return a.nj > b.nj;
@@ -223,7 +225,7 @@ extern "C" int mcf_list_candidates(const mcf_problem *p, int softmax, mcf_tiles 
 int mcf::pick_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *out) {
     bool first = true;
     return each_candidate(p, softmax, b_kcontig, [&](const mcf_tiles &t) {
-        if (first || better(t, *out)) *out = t;
+        if (first || better(t, *out, softmax, p->K)) *out = t;
         first = false;
     });
 }
