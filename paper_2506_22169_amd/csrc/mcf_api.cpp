@@ -160,6 +160,78 @@ static bool built(const mcf_problem *p, int softmax, int b_kcontig, int64_t tn_n
     const int64_t pad = padding_of(p->N, t->tn);
     return 20 * pad < p->N || pad <= padding_of(p->N, tn_now); // Rule 3
 }
+// Columns that the m-tiles of tm rows see under a mask of that offset, and the last row: m-tile m sees tm (m + 1) + off of them, within 0 .. N.
+static int64_t visible_columns(int64_t M, int64_t N, int64_t tm, int64_t off, int64_t *last) {
+    const auto within = [](int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : x > hi ? hi : x; };
+    const int64_t tiles = (M + tm - 1) / tm;
+    const int64_t none = within(off < 0 ? -off / tm : 0, 0, tiles);                     // m-tiles [0, none) see nothing,
+    const int64_t all = within(N > off ? (N - off + tm - 1) / tm - 1 : 0, none, tiles);  // [all, tiles) everything
+    const int64_t rising = all - none;
+    *last = within(M + off, 0, N);
+    return rising * off + tm * (rising * (none + 1 + all) / 2) + (tiles - all) * N;
+}
+
+// Time of a softmax chain in us from how many blocks a compute unit holds, which the model's estimate does not see: its units
+// take their blocks in rounds of as many as LDS and registers let them hold, a round lasts as long as the
+// matrix and vector work of its blocks at the rate that their waves reach together, and ends with a fill and a drain.
+// Under a mask (off: its offset) a call takes as long as its longest block at least.  Constants fitted to 419 calls drawn from the
+// ranges of the chains with 129 blocks or more, nine arrangements each.
+static double softmax_time(const mcf_problem *p, const Built *v, double cost, const int64_t *off) {
+    static const double kRate[4] = {0.72, 1.0, 1.08, 1.08}; // of 1 to 4 waves a SIMD, against two
+    const int waves = v->rg * v->ns, simd = waves > 4 ? waves / 4 : 1;
+    const int tm = 32 * v->mb * v->rg, tn = 32 * v->ns * v->nj;
+    int held = kVgprBudget / ((v->vgprs + 7) / 8 * 8) / simd;
+    held = held < kLdsBytesPerBlock / v->lds_bytes ? held : kLdsBytesPerBlock / v->lds_bytes;
+    if (held < 1) held = 1;
+    const int64_t m_tiles = (p->M + tm - 1) / tm, blocks = p->batch * m_tiles;
+    const double padded = (double)((p->N + tn - 1) / tn * tn);
+    double mean = padded, longest = padded;
+    if (off) {
+        int64_t last;
+        mean = (double)visible_columns(p->M, p->N, tm, *off, &last) / (double)m_tiles + 0.5 * tn;
+        mean = mean < padded ? mean : padded;
+        longest = (double)((last + tn - 1) / tn * tn);
+    }
+    const double column = tm * (0.325 * (double)(p->K + p->L) + 20.1) * cost * 1e-6, ends = 4.3;
+    const auto rate = [&](int64_t r) { return kRate[r * simd < 4 ? r * simd - 1 : 3]; };
+    const int64_t slots = (int64_t)kComputeUnits * held, full = blocks / slots, rest = blocks - full * slots;
+    const int64_t together = rest > 0 ? (rest + kComputeUnits - 1) / kComputeUnits : 0;
+    double t = (double)full * ((double)held * column * mean / rate(held) + ends);
+    if (together > 0) t += (double)together * column * mean / rate(together) + ends;
+    if (longest > mean) {
+        int64_t beside = blocks <= kComputeUnits ? 1 : (blocks + kComputeUnits - 1) / kComputeUnits;
+        beside = beside < held ? beside : held;
+        const double alone = (double)beside * column * longest / rate(beside) + ends;
+        t = blocks > slots && t > alone ? t : alone;
+    }
+    return t + 1.0;
+}
+// A softmax chain that n is not split for (more blocks than half the compute units): another arrangement of whole L where that is a tenth faster at
+// least by softmax_time.  279 calls without a mask that were not in the fit's first half: 0.42 to 1.08 of the time, 0.96 in the mean;
+// 140 with one: 0.64 to 1.10, 0.98.
+static void settle_softmax(const mcf_problem *p, int b_kcontig, const int64_t *off, mcf_tiles *t) {
+    static const struct { int rg, ns, nj; double cost; } kCost[] = { // of a column of an m-tile, against each other
+        {8, 1, 2, 0.88}, {8, 1, 1, 1.00}, {4, 1, 2, 0.92}, {4, 1, 1, 1.01}, {4, 2, 2, 0.98}, {4, 2, 1, 1.12}, {2, 2, 2, 1.27}, {2, 2, 1, 1.22}, {1, 4, 1, 1.82}};
+    if (p->N <= 0 || t->tl != p->L || 2 * t->blocks <= kComputeUnits) return;
+    const Group *g = resolve_group(p->in_dtype, p->K, p->L);
+    if (!g || g->ksplit) return;
+    const Built *best = nullptr;
+    double now = 0., least = 0.;
+    for (const Built *v : g->of[1][b_kcontig]) {
+        if (v->mb != 1 || !v->fits || v->vgprs <= 0) continue;
+        for (const auto &c : kCost) {
+            if (v->rg != c.rg || v->ns != c.ns || v->nj != c.nj) continue;
+            const bool same = t->mb == 1 && t->rg == c.rg && t->ns == c.ns && t->nj == c.nj;
+            // (three blocks a unit and more: the fit is least sure of these, so a call does not leave them)
+            if (same && c.rg == 2 && c.nj == 1 && p->K <= 64) return;
+            const double us = softmax_time(p, v, c.cost, off);
+            if (same) now = us;
+            const int64_t blocks = p->batch * ((p->M + 32 * c.rg - 1) / (32 * c.rg));
+            if (2 * blocks > kComputeUnits && (!best || us < least)) { best = v; least = us; }
+        }
+    }
+    if (best && now > 0. && 1.1 * least < now) eval_model(p, best, t);
+}
 static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *t) {
     if (t->tk < p->K) return; // a k loop: measured as it is
     mcf_tiles w;
@@ -206,16 +278,11 @@ static int64_t ranges_for(int64_t blocks, int64_t n_tiles, int64_t items_per_til
 // 79 x 704 x 3200, K = L = 64, nothing hidden: 70 against 100 us; 102 x 538 x 6145, the last row seeing all: 294 against 347.
 // Over 100 calls with 257 to 4000 blocks, longest first took 0.88 to 1.43 of the time (1.05 in the mean) where the
 // longest block is less than an eighth longer than the mean one, 0.70 to 1.02 (0.88) where it is more.
-// Lengths in columns: m-tile m sees tm (m + 1) + off of them, within 0 .. N.
 bool longest_first(int64_t M, int64_t N, int64_t tm, int64_t off) {
     if (M <= 0 || N <= 0) return false;
-    const auto within = [](int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : x > hi ? hi : x; };
-    const int64_t tiles = (M + tm - 1) / tm;
-    const int64_t none = within(off < 0 ? -off / tm : 0, 0, tiles);                           // m-tiles [0, none) see nothing,
-    const int64_t all = within(N > off ? (N - off + tm - 1) / tm - 1 : 0, none, tiles);        // [all, tiles) everything
-    const int64_t rising = all - none;
-    const int64_t sum = rising * off + tm * (rising * (none + 1 + all) / 2) + (tiles - all) * N;
-    return 8 * within(M + off, 0, N) * tiles >= 9 * sum && sum > 0;
+    int64_t last;
+    const int64_t sum = visible_columns(M, N, tm, off, &last);
+    return 8 * last * ((M + tm - 1) / tm) >= 9 * sum && sum > 0;
 }
 
 // Validation, tile choice and kernel arguments of one call.  P == 0: the two-GEMM chain into
@@ -279,6 +346,10 @@ int prepare(const mcf_call *call, Launch *o) {
         st = ch3 ? pick3(p, softmax, lay.b_kcontig, P, &chosen) : pick_tiles(p, softmax, lay.b_kcontig, &chosen);
         if (st != MCF_OK) return st;
         if (!ch3) settle_tiles(p, softmax, lay.b_kcontig, &chosen);
+        if (!ch3 && softmax) {
+            const int64_t off = call->causal_offset > p->N ? p->N : call->causal_offset < -p->M ? -p->M : call->causal_offset;
+            settle_softmax(p, lay.b_kcontig, call->causal ? &off : nullptr, &chosen);
+        }
     }
     const int64_t tl = ch3 ? p->L : (chosen.tl > 0 ? chosen.tl : p->L);
     if (p->L % tl != 0) return MCF_EINVAL;

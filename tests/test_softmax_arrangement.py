@@ -1,0 +1,52 @@
+"""What a softmax call without tiles runs where the model's pick leaves blocks waiting that another arrangement would hold at once (host only)."""
+import random
+
+import pytest
+
+import paper_2506_22169_amd as mcf
+from paper_2506_22169_amd.binding import call_tiles, list_candidates, make_problem
+
+
+def _ran(b, M, K, N, L, causal=False, dtype="bf16", off=None, **kw):
+    p = make_problem(b, M, K, N, L, dtype, b_stride=(N * K, 1, K))
+    t, ranges = call_tiles(p, True, causal_offset=(N - M if off is None else off) if causal else None, **kw)
+    return (t.mb, t.rg, t.ns, t.nj, t.tl), ranges, t, p
+
+
+@pytest.mark.parametrize("call,run", [
+    (dict(b=103, M=1088, K=192, N=512, L=192), (1, 4, 1, 1, 192)),                  # 1751 blocks of 64 rows, one a unit: 95 -> 54 us
+    (dict(b=40, M=1216, K=128, N=1280, L=128, dtype="f16"), (1, 8, 1, 2, 128)),      # 760 blocks of 64 rows: 62 -> 39 us
+    (dict(b=35, M=1364, K=128, N=1096, L=128, dtype="f16"), (1, 4, 1, 1, 128)),      # less than a tenth to win: the pick
+    (dict(b=64, M=4096, K=128, N=4096, L=128), (1, 8, 1, 2, 128)),
+    (dict(b=14, M=3072, K=64, N=3072, L=64, causal=True), None),                     # 168 blocks of unequal length: smaller ones
+])
+def test_arrangement_of_many_blocks(call, run):
+    got, ranges, t, p = _ran(**call)
+    assert ranges == 1 and t.scratch_bytes == 0
+    if run is None:
+        q = mcf.pick_tiles(p, True)
+        assert t.tm < q.tm and t.blocks > q.blocks
+    else:
+        assert got == run
+
+
+def test_what_is_left_alone():
+    """Calls of 128 blocks and fewer (n may be split), given tiles, T_L < L; and an arrangement that is taken in their place is a candidate
+    that leaves more than 128 blocks, for any size and offset."""
+    rng = random.Random(4)
+    moved = 0
+    for _ in range(1500):
+        K = rng.choice([32, 64, 80, 96, 128, 160, 192, 256])
+        b, M, N = rng.randint(1, 200), rng.choice([1, 7, 64, 333, 1000, 4096, rng.randint(1, 5000)]), rng.choice([1, 64, 777, rng.randint(1, 9000)])
+        causal = rng.random() < 0.5
+        off = rng.choice([0, N - M, -M // 2, N, -M - 5, 10**9, -10**9])
+        got, ranges, t, p = _ran(b, M, K, N, K, causal, off=off)
+        q = mcf.pick_tiles(p, True)
+        if q.blocks <= 128:
+            assert (t.mb, t.rg) == (q.mb, q.rg) and t.blocks == q.blocks
+        elif t.blocks != q.blocks:
+            moved += 1
+            assert t.blocks > 128 and ranges == 1 and t.tl == K and t.scratch_bytes == 0
+        given = list_candidates(p, True)[0]
+        assert _ran(b, M, K, N, K, causal, off=off, tiles=(given.mb, given.rg, given.ns, given.nj, given.tl))[0][:4] == (given.mb, given.rg, given.ns, given.nj)
+    assert moved > 50
