@@ -438,7 +438,11 @@ int prepare(const mcf_call *call, Launch *o) {
         c.E = E; c.n_split = (int32_t)n_split; c.out_f32 = p->out_dtype == MCF_F32;
         k.se_b = p->M * c.pitch; k.se_r = c.pitch; k.se_s = c.split_stride;
         o->workspace_bytes = n_split * c.split_stride * 4;
-        if (c.rows * (c.L >> 2) / 256 >= (1ll << 31) - 1 || c.split_stride > (1ll << 40)) return MCF_EUNSUPPORTED;
+        // (rows and their places are formed in 32 bits: a workspace of more would be 550 GB at least)
+        if (c.rows >= (1ll << 31) || c.split_stride > (1ll << 40)) return MCF_EUNSUPPORTED;
+        c.block_rows = 256 / (c.L >> 2);
+        division_magic((uint32_t)(c.L >> 2), &c.quads_magic, &c.quads_shift);
+        division_magic((uint32_t)p->M, &c.m_magic, &c.m_shift);
     }
     o->v = v;
     o->tiles.mb = v->mb; o->tiles.rg = v->rg; o->tiles.ns = v->ns; o->tiles.nj = v->nj; o->tiles.tl = (int32_t)tl;

@@ -71,6 +71,9 @@ struct CombineParams {
     int64_t se_b, se_r;   // E: batch / row stride
     void *E;
     int32_t pitch, L, n_split, out_f32;
+    int32_t block_rows;   // rows of a block of 256 lanes, each of four columns
+    uint32_t quads_magic, m_magic; // division_magic of L / 4 and of M
+    int32_t quads_shift, m_shift;
 };
 int launch_combine(const CombineParams &p, int dtype, int softmax, void *stream); // returns hipError_t as int
 
