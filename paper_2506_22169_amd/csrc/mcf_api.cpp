@@ -390,7 +390,7 @@ int prepare(const mcf_call *call, Launch *o) {
     division_magic((uint32_t)k.divisor, &k.d_magic, &k.d_shift);
     division_magic((uint32_t)h_tiles, &k.h_magic, &k.h_shift);
     k.c1 = 1.0f; k.a_mode = 0;
-    k.k_chunks = (int32_t)(p->K / v->item_k);
+    k.k_chunks = (int32_t)(p->K / v->K);
     k.F = F; k.sf_b = sf[0]; k.sf_r = sf[1];
     if (p->out_dtype == MCF_F32) k.E = (void *)((uintptr_t)E | 1); // the kernels read bit 0 as "store fp32"
     if (softmax) {
@@ -419,7 +419,7 @@ int prepare(const mcf_call *call, Launch *o) {
             const int64_t seen = p->M + k.causal_off < p->N ? p->M + k.causal_off : p->N;
             n_tiles = seen > 0 ? (seen + tn - 1) / tn : 0;
         }
-        n_split = ranges_for(k.n_blocks, n_tiles, v->ksplit ? p->K / v->K + 1 : 1);
+        n_split = ranges_for(k.n_blocks, n_tiles, v->ksplit ? k.k_chunks + 1 : 1);
     }
     int64_t per = n_split < n_tiles ? (n_tiles + n_split - 1) / n_split : 1;
     n_split = n_tiles > 0 ? (n_tiles + per - 1) / per : 1;

@@ -114,13 +114,6 @@ constexpr int pick_stages(int K, int L, int mb, int rg, int ns, int nj, int budg
 // blocks can share the 160 KiB LDS of a compute unit (measured: a deeper ring that costs the
 // second resident block loses more than it gains).
 constexpr int kLdsRingBudget = 80 * 1024;
-// k depth of a ring item of a kernel with a k loop: the chunk T_K, or half of it where the LDS has room for two whole items only.
-// With two, a block waits for all of an item with nothing requested behind it; with four of half the depth three are in
-// flight.  Plain chains, (1,1,8,1), L = 64: 192 blocks of 12 x [256,896].[896,1216] 43.0 -> 39.3 us, 234 of 13 x [576,768].[768,1600] 52.9 ->
-// 47.4, 110 of 10 x [329,896].[896,1616] 62.4 -> 52.6; 40 blocks of a softmax chain, 4 x 300 x 1000, K = 512: 22.5 -> 23.9, so not those.
-constexpr int ksplit_depth(int TK, int L, int mb, int rg, int ns, int nj, bool softmax) {
-    return !softmax && pick_stages(TK, L, mb, rg, ns, nj, 2 * kLdsRingBudget, true) < 3 && pick_stages(TK / 2, L, mb, rg, ns, nj, 2 * kLdsRingBudget, true) >= 3 ? TK / 2 : TK;
-}
 // Softmax chains (and the plain chains named below) run a software pipeline over three consecutive n-tiles: in iteration i a wave
 // issues the MFMAs of GEMM 2 of tile i-1 and of GEMM 1 of tile i+1 with the softmax arithmetic of
 // tile i spread between them.  It reads B two tiles ahead of D, so the two have rings of their own: D of tiles i-1 and i

@@ -67,7 +67,7 @@ namespace mcf {
 template <typename T, int DT, int K, int L, bool KSPLIT>
 const Variant *group_table(int *count) {
 #define MCF_ROW(mb, rg, ns, nj, sm, bkc) \
-    {DT, K, L, mb, rg, ns, nj, sm, bkc, KSPLIT, 0, launcher_or_null<T, KSPLIT ? ksplit_depth(K, L, mb, rg, ns, nj, sm) : K, L, mb, rg, ns, nj, sm, bkc, KSPLIT>()},
+    {DT, K, L, mb, rg, ns, nj, sm, bkc, KSPLIT, 0, launcher_or_null<T, K, L, mb, rg, ns, nj, sm, bkc, KSPLIT>()},
 #define MCF_X(mb, rg, ns, nj)             \
     MCF_ROW(mb, rg, ns, nj, false, false) \
     MCF_ROW(mb, rg, ns, nj, false, true)  \

@@ -36,7 +36,7 @@ struct KParams {
     int32_t split_cols; // columns of an n range (N where n is not split), a multiple of T_N
     int32_t n_split;    // n ranges: the second dimension of the grid
     int32_t a_mode;     // 0: A as is, 1: -A (negative scale), 2: A := 0 (scale == 0)
-    int32_t k_chunks;   // kernels with a k loop: ring items of A and B to an n-tile (otherwise unused)
+    int32_t k_chunks;   // kernels with a k loop: K / T_K (otherwise unused)
     float c1;           // |scale| * log2(e) (softmax only)
     int32_t causal_off; // softmax only: row i sees the columns n <= i + causal_off (N - 1: no mask); no flag
                         // beside it: a branch on one splits the scalar loads of the arguments in two
@@ -94,7 +94,6 @@ struct Variant {
 // A variant in the registry (mcf_registry.cpp), with what the picker asks of every variant of a group on every call.
 struct Built : Variant {
     int32_t stages, lds_bytes, vgpr_est;
-    int32_t item_k;   // kernels with a k loop: k depth of a ring item, K or half of it; otherwise K
     bool fits;        // eq. (1) and no spills in loops: a candidate
     const Built *two; // three-GEMM chain: the variant of its two-GEMM part, which the model ranks (or nullptr)
 };

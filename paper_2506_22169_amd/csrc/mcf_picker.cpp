@@ -65,9 +65,8 @@ int vgpr_estimate(int K, int L, int mb, int rg, int ns, int nj, int softmax, int
 static int vgpr_cap(int waves) { return kVgprBudget / ((waves + 3) / 4); }
 
 void describe(Built *v) {
-    v->item_k = v->ksplit ? ksplit_depth(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0) : v->K;
-    v->stages = ring_stages(v->item_k, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0, v->P) * v->item_k / v->K; // in whole chunks
-    v->lds_bytes = block_lds_bytes(v->item_k, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0, v->P);
+    v->stages = ring_stages(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0, v->P);
+    v->lds_bytes = block_lds_bytes(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax != 0, v->ksplit != 0, v->P);
     v->vgpr_est = vgpr_estimate(v->K, v->L, v->mb, v->rg, v->ns, v->nj, v->softmax, v->ksplit);
     v->fits = v->lds_bytes <= kLdsBytesPerBlock && v->vgpr_est <= vgpr_cap(v->rg * v->ns) && v->scratch_bytes == 0;
     v->two = nullptr;

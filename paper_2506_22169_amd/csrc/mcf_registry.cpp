@@ -2,7 +2,6 @@
 #include <utility>
 #include <vector>
 
-#include "mcf_geometry.h"
 #include "mcf_internal.h"
 
 namespace mcf {
@@ -38,7 +37,7 @@ static void add(std::vector<Built> *t, const Variant *(*group)(int *)) {
         b.vgprs = -1;
         b.scratch_bytes = 0;
         for (const Resources &r : kResources)
-            if (r.dtype == b.dtype && r.K == (b.ksplit ? ksplit_depth(b.K, b.L, b.mb, b.rg, b.ns, b.nj, b.softmax != 0) : b.K) && r.L == b.L && r.mb == b.mb && r.rg == b.rg && r.ns == b.ns &&
+            if (r.dtype == b.dtype && r.K == b.K && r.L == b.L && r.mb == b.mb && r.rg == b.rg && r.ns == b.ns &&
                 r.nj == b.nj && r.softmax == b.softmax && r.b_kcontig == b.b_kcontig && r.ksplit == b.ksplit && r.P == b.P) {
                 b.vgprs = r.vgprs;
                 // registers parked in scratch across the n loop (stored before it, fetched after it)
