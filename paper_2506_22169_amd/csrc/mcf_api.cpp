@@ -171,20 +171,24 @@ static int64_t visible_columns(int64_t M, int64_t N, int64_t tm, int64_t off, in
     return rising * off + tm * (rising * (none + 1 + all) / 2) + (tiles - all) * N;
 }
 
-// Time of a softmax chain in us from how many blocks a compute unit holds, which the model's estimate does not see: its units
+// Time of a chain in us from how many blocks a compute unit holds, which the model's estimate does not see: its units
 // take their blocks in rounds of as many as LDS and registers let them hold, a round lasts as long as the
-// matrix and vector work of its blocks at the rate that their waves reach together, and ends with a fill and a drain.
-// Under a mask (off: its offset) a call takes as long as its longest block at least.  Constants fitted to 419 calls drawn from the
-// ranges of the chains with 129 blocks or more, nine arrangements each.
-static double softmax_time(const mcf_problem *p, const Built *v, double cost, const int64_t *off) {
-    static const double kRate[4] = {0.72, 1.0, 1.08, 1.08}; // of 1 to 4 waves a SIMD, against two
+// matrix and vector work of its blocks at the rate that their waves reach together, or as its n-tiles take whatever their width,
+// and ends with a fill and a drain; and no call is faster than its bytes.
+// Under a mask (off: its offset) a call takes as long as its longest block at least.  Constants fitted to calls drawn from the
+// ranges of the chains with 129 blocks or more: 419 softmax chains in nine arrangements, 312 plain ones in fourteen and T_L.
+struct TimeFit {
+    double mac, column, ends, first, tile, bytes_per_us;
+    double rate[4]; // of 1 to 4 waves a SIMD, against two
+};
+static double chain_time(const TimeFit &fit, const mcf_problem *p, const Built *v, double cost, const int64_t *off) {
     const int waves = v->rg * v->ns, simd = waves > 4 ? waves / 4 : 1;
     const int tm = 32 * v->mb * v->rg, tn = 32 * v->ns * v->nj;
     int held = kVgprBudget / ((v->vgprs + 7) / 8 * 8) / simd;
     held = held < kLdsBytesPerBlock / v->lds_bytes ? held : kLdsBytesPerBlock / v->lds_bytes;
     if (held < 1) held = 1;
-    const int64_t m_tiles = (p->M + tm - 1) / tm, blocks = p->batch * m_tiles;
-    const double padded = (double)((p->N + tn - 1) / tn * tn);
+    const int64_t m_tiles = (p->M + tm - 1) / tm, n_tiles = (p->N + tn - 1) / tn, blocks = p->batch * m_tiles * (p->L / v->L);
+    const double padded = (double)(n_tiles * tn);
     double mean = padded, longest = padded;
     if (off) {
         int64_t last;
@@ -192,62 +196,85 @@ static double softmax_time(const mcf_problem *p, const Built *v, double cost, co
         mean = mean < padded ? mean : padded;
         longest = (double)((last + tn - 1) / tn * tn);
     }
-    const double column = tm * (0.325 * (double)(p->K + p->L) + 20.1) * cost * 1e-6, ends = 4.3;
-    const auto rate = [&](int64_t r) { return kRate[r * simd < 4 ? r * simd - 1 : 3]; };
+    const double column = tm * (fit.mac * (double)(p->K + v->L) + fit.column) * cost * 1e-6;
+    const auto round = [&](int64_t blocks_a_unit, double columns) {
+        const double work = (double)blocks_a_unit * column * columns / fit.rate[blocks_a_unit * simd < 4 ? blocks_a_unit * simd - 1 : 3];
+        const double tiles = fit.tile * (double)n_tiles;
+        return (work > tiles ? work : tiles) + fit.ends;
+    };
     const int64_t slots = (int64_t)kComputeUnits * held, full = blocks / slots, rest = blocks - full * slots;
-    const int64_t together = rest > 0 ? (rest + kComputeUnits - 1) / kComputeUnits : 0;
-    double t = (double)full * ((double)held * column * mean / rate(held) + ends);
-    if (together > 0) t += (double)together * column * mean / rate(together) + ends;
+    double t = (double)full * round(held, mean);
+    if (rest > 0) t += round((rest + kComputeUnits - 1) / kComputeUnits, mean);
     if (longest > mean) {
-        int64_t beside = blocks <= kComputeUnits ? 1 : (blocks + kComputeUnits - 1) / kComputeUnits;
-        beside = beside < held ? beside : held;
-        const double alone = (double)beside * column * longest / rate(beside) + ends;
+        int64_t beside = (blocks + kComputeUnits - 1) / kComputeUnits;
+        const double alone = round(beside < held ? beside : held, longest);
         t = blocks > slots && t > alone ? t : alone;
     }
-    return t + 1.0;
+    if (fit.bytes_per_us > 0.) {
+        const double bytes = 2.0 * (double)p->batch * ((double)p->M * p->K + (double)p->K * p->N + (double)p->N * p->L + (double)p->M * p->L * (p->out_dtype == MCF_F32 ? 2 : 1));
+        if (t < bytes / fit.bytes_per_us) t = bytes / fit.bytes_per_us;
+    }
+    return t + fit.first;
 }
-// A softmax chain that n is not split for (more blocks than half the compute units): another arrangement of whole L where that is a tenth faster at
-// least by softmax_time.  279 calls without a mask that were not in the fit's first half: 0.42 to 1.08 of the time, 0.96 in the mean;
-// 140 with one: 0.64 to 1.10, 0.98.
-static void settle_softmax(const mcf_problem *p, int b_kcontig, const int64_t *off, mcf_tiles *t) {
-    static const struct { int rg, ns, nj; double cost; } kCost[] = { // of a column of an m-tile, against each other
-        {8, 1, 2, 0.88}, {8, 1, 1, 1.00}, {4, 1, 2, 0.92}, {4, 1, 1, 1.01}, {4, 2, 2, 0.98}, {4, 2, 1, 1.12}, {2, 2, 2, 1.27}, {2, 2, 1, 1.22}, {1, 4, 1, 1.82}};
-    if (p->N <= 0 || t->tl != p->L || 2 * t->blocks <= kComputeUnits) return;
-    const Group *g = resolve_group(p->in_dtype, p->K, p->L);
-    if (!g || g->ksplit) return;
+// A call that n is not split for (more blocks than half the compute units): another arrangement where that is a tenth faster at
+// least by chain_time (softmax chains: of whole L); a fifth where the rules of settle_tiles have acted, whose arrangements it underrates (128 x
+// [2881,128].[128,976].[976,128]: 1.19 by chain_time, 1.10 measured).  Calls that were not in the fit's first half, against the pick: 279 softmax chains 0.42
+// to 1.08 of the time (0.96 in the mean), 140 under a mask 0.64 to 1.10 (0.98), 129 plain ones 0.51 to 1.00 (0.93).
+static void settle_many(const mcf_problem *p, int softmax, int b_kcontig, const int64_t *off, bool settled, mcf_tiles *t) {
+    struct Cost { int mb, rg, ns, nj; double cost; }; // of a column of an m-tile, against each other
+    static const Cost kSoftmax[] = {{1, 8, 1, 2, 0.88}, {1, 8, 1, 1, 1.00}, {1, 4, 1, 2, 0.92}, {1, 4, 1, 1, 1.01}, {1, 4, 2, 2, 0.98},
+                                    {1, 4, 2, 1, 1.12}, {1, 2, 2, 2, 1.27}, {1, 2, 2, 1, 1.22}, {1, 1, 4, 1, 1.82}};
+    static const Cost kPlain[] = {{1, 8, 1, 2, 0.65}, {1, 8, 1, 1, 0.72}, {1, 4, 1, 2, 0.83}, {1, 4, 1, 1, 1.08}, {1, 4, 2, 2, 0.70},
+                                  {1, 4, 2, 1, 0.76}, {1, 2, 2, 2, 0.81}, {1, 2, 2, 1, 0.91}, {1, 1, 4, 1, 1.17}, {2, 4, 2, 2, 0.59},
+                                  {2, 4, 2, 1, 0.66}, {2, 2, 4, 1, 0.69}, {2, 2, 2, 1, 0.72}, {4, 2, 4, 1, 0.57}};
+    static const TimeFit kSoftmaxFit = {0.325, 20.1, 4.3, 1.0, 0., 0., {0.72, 1.0, 1.08, 1.08}};
+    static const TimeFit kPlainFit = {0.519, 1.86, 3.16, 1.5, 0.356, 2.92e6, {0.71, 1.0, 0.95, 1.11}};
+    const TimeFit &fit = softmax ? kSoftmaxFit : kPlainFit;
+    const Cost *costs = softmax ? kSoftmax : kPlain;
+    const int n_costs = softmax ? (int)(sizeof(kSoftmax) / sizeof(Cost)) : (int)(sizeof(kPlain) / sizeof(Cost));
+    if (p->N <= 0 || 2 * t->blocks <= kComputeUnits || t->tk < p->K || (softmax && t->tl != p->L)) return;
+    // (K, L of 64 and fewer, three blocks a unit and more: the softmax fit is least sure of these, so a call does not leave them)
+    if (softmax && t->mb == 1 && t->rg == 2 && t->ns == 2 && t->nj == 1 && p->K <= 64) return;
     const Built *best = nullptr;
     double now = 0., least = 0.;
-    for (const Built *v : g->of[1][b_kcontig]) {
-        if (v->mb != 1 || !v->fits || v->vgprs <= 0) continue;
-        for (const auto &c : kCost) {
-            if (v->rg != c.rg || v->ns != c.ns || v->nj != c.nj) continue;
-            const bool same = t->mb == 1 && t->rg == c.rg && t->ns == c.ns && t->nj == c.nj;
-            // (three blocks a unit and more: the fit is least sure of these, so a call does not leave them)
-            if (same && c.rg == 2 && c.nj == 1 && p->K <= 64) return;
-            const double us = softmax_time(p, v, c.cost, off);
-            if (same) now = us;
-            const int64_t blocks = p->batch * ((p->M + 32 * c.rg - 1) / (32 * c.rg));
-            if (2 * blocks > kComputeUnits && (!best || us < least)) { best = v; least = us; }
+    for (int parts = 1; parts == 1 || (!softmax && p->L / parts >= 32); ++parts) {
+        if (p->L % parts != 0) continue;
+        const Group *g = resolve_group(p->in_dtype, p->K, p->L / parts);
+        if (!g || g->ksplit) continue;
+        for (const Built *v : g->of[softmax][b_kcontig]) {
+            if (!v->fits || v->vgprs <= 0) continue;
+            for (int i = 0; i < n_costs; ++i) {
+                const Cost &c = costs[i];
+                if (v->mb != c.mb || v->rg != c.rg || v->ns != c.ns || v->nj != c.nj) continue;
+                const double us = chain_time(fit, p, v, c.cost, off);
+                if (t->mb == c.mb && t->rg == c.rg && t->ns == c.ns && t->nj == c.nj && t->tl == v->L) now = us;
+                const int64_t tm = 32ll * c.mb * c.rg, blocks = p->batch * ((p->M + tm - 1) / tm) * parts;
+                // (plain chains: not to m-tiles of 32 and 64 rows in four waves, of which the fit is least sure: 108 x [607,32].[32,608].[608,32] 12.6
+                // -> 13.7 us, 2 x [2152,128].[128,3808].[3808,128] 32.4 -> 33.8)
+                if (!softmax && c.mb * c.rg <= 2 && c.rg * c.ns == 4) continue;
+                if (2 * blocks > kComputeUnits && (!best || us < least)) { best = v; least = us; }
+            }
         }
     }
-    if (best && now > 0. && 1.1 * least < now) eval_model(p, best, t);
+    if (best && now > 0. && (settled ? 1.2 : 1.1) * least < now) eval_model(p, best, t);
 }
-static void settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *t) {
-    if (t->tk < p->K) return; // a k loop: measured as it is
+static bool settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *t) {
+    if (t->tk < p->K) return false; // a k loop: measured as it is
     mcf_tiles w;
     memset(&w, 0, sizeof(w));
     w.mb = t->mb; w.rg = t->rg; w.ns = t->ns; w.tl = t->tl;
     if (t->mb == 1 && t->rg == 4 && t->ns == 1 && t->nj == 1 && (!softmax || t->blocks <= kComputeUnits)) {
         w.ns = 2;
         for (w.nj = 2; w.nj >= 1; --w.nj)
-            if (built(p, softmax, b_kcontig, t->tn, &w)) { *t = w; return; }
+            if (built(p, softmax, b_kcontig, t->tn, &w)) { *t = w; return true; }
     } else if (!softmax && t->mb == 1 && t->rg == 8 && t->ns == 1 && t->nj == 1 && t->blocks <= kComputeUnits) {
         w.nj = 2;
-        if (eval_tiles(p, softmax, b_kcontig, &w) == MCF_OK && 8 * padding_of(p->N, w.tn) <= p->N) *t = w;
+        if (eval_tiles(p, softmax, b_kcontig, &w) == MCF_OK && 8 * padding_of(p->N, w.tn) <= p->N) { *t = w; return true; }
     } else if (softmax && t->rg * t->ns == 4 && t->mb == 1 && t->nj == 2 && pitch_elems(t->tk) != t->tk) {
         w.nj = 1;
-        if (built(p, softmax, b_kcontig, t->tn, &w)) *t = w;
+        if (built(p, softmax, b_kcontig, t->tn, &w)) { *t = w; return true; }
     }
+    return false;
 }
 
 // Ranges of n of a call that may have a workspace and leaves the choice to the library.  They pay where
@@ -345,10 +372,10 @@ int prepare(const mcf_call *call, Launch *o) {
     } else {
         st = ch3 ? pick3(p, softmax, lay.b_kcontig, P, &chosen) : pick_tiles(p, softmax, lay.b_kcontig, &chosen);
         if (st != MCF_OK) return st;
-        if (!ch3) settle_tiles(p, softmax, lay.b_kcontig, &chosen);
-        if (!ch3 && softmax) {
+        if (!ch3) {
+            const bool settled = settle_tiles(p, softmax, lay.b_kcontig, &chosen);
             const int64_t off = call->causal_offset > p->N ? p->N : call->causal_offset < -p->M ? -p->M : call->causal_offset;
-            settle_softmax(p, lay.b_kcontig, call->causal ? &off : nullptr, &chosen);
+            settle_many(p, softmax, lay.b_kcontig, call->causal ? &off : nullptr, settled, &chosen);
         }
     }
     const int64_t tl = ch3 ? p->L : (chosen.tl > 0 ? chosen.tl : p->L);

@@ -1,4 +1,5 @@
-"""What a softmax call without tiles runs where the model's pick leaves blocks waiting that another arrangement would hold at once (host only)."""
+"""What a call without tiles runs where the model's pick leaves blocks waiting that another arrangement would hold at once, and which
+calls of wide n-tiles are split (host only)."""
 import random
 
 import pytest
@@ -50,3 +51,15 @@ def test_what_is_left_alone():
         given = list_candidates(p, True)[0]
         assert _ran(b, M, K, N, K, causal, off=off, tiles=(given.mb, given.rg, given.ns, given.nj, given.tl))[0][:4] == (given.mb, given.rg, given.ns, given.nj)
     assert moved > 50
+
+
+@pytest.mark.parametrize("call,tm", [
+    ((51, 715, 32, 744, 32), 256),                    # 1173 blocks of 32 rows: 15.3 -> 8.2 - 8.8 us
+    ((92, 3264, 64, 128, 128), None),
+    ((64, 512, 64, 512, 64), 128),
+    ((16, 4096, 32, 1024, 32), 256),
+])
+def test_arrangement_of_many_plain_blocks(call, tm):
+    p = make_problem(*call, "bf16")
+    t, ranges = call_tiles(p, False)
+    assert ranges == 1 and t.scratch_bytes == 0 and t.blocks > 128 and tm in (t.tm, None)
