@@ -289,14 +289,21 @@ static bool settle_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_t
 // (10 to 18 items saved) five take 1.00 to 1.17 of their time, K = L of 32 and 64, the others less.  32 rows against 8192 keys of 128:
 // 92 -> 33 us; 1 x [639,1024].[1024,664].[664,128]: 100 -> 19 us.  Chains of three are not split unasked: each range would
 // round its part of E before the third GEMM.
-static int64_t ranges_for(int64_t blocks, int64_t n_tiles, int64_t items_per_tile) {
+// An n-tile of more than 28 KiB of B and D counts by its bytes (tile_bytes): 3 x 300 x 1500, K = L = 128, twelve of 48 KiB: 15.4 unsplit, 10.7 us in four
+// ranges; 2 x [500,160].[160,1400].[1400,160], eleven of 80 KiB: 16.7 and 12.2; 1 x [132,160].[160,816].[816,160], seven: 12.5 and 11.0 in three.
+// Where fewer than ten n-tiles are saved, the results of the ranges (range_bytes each), written and read again, count as well: 2 x [1241,192].[192,616].[616,192], 9.8 MB in
+// five: 13.5 and 15.6; 2 x 3983 x 399, K = L = 256, 33 MB in four: 20.1 and 27.5.
+static int64_t ranges_for(int64_t blocks, int64_t n_tiles, int64_t items_per_tile, int64_t tile_bytes, int64_t range_bytes) {
     if (blocks <= 0 || 2 * blocks > kComputeUnits) return 1;
     const int64_t least = items_per_tile >= 2 ? 1 : 2; // n-tiles of a range
     int64_t s = kComputeUnits / blocks;
     if (s > n_tiles / least) s = n_tiles / least;
     if (s < 2) return 1;
     const int64_t per = (n_tiles + s - 1) / s;
-    return (n_tiles - per) * items_per_tile >= (items_per_tile >= 2 ? 8 : 10) ? s : 1;
+    if (items_per_tile >= 2) return (n_tiles - per) * items_per_tile >= 8 ? s : 1;
+    const int64_t unit = 28 * 1024;
+    if (n_tiles - per >= 10 || tile_bytes <= unit) return n_tiles - per >= 10 ? s : 1;
+    return (n_tiles - per) * tile_bytes >= 10 * unit + s * range_bytes / 40 ? s : 1;
 }
 
 // Longest first pays where blocks wait for a compute unit and differ in length; otherwise the order that keeps a batch
@@ -446,7 +453,7 @@ int prepare(const mcf_call *call, Launch *o) {
             const int64_t seen = p->M + k.causal_off < p->N ? p->M + k.causal_off : p->N;
             n_tiles = seen > 0 ? (seen + tn - 1) / tn : 0;
         }
-        n_split = ranges_for(k.n_blocks, n_tiles, v->ksplit ? k.k_chunks + 1 : 1);
+        n_split = ranges_for(k.n_blocks, n_tiles, v->ksplit ? k.k_chunks + 1 : 1, stage_bytes(v->K, v->L, (int)tn), p->batch * p->M * (p->L + 4) * 4);
     }
     int64_t per = n_split < n_tiles ? (n_tiles + n_split - 1) / n_split : 1;
     n_split = n_tiles > 0 ? (n_tiles + per - 1) / per : 1;

@@ -63,3 +63,16 @@ def test_arrangement_of_many_plain_blocks(call, tm):
     p = make_problem(*call, "bf16")
     t, ranges = call_tiles(p, False)
     assert ranges == 1 and t.scratch_bytes == 0 and t.blocks > 128 and tm in (t.tm, None)
+
+
+@pytest.mark.parametrize("call,kind,ranges", [
+    ((3, 300, 128, 1500, 128), 1, 4),      # twelve n-tiles of 48 KiB
+    ((2, 500, 160, 1400, 160), 0, 4),      # eleven of 80 KiB
+    ((1, 132, 160, 816, 160), 0, 3),
+    ((2, 1241, 192, 616, 192), 0, 1),      # ten of 48 KiB, but 1.9 MB of results a range
+    ((20, 192, 64, 2624, 64), 1, 2),       # ten n-tiles saved: whatever the results take
+    ((4, 128, 64, 512, 64), 1, 1),
+])
+def test_ranges_of_wide_n_tiles(call, kind, ranges):
+    b, M, K, N, L = call
+    assert call_tiles(make_problem(*call, "f16", b_stride=(N * K, 1, K) if kind else None), bool(kind))[1] == ranges
