@@ -120,8 +120,9 @@ int mcf_list_candidates(const mcf_problem *problem, int softmax, mcf_tiles *out,
 
 /*
  * E = (A . B) . D   (Sec. III-A).  Device pointers; tiles_or_null == NULL means
- * mcf_pick_tiles() decides (where it takes four waves with an n-tile of 32 columns, or a softmax chain of four waves
- * with two slices each, the rows stay and the waves are arranged as measured faster: mcf_call_tiles says how), otherwise only its mb, rg, ns, nj and
+ * mcf_pick_tiles() decides (where it takes four waves with an n-tile of 32 columns, eight across m with one, or a softmax chain of four waves
+ * with two slices each, the rows stay and the waves are arranged as measured faster; with more than 128 blocks another
+ * arrangement may run whose blocks a compute unit holds better: mcf_call_tiles says which), otherwise only its mb, rg, ns, nj and
  * tl (0 = L) fields are read.  hip_stream is a
  * hipStream_t (NULL = the default stream).  E must not overlap A, B or D.  batch, M or L of
  * zero is a no-op; N == 0 writes zeros.

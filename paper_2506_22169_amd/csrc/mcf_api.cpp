@@ -148,9 +148,7 @@ static int pick3(const mcf_problem *p, int softmax, int b_kcontig, int64_t P, mc
 //    14.7 -> 13.4 and with 128 22.4 -> 21.5; 80 x [500,64].[64,520].[520,128] 15.4 -> 13.9 us.  Not with more blocks than compute
 //    units, where the registers of one slice let two blocks share one: 70 x [2707,96].[96,2464].[2464,96] 173 against 188 us.
 //  * Among equal estimates it takes the wider n-tile.  Softmax kernels of four waves whose rows are padded to the
-//    LDS pitch (K = 80, 96, 160, 192) spill scalar registers with two slices a wave, and run better with one: the calls
-//    of a sweep that were picked so take 0.80 to 1.02 of their time; causal 40 x 333 x 1357, K = L = 80: 23 -> 20.5 us.
-//    With K = 128 and 256 the two are level (0.97 to 1.09).
+//    LDS pitch (K = 80) run better with one slice a wave: 40 x 333 x 1357, causal: 19.9 us with two, 18.7 with one.
 // Chains of three GEMMs keep the pick: a wave that holds part of a row's n range rounds its part of E to 16 bits before the
 // third GEMM, which is the caller's or the model's choice and not one to be made behind it (parts that cancel, or that
 // leave fp16, are lost).
