@@ -6,9 +6,11 @@
 //     E[i,:] = sum_s P_s[i,:]                                                   (plain)
 //
 // Bound by being a launch: what its blocks wait for one after the other.  So a lane finds its row and its four columns with
-// constants of the host in place of 64-bit divisions, and requests the logarithms and the values of up to four ranges at once,
-// further ranges in fours.  A wave reads whole row segments.
+// constants of the host in place of 64-bit divisions, and requests the logarithms and the values of up to four ranges (G) at once,
+// of eight where there are more than four.  A wave reads whole row segments.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "mcf_internal.h"
 
@@ -20,14 +22,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // n / d of division_magic's constants
 __device__ __forceinline__ uint32_t quotient(uint32_t n, uint32_t magic, int shift) { return magic ? __umulhi(n, magic) >> shift : n; }
 
-template <typename T, bool SOFTMAX>
+template <typename T, bool SOFTMAX, int G>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
     const uint32_t r = quotient(threadIdx.x, p.quads_magic, p.quads_shift); // row of the block
     const int col = (int)(threadIdx.x - r * (uint32_t)(p.L >> 2)) * 4;
     const uint32_t row = blockIdx.x * (uint32_t)p.block_rows + r; // over all batches
     if (r >= (uint32_t)p.block_rows || row >= (uint32_t)p.rows) return;
     const float *src = p.part + (int64_t)row * p.pitch;
-    constexpr int G = 4;
     f32x4 v[G];
     float lse[G];
     const auto fetch = [&](int s0, bool values) __attribute__((always_inline)) { // (beyond the last range: the last once more, unused)
@@ -38,7 +39,12 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
             lse[g] = SOFTMAX ? q[p.L] : 0.f;
         }
         // (all of them here: left alone, the values are not requested before the logarithms have come)
-        if (values) asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(lse[0]), "+v"(lse[1]), "+v"(lse[2]), "+v"(lse[3]));
+        if (values) {
+            if constexpr (G == 4) asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(lse[0]), "+v"(lse[1]), "+v"(lse[2]), "+v"(lse[3]));
+            else
+                asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]), "+v"(lse[0]), "+v"(lse[1]),
+                             "+v"(lse[2]), "+v"(lse[3]), "+v"(lse[4]), "+v"(lse[5]), "+v"(lse[6]), "+v"(lse[7]));
+        }
     };
     float m = -INFINITY;
     if (SOFTMAX) {
@@ -90,13 +96,18 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
 int launch_combine(const CombineParams &p, int dtype, int softmax, void *stream) {
     const dim3 grid((unsigned)((p.rows + p.block_rows - 1) / p.block_rows)), block(256);
     hipStream_t st = (hipStream_t)stream;
-    if (dtype == MCF_F16) {
-        if (softmax) hipLaunchKernelGGL((combine_kernel<_Float16, true>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((combine_kernel<_Float16, false>), grid, block, 0, st, p);
-    } else {
-        if (softmax) hipLaunchKernelGGL((combine_kernel<__bf16, true>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((combine_kernel<__bf16, false>), grid, block, 0, st, p);
-    }
+    const auto run = [&](auto more) {
+        constexpr int G = decltype(more)::value ? 8 : 4;
+        if (dtype == MCF_F16) {
+            if (softmax) hipLaunchKernelGGL((combine_kernel<_Float16, true, G>), grid, block, 0, st, p);
+            else hipLaunchKernelGGL((combine_kernel<_Float16, false, G>), grid, block, 0, st, p);
+        } else {
+            if (softmax) hipLaunchKernelGGL((combine_kernel<__bf16, true, G>), grid, block, 0, st, p);
+            else hipLaunchKernelGGL((combine_kernel<__bf16, false, G>), grid, block, 0, st, p);
+        }
+    };
+    if (p.n_split > 4) run(std::true_type{});
+    else run(std::false_type{});
     return (int)hipGetLastError();
 }
 
