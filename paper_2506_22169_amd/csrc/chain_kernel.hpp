@@ -173,7 +173,7 @@ void chain_kernel(const KParams p) {
     constexpr int S = ring_stages(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD); // depth of the LDS ring
     // softmax chains: software pipeline over three consecutive n-tiles (see the loop)
     constexpr bool PIPE = pipelined(KD, LD, MB, RG, NS, NJ, SOFTMAX, KSPLIT, PD);
-        constexpr int RBA = 2 * pitch_elems(KD);                // row bytes of the A tile (rows m)
+    constexpr int RBA = 2 * pitch_elems(KD);                // row bytes of the A tile (rows m)
     constexpr int RBB = BKC ? 2 * pitch_elems(KD) : 2 * TN; // row bytes of the B tile (rows n / rows k)
     constexpr int RBD = 2 * pitch_elems(LD);                // row bytes of the D tile (rows n)
     constexpr int B_BYTES = b_tile_bytes(KD, TN);
@@ -265,7 +265,10 @@ void chain_kernel(const KParams p) {
     // Wave-load j of a stage covers LDS bytes [1024 j, 1024 j + 1024): 16-byte slot 64 j + lane.
     // Slot -> (row, stored chunk); the global source is the logical chunk = stored ^ swizzle.
     // With clamp (the ragged last tile), rows / columns beyond N are redirected to valid memory
-    // (their contribution is masked in registers), so no load ever leaves the tensors.
+    // (their contribution is masked in registers), so no load ever leaves the tensors.  A row of D beyond N meets a P or C
+    // of zero, and 0 x Inf is NaN where row N - 1, which stands in for it, holds an infinity: so a slice of
+    // 32 columns (with a k loop: all slices of a wave) that has none of the tile's stays out of GEMM 2 (phase_g2), and pipelined kernels, whose GEMM 2 has no place for a branch, clear
+    // the rows where they have landed (clear_beyond).
     auto bd_offset = [&](int u, int nt0, bool clamp) __attribute__((always_inline)) -> unsigned {
         int j = wave + u * W;
         j = j < CT ? j : CT - 1;
@@ -367,6 +370,18 @@ void chain_kernel(const KParams p) {
     };
     using Yes = std::true_type;
     using No = std::false_type;
+    // Rows of D beyond N of the ragged tile t become zeros.  Every wave clears what it has loaded itself, between its wait
+    // for it and the barrier that hands the tile to the others: no barrier of its own.
+    auto clear_beyond = [&](int t, unsigned d_slot) __attribute__((always_inline)) {
+        int l; // the lane, formed here: no register holds it through the loop
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+#pragma unroll 1
+        for (int j = wave; j < CT; j += W) {
+            const int slot = 64 * (j - CB) + l;
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            if (j >= CB && t * TN + slot / (RBD / 16) >= N) *(lds_u32x4 *)(smem + d_slot + 16 * slot) = zero;
+        }
+    };
 
     // ---- kernels with a k loop: the items that travel through the ring ----------------------
     // Item r of n-tile t: r < KC is the A chunk + B chunk of k step r ([A | B] in the slot),
@@ -719,10 +734,11 @@ void chain_kernel(const KParams p) {
         }
     };
     // ---- C_E: E^T[h][m] += sum_n D^T[h][n] P^T[n][m] ---------------------------------------
-    auto phase_g2 = [&]() __attribute__((always_inline)) { // after phase_g2_prefetch of the same tile
+    auto phase_g2 = [&](int n0) __attribute__((always_inline)) { // after phase_g2_prefetch of the same tile
 #pragma unroll
         for (int t = 0; t < T2; ++t) {
             const int j = t / (2 * HB), hb = (t / 2) % HB, qp = t % 2;
+            if (!KSPLIT && j > 0 && t % (2 * HB) == 0 && n0 + 32 * j >= N) break; // (a slice without a column, see bd_offset; a k loop: spills)
             if (t + PF < T2) dop[t + PF] = load_d((t + PF) / (2 * HB), ((t + PF) / 2) % HB, (t + PF) % 2);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
@@ -843,7 +859,7 @@ void chain_kernel(const KParams p) {
             if (n0 < N) { // (a wave with no column of a ragged tile stays out: its P = 0 would meet the rows that D's row N - 1 stands in for, and 0 x Inf is NaN)
                 phase_g2_prefetch(stage_c * STAGE);
                 phase_sm(n0);
-                phase_g2();
+                phase_g2(n0);
             }
             stage_c = next_stage(stage_c);
         }
@@ -1110,7 +1126,8 @@ void chain_kernel(const KParams p) {
             }
         };
         // top of iteration i: B of tile i+1 (if any) and D of tile i-1 have landed; the next of both are requested
-        auto landed = [&](int i) __attribute__((always_inline)) {
+        // (lastc: i may be the last tile; its D, unless requested in this very iteration, has landed as well)
+        auto landed = [&](auto lastc, int i) __attribute__((always_inline)) {
             // what has been requested ahead may still be in flight (before iteration 0: the prologue's last B and its D tiles; before
             // iteration 1 no D has been requested but those)
             if (R.ahead > 0 && i + 1 + R.ahead < n_iters) {
@@ -1120,10 +1137,13 @@ void chain_kernel(const KParams p) {
             } else {
                 wait_vm<0>();
             }
+            if constexpr (decltype(lastc)::value) {
+                if (i >= n_full && (R.ahead > 0 || i < R.d_first)) clear_beyond(i, d_at[1]);
+            }
             __syncthreads(); // what has landed is complete for every wave; the slots requested next are free
         };
-        auto top = [&](int i) __attribute__((always_inline)) {
-            landed(i);
+        auto top = [&](auto lastc, int i) __attribute__((always_inline)) {
+            landed(lastc, i);
             if (i + R.ahead >= R.d_first) request(Yes{}, Yes{}, i + 2 + R.ahead, b_at[(2 + R.ahead) % SB], i + R.ahead, d_at[1 + R.ahead]);
             else request(Yes{}, No{}, i + 2 + R.ahead, b_at[(2 + R.ahead) % SB], 0, 0); // (its D came with the prologue)
         };
@@ -1135,7 +1155,7 @@ void chain_kernel(const KParams p) {
             __syncthreads();
             g1_only(std::integral_constant<int, 0>{}, b_at[0]);
             // iteration 0: no tile before it
-            top(0);
+            top(Yes{}, 0);
             if (last >= 1) g1_only(std::integral_constant<int, 1>{}, b_at[1]);
             using Lazy = std::integral_constant<int, LAZY>;
             using Buf0 = std::integral_constant<int, 0>;
@@ -1170,7 +1190,7 @@ void chain_kernel(const KParams p) {
                 };
                 bool some_blind = last > 1 && blind();
                 auto one = [&](auto curc, int t) __attribute__((always_inline)) {
-                    top(t);
+                    top(No{}, t);
                     steady(curc, Stands{}, t);
                     if (__builtin_expect(some_blind || outgrown(), 0)) {
                         g1_only(curc, b_at[0]);
@@ -1186,16 +1206,16 @@ void chain_kernel(const KParams p) {
                 }
             } else {
                 for (; i + 1 <= last - 1; i += 2) {
-                    top(i);
+                    top(No{}, i);
                     steady(Buf1{}, Lazy{}, i);
                     turn();
-                    top(i + 1);
+                    top(No{}, i + 1);
                     steady(Buf0{}, Lazy{}, i + 1);
                     turn();
                 }
             }
             if (i <= last - 1) {
-                top(i);
+                top(No{}, i);
                 steady(Buf1{}, Lazy{}, i);
                 turn();
             }
@@ -1209,13 +1229,14 @@ void chain_kernel(const KParams p) {
 #pragma unroll
                         for (int mb = 0; mb < MB; ++mb) cc[0][j][mb] = cc[1][j][mb];
                 }
-                top(last);
+                top(Yes{}, last);
                 g2_only(d_at[0]);
                 softmax_only(Buf0{}, Lazy{}, last);
             }
             // GEMM 2 of the last tile
             if (R.ahead == 0 && last >= R.d_first) { // (whose D was requested at the top of this iteration)
                 wait_vm<0>();
+                if (last >= n_full) clear_beyond(last, last > 0 ? d_at[1] : d_slot(0));
                 __syncthreads();
             }
             g2_only(last > 0 ? d_at[1] : d_slot(0));
@@ -1239,7 +1260,7 @@ void chain_kernel(const KParams p) {
                 phase_g1(st);
                 phase_g2_prefetch(st);
                 phase_sm(n0);
-                phase_g2();
+                phase_g2(n0);
             }
             stage_c = stage_c + 1 == S ? 0 : stage_c + 1;
         }
@@ -1274,7 +1295,7 @@ void chain_kernel(const KParams p) {
                     phase_g1(st);
                     phase_g2_prefetch(st);
                     phase_sm(n0);
-                    phase_g2();
+                    phase_g2(n0);
                 }
             }
         } else {
@@ -1283,7 +1304,7 @@ void chain_kernel(const KParams p) {
                 if (n0 < N) {
                     phase_g2_prefetch((t % S) * STAGE);
                     phase_sm(n0);
-                    phase_g2();
+                    phase_g2(n0);
                 }
             };
             if (n_iters > 0) { // (no n-tile, as where a mask hides a whole range: the other group meets no barrier either)
