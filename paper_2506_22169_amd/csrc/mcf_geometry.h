@@ -162,7 +162,10 @@ constexpr int with_f_tile(int below, int L, int P, int mb, int rg, int ns) {
 // over.  Asked for when two blocks fit the LDS and the registers hold what a lane must: the E
 // accumulators, two C^T tiles, P packed to 16 bit, the A operands, and 40 for the LDS operands in flight, addresses and the
 // softmax state, more with a second row set (16) or slice (20).  (Asked for with fewer, they spill: K = 128, L = 64, (1,8,1,1).)
+// K and L of 32, whose operands are few, need 56 beside the E, C^T and P tiles, however many those are: with two blocks (1,4,1,4)
+// takes 10.8 us for 96 x 512 x 512 and 32.6 for 32 x 2048 x 2048, with one 16.8 and 47.6; (2,2,2,2) 11.4 and 31.7, 17.4 and 45.6.
 constexpr int pipe_needs(int K, int L, int mb, int nj) {
+    if (K <= 32 && L <= 32) return mb * 16 + 2 * nj * mb * 16 + nj * mb * 8 + 56;
     return mb * h_blocks(L) * 16 + 2 * nj * mb * 16 + nj * mb * 8 + mb * (K / 16) * 4 + 4 + 16 * mb + 20 * nj;
 }
 constexpr int pipe_lds_least(int K, int L, int mb, int rg, int ns, int nj, int P, bool stands) {
@@ -184,6 +187,9 @@ constexpr bool reference_stands(int K, int L, int mb, int rg, int ns, int nj, bo
 constexpr int pipe_waves_per_simd(int K, int L, int mb, int rg, int ns, int nj, bool softmax, int P) {
     // (K = L = 32 in blocks of four waves: five blocks; 95 to 97 registers when not told, and 97 cost the fifth)
     if (K <= 32 && L <= 32 && mb == 1 && nj == 1 && rg > 1 && rg * ns == 4) return 5;
+    // (plain chains, (1,4,2,2): two blocks of eight waves; 125 to 134 registers when not told, and more than 128 cost the second: 96 x
+    // [512,32].[32,512].[512,32] 7.4 us with it, 9.1 without)
+    if (!softmax && mb == 1 && nj == 2 && rg == 4 && ns == 2) return 4;
     return pipe_waves_with(K, L, mb, rg, ns, nj, P, reference_stands(K, L, mb, rg, ns, nj, softmax, P));
 }
 // The rings of a pipelined kernel, where they cost none of the blocks that the registers let a compute unit hold.  The first D tile
@@ -208,14 +214,15 @@ constexpr PipeRing pipe_ring(int K, int L, int mb, int rg, int ns, int nj, bool 
 }
 // Whether an arrangement is pipelined (P: columns of F, 0 without a third GEMM): where it fits the LDS of a compute unit and its
 // registers (blocks of four waves: the half of the file that vector instructions reach, and a little of the other; beyond that
-// they spill).  The softmax loop of the others runs the phases one after the other, see skewed_groups.
+// they spill, but for L of 64 and fewer, which stay within the file: 32 x 2048 x 2048, K = L = 64, (2,4,1,2) 53.6 us pipelined, 57.9 not,
+// (2,2,2,2) 59.7 and 64.2; K = 128, L = 64, (2,4,1,2) 67 - 70 and 71.4).  The softmax loop of the others runs the phases one after the other, see skewed_groups.
 constexpr bool pipelined(int K, int L, int mb, int rg, int ns, int nj, bool softmax, bool ksplit, int P) {
     if (ksplit) return false;
     // plain chains: only where K and L are 32, in blocks of 8 waves that own at most two row sets
     // each (measured on 16 x [4096,32].[32,1024].[1024,32]: 3-4 % faster for (1,8,1,2) and (2,4,2,2),
     // no change for (1,4,2,2), a third slower for (4,2,4,1); with K = L = 64 slower throughout)
     if (!softmax && !(K <= 32 && L <= 32 && mb <= 2 && rg * ns == 8)) return false;
-    if (softmax && pipe_needs(K, L, mb, nj) > (rg * ns > 4 ? 256 : 320)) return false;
+    if (softmax && pipe_needs(K, L, mb, nj) > (rg * ns > 4 ? 256 : L <= 64 ? 364 : 320)) return false;
     return pipe_lds_least(K, L, mb, rg, ns, nj, P, reference_stands(K, L, mb, rg, ns, nj, softmax, P)) <= 2 * kLdsRingBudget;
 }
 // Softmax chains that cannot be pipelined, in blocks of 8 waves, run their two wave groups a

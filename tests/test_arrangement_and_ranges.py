@@ -5,7 +5,7 @@ import random
 import pytest
 
 import paper_2506_22169_amd as mcf
-from paper_2506_22169_amd.binding import call_tiles, list_candidates, make_problem
+from paper_2506_22169_amd.binding import call_tiles, eval_tiles, list_candidates, make_problem
 
 
 def _ran(b, M, K, N, L, causal=False, dtype="bf16", off=None, **kw):
@@ -63,6 +63,24 @@ def test_arrangement_of_many_plain_blocks(call, tm):
     p = make_problem(*call, "bf16")
     t, ranges = call_tiles(p, False)
     assert ranges == 1 and t.scratch_bytes == 0 and t.blocks > 128 and tm in (t.tm, None)
+
+
+# registers: what lets a compute unit hold two blocks of four waves (256) or of eight (128)
+@pytest.mark.parametrize("tiles,softmax,registers", [((1, 4, 1, 4), True, 256), ((2, 4, 1, 2), True, 256), ((2, 2, 2, 2), True, 256),
+                                                     ((2, 4, 2, 2), True, 256), ((1, 4, 2, 2), False, 128), ((1, 8, 1, 2), False, 128)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_kernels_of_32_keep_their_blocks(tiles, softmax, registers, dtype):
+    p = make_problem(96, 512, 32, 512, 32, dtype, b_stride=(512 * 32, 1, 32) if softmax else None)
+    t = eval_tiles(p, *tiles, softmax=softmax)
+    assert t.vgpr_used <= registers and t.scratch_bytes == 0 and t.stages == 2
+
+
+@pytest.mark.parametrize("K,L,tiles", [(64, 64, (2, 4, 1, 2)), (64, 64, (2, 2, 2, 2)), (128, 64, (2, 4, 1, 2)), (32, 32, (4, 1, 4, 1)),
+                                       (32, 32, (4, 2, 2, 1))])
+def test_pipelined_where_the_registers_hold_it(K, L, tiles):
+    """Rings of their own for B and D (stages 2), which these ran before more than 320 estimated registers were refused, and without spills."""
+    t = eval_tiles(make_problem(32, 2048, K, 2048, L, "f16", b_stride=(2048 * K, 1, K)), *tiles, softmax=True)
+    assert t.stages == 2 and t.scratch_bytes == 0
 
 
 @pytest.mark.parametrize("call,kind,ranges", [
