@@ -8,6 +8,11 @@ import paper_2506_22169_amd as mcf
 from paper_2506_22169_amd.binding import call_tiles, eval_tiles, list_candidates, make_problem
 
 
+def _feasible(t, p, softmax):
+    """Built, within LDS and registers, no spills in loops.  (Not always a candidate of the picker, which also asks that a tile pads little.)"""
+    return eval_tiles(p, t.mb, t.rg, t.ns, t.nj, tl=t.tl, softmax=softmax).feasible
+
+
 def _ran(b, M, K, N, L, causal=False, dtype="bf16", off=None, **kw):
     p = make_problem(b, M, K, N, L, dtype, b_stride=(N * K, 1, K))
     t, ranges = call_tiles(p, True, causal_offset=(N - M if off is None else off) if causal else None, **kw)
@@ -32,7 +37,7 @@ def test_arrangement_of_many_blocks(call, run):
 
 
 def test_what_is_left_alone():
-    """Calls of 128 blocks and fewer (n may be split), given tiles, T_L < L; and an arrangement that is taken in their place is a candidate
+    """Calls of 128 blocks and fewer (n may be split), given tiles, T_L < L; and an arrangement that is taken in their place is feasible and one
     that leaves more than 128 blocks, for any size and offset."""
     rng = random.Random(4)
     moved = 0
@@ -47,22 +52,49 @@ def test_what_is_left_alone():
             assert (t.mb, t.rg) == (q.mb, q.rg) and t.blocks == q.blocks
         elif t.blocks != q.blocks:
             moved += 1
-            assert t.blocks > 128 and ranges == 1 and t.tl == K and t.scratch_bytes == 0
+            assert t.blocks > 128 and ranges == 1 and t.tl == K and t.scratch_bytes == 0 and _feasible(t, p, True)
         given = list_candidates(p, True)[0]
         assert _ran(b, M, K, N, K, causal, off=off, tiles=(given.mb, given.rg, given.ns, given.nj, given.tl))[0][:4] == (given.mb, given.rg, given.ns, given.nj)
     assert moved > 50
 
 
+def test_what_plain_calls_move_to():
+    """The same of plain chains, whose T_L may change with the arrangement."""
+    rng = random.Random(5)
+    moved = other_tl = 0
+    for _ in range(1500):
+        K, L = rng.choice([(32, 32), (64, 64), (64, 128), (64, 256), (128, 64), (96, 96), (192, 192), (256, 256)])
+        b, M, N = rng.randint(1, 100), rng.choice([64, 333, 1000, rng.randint(1, 4000)]), 8 * rng.randint(1, 400)
+        p = make_problem(b, M, K, N, L, rng.choice(["f16", "bf16"]))
+        t, ranges = call_tiles(p, False)
+        q = mcf.pick_tiles(p, False)
+        if q.blocks <= 128:
+            assert t.blocks == q.blocks and t.tl == q.tl
+        elif t.blocks != q.blocks:
+            moved += 1
+            other_tl += t.tl != q.tl
+            assert t.blocks > 128 and ranges == 1 and t.scratch_bytes == 0 and L % t.tl == 0 and _feasible(t, p, False)
+    assert moved > 50 and other_tl > 5
+
+
+# decode calls of more blocks than compute units; us: the pick's time, the time of what runs
+@pytest.mark.parametrize("b,M,K,N,run,us", [(1024, 1, 128, 2048, (1, 2, 2, 1), (189.4, 178.6)), (512, 4, 64, 4096, (1, 2, 2, 1), (97.6, 88.4)),
+                                            (512, 1, 96, 4096, (1, 2, 2, 1), (136.2, 136.2)), (1024, 1, 64, 2048, (1, 2, 2, 2), (97.1, 94.4))])
+def test_decode_calls_of_many_blocks(b, M, K, N, run, us):
+    got, ranges, t, _ = _ran(b, M, K, N, K)
+    assert got == run + (K,) and ranges == 1 and t.blocks == b
+
+
 @pytest.mark.parametrize("call,tm", [
     ((51, 715, 32, 744, 32), 256),                    # 1173 blocks of 32 rows: 15.3 -> 8.2 - 8.8 us
-    ((92, 3264, 64, 128, 128), None),
+    ((92, 3264, 64, 128, 128), 256),
     ((64, 512, 64, 512, 64), 128),
     ((16, 4096, 32, 1024, 32), 256),
 ])
 def test_arrangement_of_many_plain_blocks(call, tm):
     p = make_problem(*call, "bf16")
     t, ranges = call_tiles(p, False)
-    assert ranges == 1 and t.scratch_bytes == 0 and t.blocks > 128 and tm in (t.tm, None)
+    assert ranges == 1 and t.scratch_bytes == 0 and t.blocks > 128 and t.tm == tm
 
 
 # registers: what lets a compute unit hold two blocks of four waves (256) or of eight (128)

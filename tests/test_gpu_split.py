@@ -134,6 +134,32 @@ def test_calls_without_tiles_match_the_oracle(case):
         assert np.max(np.abs(got - ref)) <= TOL * np.max(np.abs(ref))
 
 
+# calls of more than 128 blocks that run another arrangement, one with another T_L, than the model's pick
+MOVED = [("plain", 22, 765, 64, 152, 256, "bf16"), ("plain", 8, 897, 64, 384, 256, "f16"), ("softmax", 37, 409, 96, 124, 96, "bf16"),
+         ("softmax", 133, 80, 64, 363, 64, "f16"), ("softmax", 300, 4, 64, 1096, 64, "bf16"), ("causal", 43, 352, 96, 252, 96, "bf16"),
+         ("causal", 96, 283, 192, 122, 192, "f16")]
+
+
+@pytest.mark.parametrize("case", MOVED, ids=str)
+def test_calls_of_many_blocks_match_the_oracle(case):
+    kind, b, M, K, N, L, dtype = case
+    softmax, off = kind != "plain", N - M
+    w = mi.make_problem(b, M, K, N, L, dtype, softmax, "normal" if softmax else "uniform", seed=9180 + N)
+    x = mi.make_inputs(w)
+    A, B, D = device_inputs(w, x)
+    problem = binding.make_problem(b, M, K, N, L, dtype, b_stride=(N * K, 1, K) if softmax else None)
+    t, ranges = mcf.call_tiles(problem, softmax, causal_offset=off if kind == "causal" else None)
+    q = mcf.pick_tiles(problem, softmax)
+    assert ranges == 1 and (t.mb, t.rg, t.ns, t.nj, t.tl) != (q.mb, q.rg, q.ns, q.nj, q.tl)
+    print("case moved", case, (t.mb, t.rg, t.ns, t.nj, t.tl), flush=True)
+    if kind == "causal":
+        E, ref = mcf.causal_softmax_gemm_chain(A, B, D, w.scale, off), oracle.chain_causal(x["A"], x["B"], x["D"], scale=w.scale, causal_offset=off)
+    else:
+        E = mcf.softmax_gemm_chain(A, B, D, w.scale) if softmax else mcf.gemm_chain(A, B, D)
+        ref = oracle.chain(x["A"], x["B"], x["D"], softmax=softmax, scale=w.scale)
+    assert np.max(np.abs(to_host64(E, dtype) - ref)) <= TOL * np.max(np.abs(ref))
+
+
 @pytest.mark.parametrize("b,M,K,N,off", [(32, 1, 128, 8192, 5000), (3, 70, 64, 6000, 4000), (2, 33, 96, 4097, 4096 - 32), (9, 200, 64, 5000, 2049)])
 def test_ranges_end_with_what_a_mask_leaves(b, M, K, N, off):
     """Ranges that the library chooses under a mask stop at the columns the last row sees."""
