@@ -1360,7 +1360,7 @@ void chain_kernel(const KParams p) {
         const int x4 = i16 & 3;
         const int frow = 16 * g + (i16 >> 2); // + 32 hb + 8 qp; upper four contraction indices: + 4 rows
         const int fch = (u16 + 2 * (x4 & 1)) ^ swz_tr(RBF, frow);
-        const unsigned f_off = (unsigned)(F_LDS + frow * RBF + 16 * fch + 8 * (x4 >> 1)); // p block 0; per pb: ^ (64 pb) bytes
+        const unsigned f_off = (unsigned)(F_LDS + frow * RBF + 16 * fch + 8 * (x4 >> 1)); // p block 0
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -1373,7 +1373,7 @@ void chain_kernel(const KParams p) {
             for (int hb = 0; hb < HB; ++hb)
 #pragma unroll
                 for (int qp = 0; qp < 2; ++qp) {
-                    const lds_u8 *src = smem + (f_off ^ (unsigned)(64 * pb)) + (32 * hb + 8 * qp) * RBF;
+                    const lds_u8 *src = smem + (f_off ^ (unsigned)tr_block_xor(RBF, pb)) + tr_block_add(RBF, pb) + (32 * hb + 8 * qp) * RBF;
                     i16x4 lo = lds_read_tr(src);
                     i16x4 hi = lds_read_tr(src + 4 * RBF);
                     const v8 fop = __builtin_bit_cast(v8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));

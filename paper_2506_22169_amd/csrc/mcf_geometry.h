@@ -33,6 +33,9 @@ constexpr int swz_tr(int row_bytes, int row) {
     default: return 4 * (row & 3);
     }
 }
+// Address of 64-byte block `block` of a row from that of the row's block 0: an XOR within a span, an addition beyond it.
+constexpr int tr_block_xor(int row_bytes, int block) { return 64 * (block % (swz_span(row_bytes) / 64)); }
+constexpr int tr_block_add(int row_bytes, int block) { return block / (swz_span(row_bytes) / 64) * swz_span(row_bytes); }
 
 // Pitch of the LDS rows in elements (K a multiple of 16, L of 8): rows of whole 64-byte groups lie as they are; others (80)
 // take the next power of two, and the chunks beyond K or L in a row are loaded from valid memory and never reach a

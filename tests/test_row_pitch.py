@@ -1,5 +1,8 @@
 """LDS rows of K, L that are multiples of 32 but no powers of two lie at their own pitch (96: 192 bytes, 160: 320, 192: 384), with
 the swizzle inside the largest power of two that divides it; K = 256 spans two swizzle periods."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -21,6 +24,33 @@ def test_two_slices_where_they_pad_little(N, nj):
         assert ranges == 1 and t.nj == (2 if 8 * (-N % 64) <= N else 1) == nj, (K, N)
     t, _ = call_tiles(make_problem(40, 1000, 96, 776, 96, "bf16"))
     assert (t.mb, t.rg, t.ns, t.nj) == (1, 8, 1, 2)
+
+
+BLOCKS = """
+#include <initializer_list>
+
+#include "mcf_geometry.h"
+using namespace mcf;
+int main() {
+    for (int rb : {64, 128, 192, 256, 320, 384, 512})
+        for (int row = 0; row < 64; ++row)
+            for (int u = 0; u < 4; ++u)
+                for (int block = 0; block < rb / 64; ++block) {
+                    const int first = row * rb + 16 * (u ^ swz_tr(rb, row)), want = row * rb + 16 * ((4 * block + u) ^ swz_tr(rb, row));
+                    if ((first ^ tr_block_xor(rb, block)) + tr_block_add(rb, block) != want) return 1;
+                    if (swz_tr(rb, row) != swz_tr(rb, row + 4)) return 2;
+                }
+    return 0;
+}
+"""
+
+
+def test_blocks_of_a_row_for_every_pitch(tmp_path):
+    """The third GEMM's reads of F find every 64-byte block of a row where the loads have put it, also for pitches that no kernel has."""
+    (tmp_path / "blocks.cpp").write_text(BLOCKS)
+    csrc = os.path.join(os.path.dirname(os.path.abspath(mcf.__file__)), "csrc")
+    subprocess.run(["g++", "-std=c++17", "-I", csrc, str(tmp_path / "blocks.cpp"), "-o", str(tmp_path / "blocks")], check=True)
+    assert subprocess.run([str(tmp_path / "blocks")]).returncode == 0
 
 
 @pytest.mark.gpu
