@@ -78,8 +78,9 @@ typedef struct mcf_tiles {
     int32_t mb, rg, ns, nj;   /* 32-row blocks per wave, wave row-groups, waves across n,        */
                               /* 32-column slices per wave and n-iteration (0 reads as 1)        */
     int32_t waves;            /* rg * ns, 64 lanes each                                          */
-    int32_t stages;           /* depth of the LDS ring of (B tile + D tile) buffers, 2..4; 2 also where B and D have rings of their own (softmax pipeline) */
-    int32_t lds_bytes;        /* eq. (1) restricted to the tiles held in LDS (B, D; x stages)    */
+    int32_t stages;           /* depth of the LDS ring of (B tile + D tile) buffers, 2..4; 2 stands for the rings of  */
+                              /* their own that B (two to four tiles) and D (two or three) have in pipelined kernels  */
+    int32_t lds_bytes;        /* LDS of a block: the ring or rings, or what borrows their space; with F's tile        */
     int32_t vgpr_est;         /* eq. (1) restricted to the tiles held in registers (A, C, E)     */
     int32_t vgpr_used;        /* registers per lane the compiler allocated for this variant      */
     int32_t scratch_bytes;    /* per-lane spill space of a variant whose loops spill registers   *

@@ -371,7 +371,8 @@ void chain_kernel(const KParams p) {
     using Yes = std::true_type;
     using No = std::false_type;
     // Rows of D beyond N of the ragged tile t become zeros.  Every wave clears what it has loaded itself, between its wait
-    // for it and the barrier that hands the tile to the others: no barrier of its own.
+    // for it and the barrier that hands the tile to the others: no barrier of its own.  (40 x 333 x 1357, causal, K = L = 80, which ends in
+    // a ragged tile: 18.0 us without, 18.5 with it; 96 x 512 x 512, K = L = 64, which does not: 12.66 and 12.80.)
     auto clear_beyond = [&](int t, unsigned d_slot) __attribute__((always_inline)) {
         int l; // the lane, formed here: no register holds it through the loop
         asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));

@@ -172,9 +172,10 @@ static int64_t visible_columns(int64_t M, int64_t N, int64_t tm, int64_t off, in
 // Time of a chain in us from how many blocks a compute unit holds, which the model's estimate does not see: its units
 // take their blocks in rounds of as many as LDS and registers let them hold, a round lasts as long as the
 // matrix and vector work of its blocks at the rate that their waves reach together, or as its n-tiles take whatever their width,
-// and ends with a fill and a drain; and no call is faster than its bytes.
-// Under a mask (off: its offset) a call takes as long as its longest block at least.  Constants fitted to calls drawn from the
-// ranges of the chains with 129 blocks or more: 419 softmax chains in nine arrangements, 312 plain ones in fourteen and T_L.
+// and ends with a fill and a drain; and no plain call is faster than its bytes (softmax calls are, by this estimate: decode calls of one
+// m-tile that it moves take 0.80 to 1.00 of the pick's time all the same).
+// Under a mask (off: its offset) a call takes as long as its longest block at least.  Constants fitted to 419 softmax chains in nine
+// arrangements and 312 plain ones in fourteen and T_L, drawn with 129 blocks or more.
 struct TimeFit {
     double mac, column, ends, first, tile, bytes_per_us;
     double rate[4]; // of 1 to 4 waves a SIMD, against two
@@ -216,8 +217,9 @@ static double chain_time(const TimeFit &fit, const mcf_problem *p, const Built *
 }
 // A call that n is not split for (more blocks than half the compute units): another arrangement where that is a tenth faster at
 // least by chain_time (softmax chains: of whole L); a fifth where the rules of settle_tiles have acted, whose arrangements it underrates (128 x
-// [2881,128].[128,976].[976,128]: 1.19 by chain_time, 1.10 measured).  Calls that were not in the fit's first half, against the pick: 279 softmax chains 0.42
-// to 1.08 of the time (0.96 in the mean), 140 under a mask 0.64 to 1.10 (0.98), 129 plain ones 0.51 to 1.00 (0.93).
+// [2881,128].[128,976].[976,128]: 1.19 by chain_time, 1.10 measured).  Rule 3 (padding) is left aside.  Calls outside the fit whose arrangement is not the
+// model's pick, against that: 220 softmax chains 0.35 to 1.09 of the time (0.76 in the mean), 250 under a mask 0.27 to 1.43 (0.79; 13 of them more
+// than 3 % longer), 60 plain ones 0.43 to 1.03 (0.80).
 static void settle_many(const mcf_problem *p, int softmax, int b_kcontig, const int64_t *off, bool settled, mcf_tiles *t) {
     struct Cost { int mb, rg, ns, nj; double cost; }; // of a column of an m-tile, against each other
     static const Cost kSoftmax[] = {{1, 8, 1, 2, 0.88}, {1, 8, 1, 1, 1.00}, {1, 4, 1, 2, 0.92}, {1, 4, 1, 1, 1.01}, {1, 4, 2, 2, 0.98},

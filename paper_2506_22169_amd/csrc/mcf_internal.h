@@ -122,7 +122,8 @@ void describe(Built *v);
 int pick_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *out);
 int eval_tiles(const mcf_problem *p, int softmax, int b_kcontig, mcf_tiles *t);
 void eval_model(const mcf_problem *p, const Built *v, mcf_tiles *t);
-bool better(const mcf_tiles &a, const mcf_tiles &b, int softmax, int64_t K, int extra = 0); // extra: LDS of the F tile // the picker's order: estimate, then the tie-breaks
+// The picker's order: estimate, then the tie-breaks (extra: LDS of the F tile of a three-GEMM chain).
+bool better(const mcf_tiles &a, const mcf_tiles &b, int softmax, int64_t K, int extra = 0);
 int vgpr_estimate(int K, int L, int mb, int rg, int ns, int nj, int softmax, int ksplit);
 
 // Feasible candidates for a problem, with their model terms, in registry order (the set

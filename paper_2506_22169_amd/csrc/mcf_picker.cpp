@@ -13,13 +13,13 @@
 //     m-tiles of a batch at the L2 bandwidth, because on MI355X they are served by the XCD's
 //     L2 / the memory-side cache, not by HBM.
 //   * eq. (1) sums all five tiles against shared memory.  Here C and E (and A) live in
-//     registers, so the sum is split: B and D tiles (two stages, padded rows) against the
+//     registers, so the sum is split: the rings of B and D tiles against the
 //     160 KiB LDS, and A, C, E tiles against the share of the 512-entry VGPR file a lane gets.
 //     The LDS figure is exact and the register figure is backed by the compiler's own
 //     allocation (a variant that spills is never picked), so the 1.2x slack of Rule 4 is not
 //     applied.  The LDS
 //     holds a ring of 2..4 (B tile + D tile) stages, as deep as fits 80 KiB so that two
-//     blocks share a compute unit.
+//     blocks share a compute unit, or in pipelined kernels a ring of B tiles and one of D tiles.
 //   * eq. (5) counts parallel work against parallel hardware, alpha = (N_block + N_SM) / N_block.
 //     Here blocks run in rounds: a compute unit has four SIMDs, a block takes min(waves, 4) of
 //     them (a block of 8 or 16 waves owns the unit like one of 4), a launch takes
@@ -121,8 +121,11 @@ void eval_model(const mcf_problem *p, const Built *v, mcf_tiles *t) {
 
 // Strict ordering of candidates: smaller estimate first; among equal estimates (the model
 // does not see how the waves of a block are arranged) more waves per block, then a block
-// whose LDS leaves room for a second one on the compute unit (softmax: counted as a ring of four whole tiles), then fewer waves across n (less
+// whose LDS leaves room for a second one on the compute unit, then fewer waves across n (less
 // to combine), then more column slices per wave, then fewer rows per wave.
+// The LDS of a softmax arrangement is counted as a ring of four whole B + D tiles, which pipelined kernels no longer have: an arbitrary
+// order, which keeps the picks of that ring.  By their own LDS bytes 59 drawn calls whose pick differs take 0.59 to 1.23 of the time (0.92 in
+// the mean; 11 of them more than 3 % longer).
 static bool two_resident(const mcf_tiles &t, int softmax, int64_t K, int extra) {
     const int lds = softmax && t.tk == K ? total_lds_bytes(t.tk, t.tl, t.mb, t.rg, t.ns, t.nj, 4) : t.lds_bytes;
     return 2 * (softmax ? lds + extra : lds) <= kLdsBytesPerBlock;

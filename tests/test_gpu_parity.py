@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("KL", [(32, 32), (64, 64), (128, 128), (64, 128), (128, 64), (64, 256), (256, 256),
                                 (256, 64), (384, 128), (512, 256),    # these three: k loop inside the block
-                                (80, 80), (96, 96), (160, 160), (192, 192)])   # rows padded to a power-of-two pitch in LDS
+                                (80, 80), (96, 96), (160, 160), (192, 192)])   # rows of 80 padded to a pitch of 128 in LDS
 def test_every_variant_small_ragged(KL, dtype, softmax):
     """Every built wave arrangement on a shape with a ragged m tail and a ragged n tail that
     spans several tiles of the largest variant (tm up to 256, tn up to 256)."""
